@@ -186,26 +186,121 @@ __device__ __forceinline__ long long xcd_item(int b, int j, int grid, long long 
     return t < nitems ? t : -1;
 }
 
-__device__ __forceinline__ double wave_sum(double v)
+// ---- FP64 sums over a wavefront --------------------------------------------
+// NQ sums are reduced together: at each of the six levels of the lane tree
+// (lane pairs 32, 16, 8, 4, 2, 1 apart) the lanes of a pair exchange one half
+// of the sums each, so a level halves the number of sums a lane holds.  13
+// sums take 16 additions and 19 exchanges instead of the 78 of each a full
+// butterfly per sum takes; the additions that form any one sum, and their
+// order, are those of the butterfly.
+
+// Value of the lane 2^BIT away.
+template <int BIT>
+__device__ __forceinline__ double lane_pair(double v)
 {
+    const long long b = __double_as_longlong(v);
+    int lo = (int)(b & 0xffffffffLL), hi = (int)(b >> 32);
+    if constexpr (BIT == 3) {          // rotate by 8 within 16 lanes
+        lo = __builtin_amdgcn_update_dpp(0, lo, 0x128, 0xF, 0xF, false);
+        hi = __builtin_amdgcn_update_dpp(0, hi, 0x128, 0xF, 0xF, false);
+    } else if constexpr (BIT == 2) {   // mirror 8 lanes, then mirror 4
+        lo = __builtin_amdgcn_update_dpp(0, lo, 0x141, 0xF, 0xF, false);
+        hi = __builtin_amdgcn_update_dpp(0, hi, 0x141, 0xF, 0xF, false);
+        lo = __builtin_amdgcn_update_dpp(0, lo, 0x1B, 0xF, 0xF, false);
+        hi = __builtin_amdgcn_update_dpp(0, hi, 0x1B, 0xF, 0xF, false);
+    } else if constexpr (BIT == 1) {
+        lo = __builtin_amdgcn_update_dpp(0, lo, 0x4E, 0xF, 0xF, false);
+        hi = __builtin_amdgcn_update_dpp(0, hi, 0x4E, 0xF, 0xF, false);
+    } else {
+        static_assert(BIT == 0, "wider pairs use the lane swaps");
+        lo = __builtin_amdgcn_update_dpp(0, lo, 0xB1, 0xF, 0xF, false);
+        hi = __builtin_amdgcn_update_dpp(0, hi, 0xB1, 0xF, 0xF, false);
+    }
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Lanes with bit BIT clear: a plus the pair lane's a; lanes with it set: the
+// same of b.
+template <int BIT>
+__device__ __forceinline__ double pair_add(double a, double b)
+{
+    if constexpr (BIT >= 4) {
+        const long long ab = __double_as_longlong(a), bb = __double_as_longlong(b);
+        const unsigned alo = (unsigned)(ab & 0xffffffffLL), ahi = (unsigned)(ab >> 32);
+        const unsigned blo = (unsigned)(bb & 0xffffffffLL), bhi = (unsigned)(bb >> 32);
+        unsigned l0, l1, h0, h1;
+        if constexpr (BIT == 5) {
+            const auto l = __builtin_amdgcn_permlane32_swap(alo, blo, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(ahi, bhi, false, false);
+            l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+        } else {
+            const auto l = __builtin_amdgcn_permlane16_swap(alo, blo, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap(ahi, bhi, false, false);
+            l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+        }
+        return __longlong_as_double(((long long)h0 << 32) | l0) + __longlong_as_double(((long long)h1 << 32) | l1);
+    } else {
+        const bool up = (__lane_id() >> BIT) & 1;
+        const double keep = up ? b : a, send = up ? a : b;
+        return keep + lane_pair<BIT>(send);
+    }
+}
+
+template <int BIT, int N, int K>
+__device__ __forceinline__ double tree_sum(double (&v)[K])
+{
+    if constexpr (BIT < 0) {
+        static_assert(N == 1, "six levels take up to 64 sums");
+        return v[0];
+    } else if constexpr (N == 1) {
+        v[0] = BIT >= 4 ? pair_add<(BIT >= 4 ? BIT : 4)>(v[0], v[0]) : v[0] + lane_pair<(BIT < 4 ? BIT : 0)>(v[0]);
+        return tree_sum<BIT - 1, 1>(v);
+    } else {
+        constexpr int H = (N + 1) / 2;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+        for (int j = 0; j < H; j++) v[j] = pair_add<BIT>(v[j], j + H < N ? v[j + H] : v[j]);
+        return tree_sum<BIT - 1, H>(v);
+    }
+}
+
+// Which sum a lane holds after tree_sum<5, NQ> (-1: a copy of no use).
+template <int NQ>
+__device__ __forceinline__ int tree_index()
+{
+    int n[6], h[6];
+    int m = NQ;
+#pragma unroll
+    for (int l = 0; l < 6; l++) {
+        n[l] = m;
+        h[l] = m == 1 ? 0 : (m + 1) / 2;
+        m = (m + 1) / 2;
+    }
+    const int lane = __lane_id();
+    int q = 0;
+    bool ok = true;
+#pragma unroll
+    for (int l = 5; l >= 0; l--) {
+        const int bit = (lane >> (5 - l)) & 1;
+        if (n[l] == 1)
+            ok &= bit == 0;   // one writer per sum
+        else
+            q += bit * h[l];
+        ok &= q < n[l];
+    }
+    return ok ? q : -1;
 }
 
 // Sum acc[0..NQ) over the block (blockDim.x a multiple of 64, red holding
-// one row per wave); the totals land in red[0][q].  Fixed order.
+// one row per wave); the totals land in red[0][q].  Fixed order: the lane
+// tree within a wave, then the waves in order.
 template <int NQ>
 __device__ __forceinline__ void block_sum(double (&acc)[NQ], double (*red)[kMaxSums])
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wave = threadIdx.x >> 6;
     const int nwaves = blockDim.x >> 6;
-#pragma unroll
-    for (int q = 0; q < NQ; q++) acc[q] = wave_sum(acc[q]);
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < NQ; q++) red[wave][q] = acc[q];
-    }
+    const double v = tree_sum<5, NQ>(acc);
+    const int q = tree_index<NQ>();
+    if (q >= 0) red[wave][q] = v;
     __syncthreads();
     if (threadIdx.x < NQ) {
         double s = red[0][threadIdx.x];
@@ -221,68 +316,150 @@ __device__ __forceinline__ double round_to_storage(double v)
     return (double)(T)v;
 }
 
-// a^k for an integer k (|k| <= 8), by repeated multiplication or division.
-__device__ __forceinline__ double int_power(double a, int k)
+// a^k, k = -4..3, formed by repeated multiplication or division: what a
+// polynomial term of degree 4 - k is scaled with.
+struct Powers {
+    double p[4], m[5];   // a^0..a^3, a^0..a^-4
+};
+__device__ __forceinline__ Powers powers_of(double a)
 {
-    double r = 1.0;
-    for (int j = 0; j < k; j++) r *= a;
-    for (int j = 0; j < -k; j++) r /= a;
-    return r;
+    Powers w;
+    w.p[0] = w.m[0] = 1.0;
+#pragma unroll
+    for (int j = 1; j < 4; j++) w.p[j] = w.p[j - 1] * a;
+#pragma unroll
+    for (int j = 1; j < 5; j++) w.m[j] = w.m[j - 1] / a;
+    return w;
+}
+__device__ __forceinline__ double power(const Powers &w, int k)
+{
+    switch (k) {   // uniform: k comes from the model
+    case 3: return w.p[3];
+    case 2: return w.p[2];
+    case 1: return w.p[1];
+    case -1: return w.m[1];
+    case -2: return w.m[2];
+    case -3: return w.m[3];
+    case -4: return w.m[4];
+    default: return 1.0;
+    }
+}
+static_assert(CE_MAX_DEGREE == 8, "powers_of covers degrees 1..8");
+
+// The scalar state a tail reads and writes, held in registers: one lattice's
+// a(t) and homogeneous references at step n, with the coefficients of the
+// next pass derived from them.
+template <int NF>
+struct RunState {
+    double a, a_next, adot_half, beta, tau;
+    long long step, first_bad;
+    double m[NF], fdot_mean[NF], r[NF];
+};
+
+// Scalar loads, all independent: the state is the same for every lane, and
+// no kernel that calls this changes it before its tail.
+template <int NF>
+__device__ __forceinline__ RunState<NF> load_state(const Lattice &lat)
+{
+    const auto *sc = (const __attribute__((address_space(4))) Scalars *)lat.sc;
+    RunState<NF> s;
+    s.a = sc->a;
+    s.a_next = sc->a_next;
+    s.adot_half = sc->adot_half;
+    s.beta = sc->beta;
+    s.tau = sc->tau;
+    s.step = sc->step;
+    s.first_bad = sc->first_bad;
+#pragma unroll
+    for (int i = 0; i < NF; i++) {
+        s.m[i] = sc->m[i];
+        s.fdot_mean[i] = sc->fdot_mean[i];
+        s.r[i] = sc->r[i];
+    }
+    return s;
 }
 
-template <typename T>
-__device__ __forceinline__ void fill_pass_scalars(PassScalars<T> &ps, const Scalars *sc, const Lattice &lat,
-                                                  double a1)
+// Coefficients of the pass that follows state s, in the storage type.
+template <typename T, int NF>
+__device__ __forceinline__ void fill_pass_scalars(PassScalars<T> &ps, const RunState<NF> &s, const Lattice &lat,
+                                                  const Powers &w)
 {
-    const double a2 = a1 * a1;
-    ps.beta = (T)sc->beta;
+    const double a2 = s.a_next * s.a_next;
+    ps.beta = (T)s.beta;
+#pragma unroll
     for (int i = 0; i < kMaxFields; i++) {
-        const bool on = i < lat.nf;
-        ps.bm[i] = on ? (T)(sc->beta * sc->m[i]) : (T)0;
-        ps.r[i] = on ? (T)sc->r[i] : (T)0;
-        ps.m1[i] = on ? (T)sc->nx_m1[i] : (T)0;
-        ps.m2a[i] = on ? (T)(a2 * lat.mu2[i]) : (T)0;
-        ps.hm[i] = on ? (T)(0.5 * a2 * lat.mu2[i]) : (T)0;
+        if (i < NF) {
+            const int k = i < NF ? i : 0;
+            ps.bm[i] = (T)(s.beta * s.m[k]);
+            ps.r[i] = (T)s.r[k];
+            ps.m1[i] = (T)(s.m[k] + lat.dt * s.r[k]);
+            ps.m2a[i] = (T)(a2 * lat.mu2[i]);
+            ps.hm[i] = (T)(0.5 * a2 * lat.mu2[i]);
+        } else {
+            ps.bm[i] = ps.r[i] = ps.m1[i] = ps.m2a[i] = ps.hm[i] = (T)0;
+        }
     }
     // a term of degree D of the physical potential is coef a^(4 - D) in the
     // program variables
+#pragma unroll
     for (int t = 0; t < kMaxTerms; t++)
-        ps.tc[t] = t < lat.nterms ? (T)(lat.tcoef[t] * int_power(a1, 4 - lat.tdeg[t])) : (T)0;
+        ps.tc[t] = t < lat.nterms ? (T)(lat.tcoef[t] * power(w, 4 - lat.tdeg[t])) : (T)0;
 }
 
-// Derive the next step pass's coefficients from the scalar state (one thread).
-__device__ __forceinline__ void publish_next_pass(const Lattice &lat, Scalars *sc)
-{
-#pragma clang fp contract(off)
-    const double a2 = sc->a_next * sc->a_next;
-    for (int i = 0; i < kMaxFields; i++) {
-        const bool on = i < lat.nf;
-        sc->nx_m1[i] = on ? sc->m[i] + lat.dt * sc->r[i] : 0.0;
-        sc->nx_hm[i] = on ? 0.5 * a2 * lat.mu2[i] : 0.0;
-    }
-    fill_pass_scalars(sc->nxf, sc, lat, sc->a_next);
-    fill_pass_scalars(sc->nxd, sc, lat, sc->a_next);
-}
-
-// FP64 tail after a step pass n -> n+1 (one thread).  Sums of field i at
-// 6i: sum d, sum d^2, sum d Lap d, sum ubar^2, sum ubar, sum ubar d, all at
-// n+1, with ubar = (fdot^{n+1/2} + p^{n+3/2})/2; last: sum V.
-template <typename T>
-__device__ __forceinline__ void step_tail(const Lattice &lat, const double *tot)
+// Store state s and the next pass's coefficients (one thread).
+template <int NF>
+__device__ __forceinline__ void store_state(const Lattice &lat, const RunState<NF> &s)
 {
 #pragma clang fp contract(off)
     Scalars *sc = lat.sc;
+    sc->a = s.a;
+    sc->a_next = s.a_next;
+    sc->adot_half = s.adot_half;
+    sc->beta = s.beta;
+    sc->tau = s.tau;
+    sc->step = s.step;
+    sc->first_bad = s.first_bad;
+    const double a2 = s.a_next * s.a_next;
+#pragma unroll
+    for (int i = 0; i < kMaxFields; i++) {
+        const int k = i < NF ? i : 0;
+        if (i < NF) {
+            sc->m[i] = s.m[k];
+            sc->fdot_mean[i] = s.fdot_mean[k];
+            sc->r[i] = s.r[k];
+        }
+        sc->nx_m1[i] = i < NF ? s.m[k] + lat.dt * s.r[k] : 0.0;
+        sc->nx_hm[i] = i < NF ? 0.5 * a2 * lat.mu2[i] : 0.0;
+    }
+    Powers w;
+    if (lat.nterms > 0) w = powers_of(s.a_next);
+    fill_pass_scalars<float, NF>(sc->nxf, s, lat, w);
+    fill_pass_scalars<double, NF>(sc->nxd, s, lat, w);
+}
+
+// FP64 tail after a step pass n -> n+1: s goes from step n to n+1, e receives
+// the diagnostics.  tot: sums of field i at 6i: sum d, sum d^2, sum d Lap d,
+// sum ubar^2, sum ubar, sum ubar d, all at n+1, with
+// ubar = (fdot^{n+1/2} + p^{n+3/2})/2; last: sum V.  The chain of dependent
+// divisions is the tail's length, so everything is in registers and the field
+// loops are unrolled (with a run-time field count the arrays lived in scratch
+// memory and a pass over a 1024-site line took 12 us, most of it here).
+template <typename T, int NF>
+__device__ __forceinline__ void step_tail(const Lattice &lat, RunState<NF> &s, const double (&tot)[kSumsPerField * NF + 1],
+                                          ce_energy &e)
+{
+#pragma clang fp contract(off)
     const double Ns = (double)lat.nsites;
     const double dt = lat.dt;
-    const double a1 = sc->a_next;
-    const double y = sc->adot_half;
-    double m1[kMaxFields], sumf2[kMaxFields], gsum = 0.0;
-    ce_energy e;
-    for (int i = 0; i < kMaxFields; i++) {
-        e.kin[i] = e.grad[i] = e.mean[i] = e.mean_sq[i] = 0.0;
-        if (i >= lat.nf) continue;
+    const double a1 = s.a_next;
+    const double y = s.adot_half;
+    double m1[NF], sumf2[NF], gsum = 0.0;
+#pragma unroll
+    for (int i = 0; i < kMaxFields; i++) e.kin[i] = e.grad[i] = e.mean[i] = e.mean_sq[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < NF; i++) {
         const double *t = tot + kSumsPerField * i;
-        m1[i] = sc->m[i] + dt * sc->r[i];
+        m1[i] = s.m[i] + dt * s.r[i];
         sumf2[i] = Ns * m1[i] * m1[i] + 2.0 * m1[i] * t[0] + t[1];
         e.mean[i] = m1[i] + t[0] / Ns;
         e.mean_sq[i] = sumf2[i] / Ns;
@@ -291,7 +468,7 @@ __device__ __forceinline__ void step_tail(const Lattice &lat, const double *tot)
     }
     // mean comoving potential at n+1, with the vacuum term a^4 V0
     const double a1sq = a1 * a1;
-    const double V = tot[kSumsPerField * lat.nf] / Ns + a1sq * a1sq * lat.vacuum;
+    const double V = tot[kSumsPerField * NF] / Ns + a1sq * a1sq * lat.vacuum;
     double x = 0.0, abar = 0.0, c = 0.0;
     if (lat.expansion) {
         // a'^{n+3/2} from the time-centred kick of a' (quadratic in x; the
@@ -310,22 +487,26 @@ __device__ __forceinline__ void step_tail(const Lattice &lat, const double *tot)
     const double eta = 0.5 * dt * c - abar / a1;
     double rho = V;
     int bad = 0;
-    for (int i = 0; i < lat.nf; i++) {
+#pragma unroll
+    for (int i = 0; i < NF; i++) {
         const double *t = tot + kSumsPerField * i;
         const double sum_uf = m1[i] * t[4] + t[5];
         e.kin[i] = 0.5 * (t[3] + 2.0 * eta * sum_uf + eta * eta * sumf2[i]) / Ns;
         rho += e.kin[i] + e.grad[i];
         // mean of fdot^{n+3/2} = mean p^{n+3/2} + beta_{n+1} mean f^{n+1},
         // mean p^{n+3/2} = 2 mean ubar - mean fdot^{n+1/2}
-        const double fm = 2.0 * t[4] / Ns - sc->fdot_mean[i] + beta1 * e.mean[i];
-        sc->m[i] = m1[i];
-        sc->fdot_mean[i] = fm;
-        sc->r[i] = round_to_storage<T>(fm);
+        const double fm = 2.0 * t[4] / Ns - s.fdot_mean[i] + beta1 * e.mean[i];
+        s.m[i] = m1[i];
+        s.fdot_mean[i] = fm;
+        s.r[i] = round_to_storage<T>(fm);
     }
-    for (int q = 0; q <= kSumsPerField * lat.nf; q++) bad |= !isfinite(tot[q]);
+#pragma unroll
+    for (int q = 0; q <= kSumsPerField * NF; q++) bad |= !isfinite(tot[q]);
     bad |= !isfinite(x) || !isfinite(c);
-    e.step = sc->step + 1;
-    e.tau = sc->tau + dt;
+    s.step += 1;
+    s.tau += dt;
+    e.step = s.step;
+    e.tau = s.tau;
     e.a = a1;
     e.adot = abar;
     e.hubble = abar / (a1 * a1);
@@ -335,36 +516,29 @@ __device__ __forceinline__ void step_tail(const Lattice &lat, const double *tot)
         (lat.expansion && abar != 0.0) ? (abar * abar - lat.kappa * rho / 3.0) / (abar * abar) : 0.0;
     e.nonfinite = bad;
     e.pad_ = 0;
-    lat.ring[e.step % kLogCap] = e;
-
-    sc->a = a1;
-    sc->a_next = lat.expansion ? a1 + dt * x : 1.0;
-    sc->adot_half = x;
-    sc->beta = beta1;
-    sc->tau = e.tau;
-    sc->step = e.step;
-    sc->cur ^= 1;
-    if (sc->remaining > 0) sc->remaining -= 1;
-    if (bad && sc->first_bad < 0) sc->first_bad = e.step;
-    publish_next_pass(lat, sc);
+    s.a = a1;
+    s.a_next = lat.expansion ? a1 + dt * x : 1.0;
+    s.adot_half = x;
+    s.beta = beta1;
+    if (bad && s.first_bad < 0) s.first_bad = s.step;
 }
 
 // FP64 tail of the start-up pass.  Sums of field i at 6i: sum d, sum d^2,
 // sum d Lap d, sum fdot(0)^2, sum p^{1/2}, (unused); last: sum V at a = 1.
-template <typename T>
-__device__ __forceinline__ void init_tail(const Lattice &lat, const double *tot)
+template <typename T, int NF>
+__device__ __forceinline__ void init_tail(const Lattice &lat, RunState<NF> &s, const double (&tot)[kSumsPerField * NF + 1],
+                                          ce_energy &e)
 {
 #pragma clang fp contract(off)
-    Scalars *sc = lat.sc;
     const double Ns = (double)lat.nsites;
     const double dt = lat.dt;
-    ce_energy e;
     double gsum = 0.0, rho = 0.0;
-    for (int i = 0; i < kMaxFields; i++) {
-        e.kin[i] = e.grad[i] = e.mean[i] = e.mean_sq[i] = 0.0;
-        if (i >= lat.nf) continue;
+#pragma unroll
+    for (int i = 0; i < kMaxFields; i++) e.kin[i] = e.grad[i] = e.mean[i] = e.mean_sq[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < NF; i++) {
         const double *t = tot + kSumsPerField * i;
-        const double m = sc->m[i];
+        const double m = s.m[i];
         e.kin[i] = 0.5 * t[3] / Ns;
         e.grad[i] = -0.5 * t[2] / Ns;
         e.mean[i] = m + t[0] / Ns;
@@ -372,7 +546,7 @@ __device__ __forceinline__ void init_tail(const Lattice &lat, const double *tot)
         gsum += e.grad[i];
         rho += e.kin[i] + e.grad[i];
     }
-    const double V = tot[kSumsPerField * lat.nf] / Ns + lat.vacuum;  // a = 1
+    const double V = tot[kSumsPerField * NF] / Ns + lat.vacuum;  // a = 1
     rho += V;
     double ap0 = 0.0, app0 = 0.0;
     if (lat.expansion) {
@@ -384,12 +558,14 @@ __device__ __forceinline__ void init_tail(const Lattice &lat, const double *tot)
     // half kick omits the two f terms, beta_0 = a'(0) + dt/2 a''(0).
     const double beta0 = aph;
     int bad = 0;
-    for (int i = 0; i < lat.nf; i++) {
+#pragma unroll
+    for (int i = 0; i < NF; i++) {
         const double fm = tot[kSumsPerField * i + 4] / Ns + beta0 * e.mean[i];
-        sc->fdot_mean[i] = fm;
-        sc->r[i] = round_to_storage<T>(fm);
+        s.fdot_mean[i] = fm;
+        s.r[i] = round_to_storage<T>(fm);
     }
-    for (int q = 0; q <= kSumsPerField * lat.nf; q++) bad |= !isfinite(tot[q]);
+#pragma unroll
+    for (int q = 0; q <= kSumsPerField * NF; q++) bad |= !isfinite(tot[q]);
     bad |= !isfinite(ap0);   // a negative energy density cannot start an expanding run
     e.step = 0;
     e.tau = 0.0;
@@ -402,15 +578,13 @@ __device__ __forceinline__ void init_tail(const Lattice &lat, const double *tot)
         (lat.expansion && ap0 != 0.0) ? (ap0 * ap0 - lat.kappa * rho / 3.0) / (ap0 * ap0) : 0.0;
     e.nonfinite = bad;
     e.pad_ = 0;
-    lat.ring[0] = e;
-    sc->a = 1.0;
-    sc->adot_half = aph;
-    sc->a_next = lat.expansion ? 1.0 + dt * aph : 1.0;
-    sc->beta = beta0;
-    sc->tau = 0.0;
-    sc->step = 0;
-    sc->first_bad = bad ? 0 : -1;
-    publish_next_pass(lat, sc);
+    s.a = 1.0;
+    s.adot_half = aph;
+    s.a_next = lat.expansion ? 1.0 + dt * aph : 1.0;
+    s.beta = beta0;
+    s.tau = 0.0;
+    s.step = 0;
+    s.first_bad = bad ? 0 : -1;
 }
 
 // Partial sum q of block or tile `row`: one column per sum, so that the
@@ -420,72 +594,99 @@ __device__ __forceinline__ double *partial_at(const Lattice &lat, int q, long lo
     return lat.partials + (long long)q * lat.slots + row;
 }
 
+// Store the block's totals (red[0], after block_sum) as row `row` of the
+// partial sums: agent-scope stores, written through this XCD's L2, by threads
+// of wave 0, whose finish_pass waits for them.
+template <int NQ>
+__device__ __forceinline__ void put_partials(const Lattice &lat, const double (*red)[kMaxSums], long long row)
+{
+    if (threadIdx.x < NQ)
+        __hip_atomic_store(partial_at(lat, threadIdx.x, row), red[0][threadIdx.x], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Last-block reduction of the partial sums in a fixed order, then the FP64
-// tail.  Every block calls this after writing its partials.  The `grid`
-// blocks (this lattice's share of the launch) wrote `rows` rows of partials
-// between them (one per block, or one per tile); the block that takes the
-// last ticket reduces them in row order and clears the tile counters for the
-// next launch (every other block has finished taking tiles by then).
+// tail.  Every block calls this after writing its partials with put_partials.
+// The `grid` blocks (this lattice's share of the launch) wrote `rows` rows of
+// partials between them (one per block, or one per tile); the block that takes
+// the last ticket reduces them in row order and clears the tile counters for
+// the next launch (every other block has finished taking tiles by then).
 //
-// Ordering: the barrier completes the block's partial stores; the ticket
-// increment is a release at agent scope (the L2 of this XCD writes back, no
-// invalidate), so only the block that takes the last ticket pays an acquire,
-// whose L2 invalidate would otherwise evict the halos that the other blocks
-// on its XCD are about to re-read.
+// Ordering: wave 0 wrote the block's rows through to memory and waits until
+// they have arrived before it takes the ticket, and the last block reads them
+// past its caches, so no block writes back or invalidates an L2: a full fence
+// per block evicted the halos that the other blocks on its XCD were about to
+// re-read, and a release alone still wrote the L2 back.
 //
 // Each thread sums rows threadIdx.x, + blockDim.x, ... in that order; with
 // R > 1 it loads R of them before adding them, so R rows' loads are in
 // flight at once (the sums, and so the result, are the same for every R).
-template <typename T, int NQ, int MODE, int R = 1>
+template <typename T, int NF, int MODE, int R = 1>
 __device__ __forceinline__ void finish_pass(const Lattice &lat, int grid, int rows, double (*red)[kMaxSums])
 {
+    constexpr int NQ = kSumsPerField * NF + 1;
     __shared__ int s_last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned int t = __hip_atomic_fetch_add(lat.ticket, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        const int last = t == (unsigned int)(grid - 1);
-        if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        s_last = last;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    double acc[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; q++) acc[q] = 0.0;
-    const int stride = (int)blockDim.x;
-    int b = threadIdx.x;
-    if constexpr (R > 1) {
-        for (; b + (R - 1) * stride < rows; b += R * stride) {
-            double v[R][NQ];
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-#pragma unroll
-                for (int q = 0; q < NQ; q++)
-                    v[r][q] = __hip_atomic_load(partial_at(lat, q, b + r * stride), __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-            for (int r = 0; r < R; r++)
-#pragma unroll
-                for (int q = 0; q < NQ; q++) acc[q] += v[r][q];
+    RunState<NF> st = load_state<NF>(lat);
+    if (grid > 1 || rows > 1) {
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(0);   // wave 0's rows have arrived
+            if (threadIdx.x == 0)
+                s_last = __hip_atomic_fetch_add(lat.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                         (unsigned int)(grid - 1);
         }
-    }
-    for (; b < rows; b += stride) {
+        __syncthreads();
+        if (!s_last) return;
+        double acc[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; q++)
-            acc[q] += __hip_atomic_load(partial_at(lat, q, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    block_sum<NQ>(acc, red);
+        for (int q = 0; q < NQ; q++) acc[q] = 0.0;
+        const int stride = (int)blockDim.x;
+        int b = threadIdx.x;
+        if constexpr (R > 1) {
+            for (; b + (R - 1) * stride < rows; b += R * stride) {
+                double v[R][NQ];
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+#pragma unroll
+                    for (int q = 0; q < NQ; q++)
+                        v[r][q] = __hip_atomic_load(partial_at(lat, q, b + r * stride), __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int r = 0; r < R; r++)
+#pragma unroll
+                    for (int q = 0; q < NQ; q++) acc[q] += v[r][q];
+            }
+        }
+        for (; b < rows; b += stride) {
+            double v[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; q++)
+                v[q] = __hip_atomic_load(partial_at(lat, q, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int q = 0; q < NQ; q++) acc[q] += v[q];
+        }
+        block_sum<NQ>(acc, red);
+    }   // one block, one row: its totals are the lattice's
     if (threadIdx.x == 0) {
-        double tot[kMaxSums];
+        double tot[NQ];
+#pragma unroll
         for (int q = 0; q < NQ; q++) tot[q] = red[0][q];
+        ce_energy e;
         if (MODE == kStep)
-            step_tail<T>(lat, tot);
+            step_tail<T, NF>(lat, st, tot, e);
         else
-            init_tail<T>(lat, tot);
-        __hip_atomic_store(lat.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int i = 1; i <= kTileCounters; i++)
-            __hip_atomic_store(lat.ticket + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            init_tail<T, NF>(lat, st, tot, e);
+        store_state<NF>(lat, st);
+        lat.ring[e.step % kLogCap] = e;
+        if (MODE == kStep) {
+            lat.sc->cur ^= 1;
+            if (lat.sc->remaining > 0) lat.sc->remaining -= 1;
+        }
+        if (grid > 1 || rows > 1)
+            for (int i = 0; i <= kTileCounters; i++)
+                __hip_atomic_store(lat.ticket + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

@@ -208,8 +208,8 @@ __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b
     }
 
     block_sum<NQ>(acc, red);
-    if (threadIdx.x < NQ) *partial_at(lat, threadIdx.x, b) = red[0][threadIdx.x];
-    finish_pass<T, NQ, MODE>(lat, grid, grid, red);
+    put_partials<NQ>(lat, red, b);
+    finish_pass<T, NF, MODE>(lat, grid, grid, red);
 }
 
 template <typename T, int NF, int MODEL, int MODE>

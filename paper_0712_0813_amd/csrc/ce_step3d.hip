@@ -378,7 +378,7 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
         if (per_tile) {
             // this tile's row; the next tile starts its sums from zero
             block_sum<NQ>(acc, red);
-            if (threadIdx.x < NQ) *partial_at(lat, threadIdx.x, tile) = red[0][threadIdx.x];
+            put_partials<NQ>(lat, red, tile);
 #pragma unroll
             for (int k = 0; k < NQ; k++) acc[k] = 0.0;
         }
@@ -386,10 +386,10 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
 
     if (!per_tile) {
         block_sum<NQ>(acc, red);
-        if (threadIdx.x < NQ) *partial_at(lat, threadIdx.x, b) = red[0][threadIdx.x];
+        put_partials<NQ>(lat, red, b);
     }
     // up to a few thousand tile rows: several rows' loads in flight per thread
-    finish_pass<T, NQ, MODE, (NQ <= 13 ? 4 : 2)>(lat, grid, per_tile ? (int)ntiles : grid, red);
+    finish_pass<T, NF, MODE, (NQ <= 13 ? 4 : 2)>(lat, grid, per_tile ? (int)ntiles : grid, red);
 }
 
 template <typename T, int NF, int MODEL, int MODE, int VEC, int LPR, int BS>
