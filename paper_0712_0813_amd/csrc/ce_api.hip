@@ -58,6 +58,8 @@ Layout layout_of(const ce_params *p)
     L.off_ticket = off;
     static_assert((1 + kTileCounters) * sizeof(unsigned int) <= kAlign, "ticket and tile counters share one line");
     off += kAlign;
+    L.off_sync = off;
+    off += align_up((size_t)2 * (2 * kMaxSums * kSyncRows + 8 * kTotalWords) * sizeof(unsigned long long));
     L.off_ring = off;
     off += align_up((size_t)kLogCap * sizeof(ce_energy));
     L.off_maxabs = off;
@@ -164,6 +166,26 @@ ce_status build_graph(ce_sim *s, int parity)
     return CE_OK;
 }
 
+// Steps of one resident launch at most: a millisecond or two, for which other
+// work on the GPU may have to wait.
+constexpr int kResidentSteps = 256;
+
+hipError_t launch_resident(ce_sim *s, int steps)
+{
+    int src = s->cur;
+    void *args[] = {&s->lat, &src, &steps, &s->epoch};
+    const dim3 grid(s->resident.blocks), block(s->resident.threads);
+    // a single block waits for nobody
+    const hipError_t e = s->resident.blocks > 1
+                             ? hipLaunchCooperativeKernel(s->resident.kernel, grid, block, args, 0, s->stream)
+                             : hipLaunchKernel(s->resident.kernel, grid, block, args, 0, s->stream);
+    if (e != hipSuccess) return e;
+    s->epoch += (unsigned)steps;
+    s->cur ^= steps & 1;
+    s->step += steps;
+    return hipSuccess;
+}
+
 ce_status device_cus(int *cus)
 {
     int dev = 0;
@@ -172,9 +194,61 @@ ce_status device_cus(int *cus)
     return CE_OK;
 }
 
+// Kernel of the resident tiled pass for a launch, nullptr if there is none.
+const void *resident_kernel(const ce_params *p, const ce_launch &c)
+{
+    if (p->N % c.planes != 0 ||
+        tiled_tiles(p->N, c.sites_per_thread, c.lanes_per_row, c.block, c.planes) > kSyncRows)
+        return nullptr;
+    return p->model == kPoly ? resident_tiled_model<kPoly>(p->precision, p->nfields, c.sites_per_thread,
+                                                           c.lanes_per_row, c.block, c.planes)
+                             : resident_tiled_model<kQuartic>(p->precision, p->nfields, c.sites_per_thread,
+                                                              c.lanes_per_row, c.block, c.planes);
+}
+
+// The resident pass that takes the same steps as s's launch, if there is one:
+// its blocks must all be resident at once, one per published row.
+void plan_resident(ce_sim *s)
+{
+    s->resident = ce_sim::Resident{};
+    const Lattice &lat = s->lat;
+    ce_sim::Resident r;
+    if (lat.kind == kDirect) {
+        // one quad per thread, and no block without one; VB blocks of the
+        // launch are taken as one, so that at most kSyncRows remain
+        if ((lat.nsites / 4 + kBlock - 1) / kBlock != lat.nblocks) return;
+        const int vb = (lat.nblocks + kSyncRows - 1) / kSyncRows;
+        r.kernel = s->p.model == kPoly ? resident_direct_model<kPoly>(s->p.precision, lat.dims, lat.nf, vb)
+                                       : resident_direct_model<kQuartic>(s->p.precision, lat.dims, lat.nf, vb);
+        r.blocks = (lat.nblocks + vb - 1) / vb;
+        r.threads = kBlock * vb + 64;
+    } else if (lat.kind == kTiled3d) {
+        const ce_launch c{CE_KERNEL_TILED3D, lat.vec, lat.lpr, lat.bs, lat.zc, 0};
+        r.kernel = resident_kernel(&s->p, c);
+        r.blocks = (int)tiled_tiles(lat.N, lat.vec, lat.lpr, lat.bs, lat.zc);
+        r.threads = lat.bs + 64;
+    }
+    if (!r.kernel) return;
+    // the fewest steps worth a launch: a cooperative one costs about 22 us
+    // (32^3: 4 steps 36 us plain, 40 resident, 6 steps 54 and 48; 64^3: 2 steps
+    // 27 and 32, 3 steps 40 and 37), a single block's 3 (1-D 1024: 2 steps 10.9
+    // and 7.4)
+    r.min_steps = r.blocks == 1 ? 2 : lat.kind == kDirect ? 5 : 3;
+    int cus = 0, per = 0;
+    if (device_cus(&cus) != CE_OK) return;
+    if (r.blocks > 1 &&
+        (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, r.kernel, r.threads, 0) != hipSuccess ||
+         (long long)per * cus < r.blocks)) {
+        (void)hipGetLastError();
+        return;
+    }
+    s->resident = r;
+}
+
 // Validate cfg for the lattice and fill the kernel-facing fields of lat.
 ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
 {
+    s->resident = ce_sim::Resident{};
     Lattice &lat = s->lat;
     if (cfg.grid < 0 || cfg.grid > kMaxBlocks) return fail(CE_EINVAL, "grid must be 0..%d", kMaxBlocks);
     if (cfg.kernel == CE_KERNEL_DIRECT) {
@@ -245,12 +319,14 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
         // the shape is fixed: report it whatever the caller passed
         s->launch = ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, cfg.planes, cfg.grid};
         drop_graphs(s);
+        plan_resident(s);
         return CE_OK;
     } else {
         return fail(CE_EINVAL, "unknown kernel %d", cfg.kernel);
     }
     s->launch = cfg;
     drop_graphs(s);
+    plan_resident(s);
     return CE_OK;
 }
 
@@ -320,6 +396,20 @@ ce_launch default_launch(const ce_params *p, int cus)
                 return c;
             }
     }
+    // Lattices that a resident pass can take: the shortest chunks (up to 8
+    // planes) that leave no more tiles than it has blocks, so that the step's
+    // sites are spread over as many compute units as there are (64^3 x 2
+    // fields: 4.8 us a step with 256 tiles of one plane, 5.3 with 128 of two,
+    // 8.0 with 64 of four).  The tile shapes are those it is built for.
+    for (int a = 0; a < 2; a++) {
+        const bool fp64 = p->precision == CE_FP64;
+        const int v = fp64 ? 2 : 4, l = (fp64 ? 32 : 16) >> a, bs = fp64 ? 512 : 256;
+        for (int z = 1; z <= 8 && p->N >= 64; z *= 2) {
+            if (p->N % z || !tiled_fits(3, p->N, v, l, bs, z) || tiled_tiles(p->N, v, l, bs, z) > kSyncRows) continue;
+            const ce_launch r{CE_KERNEL_TILED3D, v, l, bs, z, 0};
+            if (resident_kernel(p, r)) return r;
+        }
+    }
     if (p->N >= 64) {
         // Medium lattices (64^3 .. 256^3 and the like): one tile per compute
         // unit where the lattice has that many, with the tallest chunks that
@@ -385,10 +475,12 @@ ce_status ce_set_launch(ce_sim *s, const ce_launch *cfg)
     if (!s || !cfg) return fail(CE_EINVAL, "NULL argument");
     const ce_launch old = s->launch;
     const Lattice saved = s->lat;
+    const ce_sim::Resident resident = s->resident;
     ce_status st = apply_launch(s, *cfg);
     if (st != CE_OK) {
         s->launch = old;
         s->lat = saved;
+        s->resident = resident;
     }
     return st;
 }
@@ -496,7 +588,9 @@ ce_status ce_create(const ce_params *p, ce_sim **out)
     lat.partials = reinterpret_cast<double *>(s->base + L.off_partials);
     lat.ticket = reinterpret_cast<unsigned int *>(s->base + L.off_ticket);
     lat.slots = L.nblocks;
+    lat.sync = reinterpret_cast<unsigned long long *>(s->base + L.off_sync);
     lat.ring = reinterpret_cast<ce_energy *>(s->base + L.off_ring);
+    lat.columns = s->base + L.off_staging;
     {
         int cus = 0;
         ce_status st2 = device_cus(&cus);
@@ -518,7 +612,7 @@ ce_status ce_create(const ce_params *p, ce_sim **out)
     init.a_next = 1.0;
     init.first_bad = -1;
     hipError_t e = hipMemcpyAsync(lat.sc, &init, sizeof(init), hipMemcpyHostToDevice, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(lat.ticket, 0, kAlign, s->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(lat.ticket, 0, L.off_ring - L.off_ticket, s->stream);
     if (e == hipSuccess) e = hipMemsetAsync(s->maxabs, 0, kAlign, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) {
@@ -688,6 +782,18 @@ ce_status ce_step(ce_sim *s, int64_t nsteps)
     if (nsteps < 0) return fail(CE_EINVAL, "nsteps must be >= 0");
     if (!s->started) return fail(CE_ESTATE, "load every field before stepping");
     long long left = nsteps;
+    // A resident pass takes the steps of a call where they are enough to pay
+    // for its launch.  Plain launches (step block 0) and captured streams take
+    // the steps one by one; the results are the same.
+    if (s->resident.kernel && s->step_block > 0 && left >= s->resident.min_steps) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        CE_HIP(hipStreamIsCapturing(s->stream, &cap));
+        while (cap == hipStreamCaptureStatusNone && left >= s->resident.min_steps) {
+            int n = (int)std::min<long long>(left, kResidentSteps);
+            CE_HIP(launch_resident(s, n));
+            left -= n;
+        }
+    }
     if (s->step_block > 0) {
         while (left >= s->step_block) {
             if (!s->graph[s->cur]) {

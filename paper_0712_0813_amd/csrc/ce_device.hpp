@@ -437,97 +437,226 @@ __device__ __forceinline__ void store_state(const Lattice &lat, const RunState<N
     fill_pass_scalars<double, NF>(sc->nxd, s, lat, w);
 }
 
-// FP64 tail after a step pass n -> n+1: s goes from step n to n+1, e receives
-// the diagnostics.  tot: sums of field i at 6i: sum d, sum d^2, sum d Lap d,
-// sum ubar^2, sum ubar, sum ubar d, all at n+1, with
-// ubar = (fdot^{n+1/2} + p^{n+3/2})/2; last: sum V.  The chain of dependent
-// divisions is the tail's length, so everything is in registers and the field
-// loops are unrolled (with a run-time field count the arrays lived in scratch
-// memory and a pass over a 1024-site line took 12 us, most of it here).
+// FP64 tail after a step pass n -> n+1, worked by one wavefront.  Sums of
+// field i at 6i: sum d, sum d^2, sum d Lap d, sum ubar^2, sum ubar, sum ubar d,
+// all at n+1, with ubar = (fdot^{n+1/2} + p^{n+3/2})/2; last: sum V.
+//
+// Bound by latency: it is one chain of dependent FP64 divisions (each about
+// 100 cycles) that everything else waits for.  So lane q divides sum q, lane i
+// works field i, what does not depend on the sums is prepared before they
+// arrive, and the diagnostics come after the next pass's coefficients.  (One
+// thread working all of it on arrays in scratch memory took most of the 12 us
+// of a step of a 1024-site line.)
 template <typename T, int NF>
-__device__ __forceinline__ void step_tail(const Lattice &lat, RunState<NF> &s, const double (&tot)[kSumsPerField * NF + 1],
-                                          ce_energy &e)
-{
+struct LaneTail {
+    static constexpr int NQ = kSumsPerField * NF + 1;
+    // step n (uniform), and the lane's field i = min(lane, NF - 1)
+    double a, a1, y, beta, tau;
+    long long step, first_bad;
+    int i;
+    double m, fdot_mean, r;
+    // the lane's polynomial term and mass
+    double tcoef, mu2;
+    int tpow;
+    // prepared
+    double m1, ns_m1sq, A4, B, C0, vac;
+    // of the solved step
+    double x, abar, c, V, gsum, sum_uf, u0, t3, sumf2, grad;
+    bool bad;
+
+    __device__ __forceinline__ void load(const Lattice &lat)
+    {
+        const Scalars *sc = lat.sc;
+        const int lane = __lane_id();
+        i = min(lane, NF - 1);
+        a = sc->a;
+        a1 = sc->a_next;
+        y = sc->adot_half;
+        beta = sc->beta;
+        tau = sc->tau;
+        step = sc->step;
+        first_bad = sc->first_bad;
+        m = sc->m[i];
+        fdot_mean = sc->fdot_mean[i];
+        r = sc->r[i];
+        tcoef = 0.0;
+        tpow = 0;
+        mu2 = lat.mu2[0];
+#pragma unroll
+        for (int f = 1; f < NF; f++) mu2 = i == f ? lat.mu2[f] : mu2;
+#pragma unroll
+        for (int t = 0; t < kMaxTerms; t++)
+            if (lane == t && t < lat.nterms) {
+                tcoef = lat.tcoef[t];
+                tpow = 4 - lat.tdeg[t];
+            }
+    }
+
+    // What the sums are not needed for.
+    __device__ __forceinline__ void prepare(const Lattice &lat)
+    {
 #pragma clang fp contract(off)
-    const double Ns = (double)lat.nsites;
-    const double dt = lat.dt;
-    const double a1 = s.a_next;
-    const double y = s.adot_half;
-    double m1[NF], sumf2[NF], gsum = 0.0;
-#pragma unroll
-    for (int i = 0; i < kMaxFields; i++) e.kin[i] = e.grad[i] = e.mean[i] = e.mean_sq[i] = 0.0;
-#pragma unroll
-    for (int i = 0; i < NF; i++) {
-        const double *t = tot + kSumsPerField * i;
-        m1[i] = s.m[i] + dt * s.r[i];
-        sumf2[i] = Ns * m1[i] * m1[i] + 2.0 * m1[i] * t[0] + t[1];
-        e.mean[i] = m1[i] + t[0] / Ns;
-        e.mean_sq[i] = sumf2[i] / Ns;
-        e.grad[i] = -0.5 * t[2] / Ns;
-        gsum += e.grad[i];
-    }
-    // mean comoving potential at n+1, with the vacuum term a^4 V0
-    const double a1sq = a1 * a1;
-    const double V = tot[kSumsPerField * NF] / Ns + a1sq * a1sq * lat.vacuum;
-    double x = 0.0, abar = 0.0, c = 0.0;
-    if (lat.expansion) {
-        // a'^{n+3/2} from the time-centred kick of a' (quadratic in x; the
-        // root continuous with a'^{n+1/2}, written without cancellation)
-        const double S = lat.kappa * (2.0 / 3.0 * gsum + V) / a1;
+        const double dt = lat.dt, Ns = (double)lat.nsites;
+        m1 = m + dt * r;
+        ns_m1sq = Ns * m1 * m1;
         const double A = dt / (4.0 * a1);
-        const double B = 1.0 + dt * y / (2.0 * a1);
-        const double C = dt * y * y / (4.0 * a1) - y - dt * S;
-        x = -2.0 * C / (B + sqrt(B * B - 4.0 * A * C));
-        abar = 0.5 * (x + y);
-        c = (S - abar * abar / a1) / a1;
+        A4 = 4.0 * A;
+        B = 1.0 + dt * y / (2.0 * a1);
+        C0 = dt * y * y / (4.0 * a1) - y;
+        const double a1sq = a1 * a1;
+        vac = a1sq * a1sq * lat.vacuum;
     }
-    const double beta1 = dt * c;
-    // kinetic energy of u = (fdot^{n+1/2} + fdot^{n+3/2})/2 - (abar/a) f
-    //                     = ubar + eta f,  eta = dt c/2 - abar/a
-    const double eta = 0.5 * dt * c - abar / a1;
-    double rho = V;
-    int bad = 0;
+
+    // From the sums (lane q: sum q) to the state at n+1.  scratch: 2 kMaxSums
+    // doubles of LDS of this wavefront's own.
+    __device__ __forceinline__ void solve(const Lattice &lat, double tot, double *scratch)
+    {
+#pragma clang fp contract(off)
+        const double dt = lat.dt, Ns = (double)lat.nsites;
+        const int lane = __lane_id();
+        if (lane < NQ) {
+            scratch[lane] = tot;
+            scratch[kMaxSums + lane] = tot / Ns;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const double *t = scratch + kSumsPerField * i, *u = t + kMaxSums;
+        gsum = 0.0;
 #pragma unroll
-    for (int i = 0; i < NF; i++) {
-        const double *t = tot + kSumsPerField * i;
-        const double sum_uf = m1[i] * t[4] + t[5];
-        e.kin[i] = 0.5 * (t[3] + 2.0 * eta * sum_uf + eta * eta * sumf2[i]) / Ns;
-        rho += e.kin[i] + e.grad[i];
+        for (int f = 0; f < NF; f++) gsum += -0.5 * scratch[kMaxSums + kSumsPerField * f + 2];
+        // mean comoving potential at n+1, with the vacuum term a^4 V0
+        V = scratch[kMaxSums + NQ - 1] + vac;
+        x = abar = c = 0.0;
+        if (lat.expansion) {
+            // a'^{n+3/2} from the time-centred kick of a' (quadratic in x; the
+            // root continuous with a'^{n+1/2}, written without cancellation)
+            const double S = lat.kappa * (2.0 / 3.0 * gsum + V) / a1;
+            const double C = C0 - dt * S;
+            x = -2.0 * C / (B + sqrt(B * B - A4 * C));
+            abar = 0.5 * (x + y);
+            c = (S - abar * abar / a1) / a1;
+        }
+        beta = dt * c;
+        u0 = u[0];
+        grad = -0.5 * u[2];
+        t3 = t[3];
+        sumf2 = ns_m1sq + 2.0 * m1 * t[0] + t[1];
+        sum_uf = m1 * t[4] + t[5];
         // mean of fdot^{n+3/2} = mean p^{n+3/2} + beta_{n+1} mean f^{n+1},
         // mean p^{n+3/2} = 2 mean ubar - mean fdot^{n+1/2}
-        const double fm = 2.0 * t[4] / Ns - s.fdot_mean[i] + beta1 * e.mean[i];
-        s.m[i] = m1[i];
-        s.fdot_mean[i] = fm;
-        s.r[i] = round_to_storage<T>(fm);
+        fdot_mean = 2.0 * u[4] - fdot_mean + beta * (m1 + u0);
+        m = m1;
+        r = round_to_storage<T>(fdot_mean);
+        bad = __ballot(lane < NQ && !isfinite(tot)) != 0 || !isfinite(x) || !isfinite(c);
+        a = a1;
+        a1 = lat.expansion ? a + dt * x : 1.0;
+        step += 1;
+        tau += dt;
+        if (bad && first_bad < 0) first_bad = step;
     }
+
+    // Coefficients of the next pass (lane i: field i; lane t: term t).
+    template <typename U>
+    __device__ __forceinline__ void next_pass(const Lattice &lat, PassScalars<U> &ps) const
+    {
+#pragma clang fp contract(off)
+        const int lane = __lane_id();
+        const double a2 = a1 * a1;
+        if (lane == 0) ps.beta = (U)beta;
+        if (lane < kMaxFields) {
+            const bool on = lane < NF;
+            ps.bm[lane] = on ? (U)(beta * m) : (U)0;
+            ps.r[lane] = on ? (U)r : (U)0;
+            ps.m1[lane] = on ? (U)(m + lat.dt * r) : (U)0;
+            ps.m2a[lane] = on ? (U)(a2 * mu2) : (U)0;
+            ps.hm[lane] = on ? (U)(0.5 * a2 * mu2) : (U)0;
+        }
+        if (lat.nterms > 0) {
+            // a term of degree D of the physical potential is coef a^(4 - D)
+            // in the program variables
+            double w = 1.0;
 #pragma unroll
-    for (int q = 0; q <= kSumsPerField * NF; q++) bad |= !isfinite(tot[q]);
-    bad |= !isfinite(x) || !isfinite(c);
-    s.step += 1;
-    s.tau += dt;
-    e.step = s.step;
-    e.tau = s.tau;
-    e.a = a1;
-    e.adot = abar;
-    e.hubble = abar / (a1 * a1);
-    e.pot = V;
-    e.rho = rho;
-    e.friedmann_residual =
-        (lat.expansion && abar != 0.0) ? (abar * abar - lat.kappa * rho / 3.0) / (abar * abar) : 0.0;
-    e.nonfinite = bad;
-    e.pad_ = 0;
-    s.a = a1;
-    s.a_next = lat.expansion ? a1 + dt * x : 1.0;
-    s.adot_half = x;
-    s.beta = beta1;
-    if (bad && s.first_bad < 0) s.first_bad = s.step;
-}
+            for (int j = 0; j < 3; j++) w = j < tpow ? w * a1 : w;
+#pragma unroll
+            for (int j = 0; j < 4; j++) w = j < -tpow ? w / a1 : w;
+            if (lane < kMaxTerms) ps.tc[lane] = (U)(tcoef * w);
+        } else if (lane < kMaxTerms) {
+            ps.tc[lane] = (U)0;
+        }
+    }
+    static_assert(CE_MAX_DEGREE == 8, "powers of a from -4 to 3");
+
+    // Diagnostics of the solved step; y is a'^{n+1/2} until advance().
+    __device__ __forceinline__ void record(const Lattice &lat) const
+    {
+#pragma clang fp contract(off)
+        const double Ns = (double)lat.nsites;
+        const int lane = __lane_id();
+        // kinetic energy of u = (fdot^{n+1/2} + fdot^{n+3/2})/2 - (abar/a) f
+        //                     = ubar + eta f,  eta = dt c/2 - abar/a
+        const double eta = 0.5 * lat.dt * c - abar / a;
+        const double kin = 0.5 * (t3 + 2.0 * eta * sum_uf + eta * eta * sumf2) / Ns;
+        double rho = V;
+        const double own = kin + grad;
+#pragma unroll
+        for (int f = 0; f < NF; f++) rho += __shfl(own, f, 64);
+        ce_energy *e = lat.ring + step % kLogCap;
+        if (lane < kMaxFields) {
+            const bool on = lane < NF;
+            e->kin[lane] = on ? kin : 0.0;
+            e->grad[lane] = on ? grad : 0.0;
+            e->mean[lane] = on ? m1 + u0 : 0.0;
+            e->mean_sq[lane] = on ? sumf2 / Ns : 0.0;
+        }
+        if (lane == 0) {
+            e->step = step;
+            e->tau = tau;
+            e->a = a;
+            e->adot = abar;
+            e->hubble = abar / (a * a);
+            e->pot = V;
+            e->rho = rho;
+            e->friedmann_residual =
+                (lat.expansion && abar != 0.0) ? (abar * abar - lat.kappa * rho / 3.0) / (abar * abar) : 0.0;
+            e->nonfinite = bad;
+            e->pad_ = 0;
+        }
+    }
+
+    __device__ __forceinline__ void advance() { y = x; }
+
+    // The state in memory, with the next pass's coefficients (after advance).
+    __device__ __forceinline__ void store(const Lattice &lat) const
+    {
+#pragma clang fp contract(off)
+        Scalars *sc = lat.sc;
+        const int lane = __lane_id();
+        if (lane == 0) {
+            sc->a = a;
+            sc->a_next = a1;
+            sc->adot_half = y;
+            sc->beta = beta;
+            sc->tau = tau;
+            sc->step = step;
+            sc->first_bad = first_bad;
+        }
+        if (lane < NF) {
+            sc->m[lane] = m;
+            sc->fdot_mean[lane] = fdot_mean;
+            sc->r[lane] = r;
+        }
+        if (lane < kMaxFields) {
+            sc->nx_m1[lane] = lane < NF ? m + lat.dt * r : 0.0;
+            sc->nx_hm[lane] = lane < NF ? 0.5 * (a1 * a1) * mu2 : 0.0;
+        }
+        next_pass(lat, sc->nxf);
+        next_pass(lat, sc->nxd);
+    }
+};
 
 // FP64 tail of the start-up pass.  Sums of field i at 6i: sum d, sum d^2,
 // sum d Lap d, sum fdot(0)^2, sum p^{1/2}, (unused); last: sum V at a = 1.
 template <typename T, int NF>
-__device__ __forceinline__ void init_tail(const Lattice &lat, RunState<NF> &s, const double (&tot)[kSumsPerField * NF + 1],
-                                          ce_energy &e)
+__device__ __forceinline__ void init_tail(const Lattice &lat, RunState<NF> &s, const double *tot, ce_energy &e)
 {
 #pragma clang fp contract(off)
     const double Ns = (double)lat.nsites;
@@ -621,12 +750,19 @@ __device__ __forceinline__ void put_partials(const Lattice &lat, const double (*
 // Each thread sums rows threadIdx.x, + blockDim.x, ... in that order; with
 // R > 1 it loads R of them before adding them, so R rows' loads are in
 // flight at once (the sums, and so the result, are the same for every R).
-template <typename T, int NF, int MODE, int R = 1>
+// RUNS (the direct pass, 256 threads): up to kRunRows rows a thread are
+// consecutive ones instead, as a resident block adds the rows of the blocks it stands for.
+template <typename T, int NF, int MODE, int R = 1, bool RUNS = false>
 __device__ __forceinline__ void finish_pass(const Lattice &lat, int grid, int rows, double (*red)[kMaxSums])
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     __shared__ int s_last;
-    RunState<NF> st = load_state<NF>(lat);
+    LaneTail<T, NF> tail;
+    if (MODE == kStep && threadIdx.x < 64) {
+        // the state is this launch's input until the last block's tail
+        tail.load(lat);
+        tail.prepare(lat);
+    }
     if (grid > 1 || rows > 1) {
         __syncthreads();
         if (threadIdx.x < 64) {
@@ -641,8 +777,16 @@ __device__ __forceinline__ void finish_pass(const Lattice &lat, int grid, int ro
         double acc[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; q++) acc[q] = 0.0;
-        const int stride = (int)blockDim.x;
+        int stride = (int)blockDim.x;
         int b = threadIdx.x;
+        if constexpr (RUNS) {
+            if (rows <= kRunRows * stride) {
+                const int run = (rows + stride - 1) / stride;
+                b *= run;
+                rows = min(rows, b + run);
+                stride = 1;
+            }
+        }
         if constexpr (R > 1) {
             for (; b + (R - 1) * stride < rows; b += R * stride) {
                 double v[R][NQ];
@@ -669,24 +813,30 @@ __device__ __forceinline__ void finish_pass(const Lattice &lat, int grid, int ro
         }
         block_sum<NQ>(acc, red);
     }   // one block, one row: its totals are the lattice's
-    if (threadIdx.x == 0) {
-        double tot[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; q++) tot[q] = red[0][q];
-        ce_energy e;
-        if (MODE == kStep)
-            step_tail<T, NF>(lat, st, tot, e);
-        else
-            init_tail<T, NF>(lat, st, tot, e);
-        store_state<NF>(lat, st);
-        lat.ring[e.step % kLogCap] = e;
+    if (threadIdx.x < 64) {
         if (MODE == kStep) {
-            lat.sc->cur ^= 1;
-            if (lat.sc->remaining > 0) lat.sc->remaining -= 1;
+            const double tot = threadIdx.x < NQ ? red[0][threadIdx.x] : 0.0;
+            __shared__ double scratch[2 * kMaxSums];
+            tail.solve(lat, tot, scratch);
+            tail.record(lat);
+            tail.advance();
+            tail.store(lat);
         }
-        if (grid > 1 || rows > 1)
-            for (int i = 0; i <= kTileCounters; i++)
-                __hip_atomic_store(lat.ticket + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) {
+            if (MODE == kStep) {
+                lat.sc->cur ^= 1;
+                if (lat.sc->remaining > 0) lat.sc->remaining -= 1;
+            } else {
+                RunState<NF> st = load_state<NF>(lat);
+                ce_energy e;
+                init_tail<T, NF>(lat, st, red[0], e);
+                store_state<NF>(lat, st);
+                lat.ring[e.step % kLogCap] = e;
+            }
+            if (grid > 1 || rows > 1)
+                for (int i = 0; i <= kTileCounters; i++)
+                    __hip_atomic_store(lat.ticket + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 

@@ -191,10 +191,12 @@ ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes)
     // the device state
     const ce_launch old = s->launch;
     const Lattice saved = s->lat;
+    const ce_sim::Resident resident = s->resident;
     st = apply_launch(s, h.launch);
     if (st != CE_OK) {
         s->launch = old;
         s->lat = saved;
+        s->resident = resident;
         return st;
     }
     CE_HIP(hipStreamSynchronize(s->stream));

@@ -80,6 +80,8 @@ struct Lattice {
     unsigned int *ticket;  // last-block counter, then the tiled pass's tile counters; 0 between launches
     int slots;             // entries per sum in `partials` (at least kMaxBlocks)
     ce_energy *ring;       // [kLogCap]
+    unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords]
+    void *columns;         // resident tiled pass: the tiles' edge columns (the staging chunk, idle during steps)
     int nblocks;           // blocks of the step launch (fixed per lattice)
     int kind;              // kDirect or kTiled3d
     int vec;               // tiled: consecutive x sites per thread (2 or 4)
@@ -91,6 +93,9 @@ struct Lattice {
 
 enum Kind { kDirect = 0, kTiled3d = 1, kStream2d = 2 };
 constexpr int kMaxBlocks = 4096;  // blocks per launch; partial-sum rows per lattice at least this
+constexpr int kRunRows = 3;      // blocks of the direct pass that one resident block takes at most
+constexpr int kSyncRows = 256;    // blocks of a resident pass at most
+constexpr int kTotalWords = 48;  // words kept for one copy of the totals (2 kMaxSums, whole lines)
 constexpr int kTileCounters = 8;  // the tiled pass's tile counters, one per XCD, after the ticket
 
 enum Mode { kStep = 0, kInit = 1 };
@@ -125,11 +130,22 @@ hipError_t launch_batched_stream2d_model(const Lattice *lats, const int *blk_lat
                                          const Lattice &proto, int precision, hipStream_t st);
 template <int MODEL>
 int stream2d_batched_resident_model(const Lattice &proto, int precision);
+// Kernel of the resident direct pass (vb consecutive blocks of the direct
+// launch per block), nullptr where that is not built.  Arguments: Lattice,
+// int src, int steps, unsigned epoch; 256 vb + 64 threads.
+template <int MODEL>
+const void *resident_direct_model(int precision, int dims, int nf, int vb);
+// The same of the tiled 3-D pass (tiles of `planes` whole planes, one per
+// block; bs + 64 threads).
+template <int MODEL>
+const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs, int planes);
 #define CE_DECLARE_MODEL_ENTRIES(M)                                                                             \
     template <> hipError_t launch_direct_model<M>(const Lattice &, int, int, Mode, hipStream_t);                \
     template <> hipError_t launch_batched_direct_model<M>(const Lattice *, const int *, int, int, const Lattice &, \
                                                           int, hipStream_t);                                     \
     template <> int direct_batched_resident_model<M>(const Lattice &, int);                                     \
+    template <> const void *resident_direct_model<M>(int, int, int, int);                                       \
+    template <> const void *resident_tiled_model<M>(int, int, int, int, int, int);                              \
     template <> hipError_t launch_tiled_model<M>(const Lattice &, int, int, Mode, hipStream_t);                 \
     template <> hipError_t launch_batched_tiled_model<M>(const Lattice *, const int *, int, int, const Lattice &, \
                                                          int, hipStream_t);                                      \

@@ -140,7 +140,7 @@ __device__ __forceinline__ void pass_body(const Lattice &lat, int src, int b, in
 
     block_sum<NQ>(acc, red);
     put_partials<NQ>(lat, red, b);
-    finish_pass<T, NF, MODE>(lat, grid, grid, red);
+    finish_pass<T, NF, MODE, 1, true>(lat, grid, grid, red);
 }
 
 template <typename T, int D, int NF, int MODEL, int MODE>

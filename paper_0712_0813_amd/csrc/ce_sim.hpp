@@ -15,7 +15,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
     size_t field_bytes;   // one array of one field
     size_t off_fields;    // 4 * nf arrays
-    size_t off_scalars, off_partials, off_ticket, off_ring, off_maxabs, off_staging;
+    size_t off_scalars, off_partials, off_ticket, off_sync, off_ring, off_maxabs, off_staging;
     size_t total;
     long long staging_elems;
     int nblocks;
@@ -58,6 +58,13 @@ struct ce_sim {
     ce_launch launch{CE_KERNEL_DIRECT, 0, 0, 0, 0, 0};
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // step block starting from buffer 0 / 1
     int graph_k = 0;
+    // resident pass for the current launch (kernel nullptr: none), and the tag
+    // of the last step taken by one
+    struct Resident {
+        const void *kernel = nullptr;
+        int blocks = 0, threads = 0, min_steps = 0;
+    } resident;
+    unsigned epoch = 0;
 };
 
 namespace ce {
