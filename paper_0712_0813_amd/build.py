@@ -29,7 +29,8 @@ HIPCC_FLAGS = [
 
 # kernel families compiled once per model of the potential (quartic,
 # polynomial): the source is built twice with CE_UNIT_MODEL set
-MODEL_UNITS = ("ce_kernels.hip", "ce_resident_direct.hip", "ce_resident_tiled.hip", "ce_step2d.hip", "ce_step3d.hip")
+MODEL_UNITS = ("ce_kernels.hip", "ce_resident_direct.hip", "ce_resident_stream2d.hip", "ce_resident_tiled.hip",
+               "ce_step2d.hip", "ce_step3d.hip")
 
 
 def sources():

@@ -194,9 +194,14 @@ ce_status device_cus(int *cus)
     return CE_OK;
 }
 
-// Kernel of the resident tiled pass for a launch, nullptr if there is none.
+// Kernel of the resident pass for a tiled or 2-D streaming launch of one tile
+// or group of units per block, nullptr if there is none.
 const void *resident_kernel(const ce_params *p, const ce_launch &c)
 {
+    if (c.kernel == CE_KERNEL_STREAM2D)
+        return stream2d_groups(p->N, c.planes) > kSyncRows ? nullptr
+               : p->model == kPoly ? resident_stream2d_model<kPoly>(p->precision, p->nfields, c.planes)
+                                   : resident_stream2d_model<kQuartic>(p->precision, p->nfields, c.planes);
     if (p->N % c.planes != 0 ||
         tiled_tiles(p->N, c.sites_per_thread, c.lanes_per_row, c.block, c.planes) > kSyncRows)
         return nullptr;
@@ -227,6 +232,12 @@ void plan_resident(ce_sim *s)
         r.kernel = resident_kernel(&s->p, c);
         r.blocks = (int)tiled_tiles(lat.N, lat.vec, lat.lpr, lat.bs, lat.zc);
         r.threads = lat.bs + 64;
+    } else if (lat.kind == kStream2d) {
+        // the streaming pass sums per block: one group of units each
+        if (stream2d_groups(lat.N, lat.zc) != lat.nblocks) return;
+        r.kernel = resident_kernel(&s->p, ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, lat.zc, lat.nblocks});
+        r.blocks = lat.nblocks;
+        r.threads = kBlock + 64;
     }
     if (!r.kernel) return;
     // the fewest steps worth a launch: a cooperative one costs about 22 us
@@ -344,6 +355,12 @@ ce_launch default_launch(const ce_params *p, int cus)
 {
     ce_launch c{CE_KERNEL_DIRECT, 0, 0, 0, 0, 0};
     if (p->dims == 2) {
+        // lattices that a resident pass can take: the shortest units that
+        // leave no more groups of four than it has blocks
+        for (int rows = 1; rows <= 16; rows *= 2) {
+            const ce_launch r{CE_KERNEL_STREAM2D, 4, 64, kBlock, rows, 0};
+            if (stream2d_fits(2, p->N, rows) && resident_kernel(p, r)) return r;
+        }
         // rows per unit: the tallest (up to 64) that still gives every
         // compute unit a group of four units
         for (int rows = 64; rows >= 8; rows /= 2)

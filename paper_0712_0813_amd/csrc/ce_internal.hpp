@@ -81,7 +81,7 @@ struct Lattice {
     int slots;             // entries per sum in `partials` (at least kMaxBlocks)
     ce_energy *ring;       // [kLogCap]
     unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords]
-    void *columns;         // resident tiled pass: the tiles' edge columns (the staging chunk, idle during steps)
+    void *columns;         // resident passes: edge columns of the tiles or units (the staging chunk, idle during steps)
     int nblocks;           // blocks of the step launch (fixed per lattice)
     int kind;              // kDirect or kTiled3d
     int vec;               // tiled: consecutive x sites per thread (2 or 4)
@@ -139,6 +139,10 @@ const void *resident_direct_model(int precision, int dims, int nf, int vb);
 // block; bs + 64 threads).
 template <int MODEL>
 const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs, int planes);
+// The same of the 2-D streaming pass (units of `rows` rows, a group of four per
+// block; 320 threads).
+template <int MODEL>
+const void *resident_stream2d_model(int precision, int nf, int rows);
 #define CE_DECLARE_MODEL_ENTRIES(M)                                                                             \
     template <> hipError_t launch_direct_model<M>(const Lattice &, int, int, Mode, hipStream_t);                \
     template <> hipError_t launch_batched_direct_model<M>(const Lattice *, const int *, int, int, const Lattice &, \
@@ -146,6 +150,7 @@ const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs
     template <> int direct_batched_resident_model<M>(const Lattice &, int);                                     \
     template <> const void *resident_direct_model<M>(int, int, int, int);                                       \
     template <> const void *resident_tiled_model<M>(int, int, int, int, int, int);                              \
+    template <> const void *resident_stream2d_model<M>(int, int, int);                                          \
     template <> hipError_t launch_tiled_model<M>(const Lattice &, int, int, Mode, hipStream_t);                 \
     template <> hipError_t launch_batched_tiled_model<M>(const Lattice *, const int *, int, int, const Lattice &, \
                                                          int, hipStream_t);                                      \

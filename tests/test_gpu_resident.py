@@ -21,6 +21,10 @@ SIZES = [
     (1, 4, 1, None), (1, 64, 3, None), (1, 1024, 2, None), (1, 1028, 2, None), (1, 5000, 1, None), (1, 65536, 2, None),
     (2, 4, 2, None), (2, 32, 2, None), (2, 36, 3, None), (2, 300, 3, None), (2, 500, 2, None), (2, 864, 1, None), (2, 1000, 1, None),
     (3, 4, 1, None), (3, 8, 2, None), (3, 16, 2, None), (3, 20, 3, None), (3, 32, 2, None), (3, 48, 2, None),
+    # units: one and several per row, one wave of four at work, 1 to 16 rows
+    (2, 256, 2, (S2, 4, 64, 256, 1, 0)), (2, 256, 3, (S2, 4, 64, 256, 8, 0)), (2, 256, 1, (S2, 4, 64, 256, 16, 4)),
+    (2, 512, 2, (S2, 4, 64, 256, 2, 0)), (2, 768, 2, (S2, 4, 64, 256, 4, 0)), (2, 1024, 1, (S2, 4, 64, 256, 16, 0)),
+    (2, 1024, 2, (S2, 4, 64, 256, 4, 0)),
     # tiles: whole rows and columns, several tiles per direction, 1 to 8 planes
     (3, 32, 2, (T3, 4, 8, 256, 1, 0)), (3, 32, 3, (T3, 4, 8, 256, 4, 8)), (3, 64, 2, (T3, 4, 16, 256, 1, 0)),
     (3, 64, 3, (T3, 4, 16, 256, 2, 0)), (3, 64, 1, (T3, 4, 8, 256, 8, 7)), (3, 64, 2, (T3, 4, 8, 256, 4, 0)),
