@@ -59,7 +59,7 @@ Layout layout_of(const ce_params *p)
     static_assert((1 + kTileCounters) * sizeof(unsigned int) <= kAlign, "ticket and tile counters share one line");
     off += kAlign;
     L.off_sync = off;
-    off += align_up((size_t)2 * (2 * kMaxSums * kSyncRows + 8 * kTotalWords) * sizeof(unsigned long long));
+    off += align_up(((size_t)2 * (2 * kMaxSums * kSyncRows + 8 * kTotalWords) + 1) * sizeof(unsigned long long));
     L.off_ring = off;
     off += align_up((size_t)kLogCap * sizeof(ce_energy));
     L.off_maxabs = off;
@@ -173,14 +173,13 @@ constexpr int kResidentSteps = 256;
 hipError_t launch_resident(ce_sim *s, int steps)
 {
     int src = s->cur;
-    void *args[] = {&s->lat, &src, &steps, &s->epoch};
+    void *args[] = {&s->lat, &src, &steps};
     const dim3 grid(s->resident.blocks), block(s->resident.threads);
     // a single block waits for nobody
     const hipError_t e = s->resident.blocks > 1
                              ? hipLaunchCooperativeKernel(s->resident.kernel, grid, block, args, 0, s->stream)
                              : hipLaunchKernel(s->resident.kernel, grid, block, args, 0, s->stream);
     if (e != hipSuccess) return e;
-    s->epoch += (unsigned)steps;
     s->cur ^= steps & 1;
     s->step += steps;
     return hipSuccess;
@@ -194,21 +193,19 @@ ce_status device_cus(int *cus)
     return CE_OK;
 }
 
-// Kernel of the resident pass for a tiled or 2-D streaming launch of one tile
-// or group of units per block, nullptr if there is none.
-const void *resident_kernel(const ce_params *p, const ce_launch &c)
+const void *resident_kernel(const ce_params *p, const ce_launch &c, bool batched)
 {
     if (c.kernel == CE_KERNEL_STREAM2D)
         return stream2d_groups(p->N, c.planes) > kSyncRows ? nullptr
-               : p->model == kPoly ? resident_stream2d_model<kPoly>(p->precision, p->nfields, c.planes)
-                                   : resident_stream2d_model<kQuartic>(p->precision, p->nfields, c.planes);
+               : p->model == kPoly ? resident_stream2d_model<kPoly>(p->precision, p->nfields, c.planes, batched)
+                                   : resident_stream2d_model<kQuartic>(p->precision, p->nfields, c.planes, batched);
     if (p->N % c.planes != 0 ||
         tiled_tiles(p->N, c.sites_per_thread, c.lanes_per_row, c.block, c.planes) > kSyncRows)
         return nullptr;
     return p->model == kPoly ? resident_tiled_model<kPoly>(p->precision, p->nfields, c.sites_per_thread,
-                                                           c.lanes_per_row, c.block, c.planes)
+                                                           c.lanes_per_row, c.block, c.planes, batched)
                              : resident_tiled_model<kQuartic>(p->precision, p->nfields, c.sites_per_thread,
-                                                              c.lanes_per_row, c.block, c.planes);
+                                                              c.lanes_per_row, c.block, c.planes, batched);
 }
 
 // The resident pass that takes the same steps as s's launch, if there is one:
@@ -229,13 +226,13 @@ void plan_resident(ce_sim *s)
         r.threads = kBlock * vb + 64;
     } else if (lat.kind == kTiled3d) {
         const ce_launch c{CE_KERNEL_TILED3D, lat.vec, lat.lpr, lat.bs, lat.zc, 0};
-        r.kernel = resident_kernel(&s->p, c);
+        r.kernel = resident_kernel(&s->p, c, false);
         r.blocks = (int)tiled_tiles(lat.N, lat.vec, lat.lpr, lat.bs, lat.zc);
         r.threads = lat.bs + 64;
     } else if (lat.kind == kStream2d) {
         // the streaming pass sums per block: one group of units each
         if (stream2d_groups(lat.N, lat.zc) != lat.nblocks) return;
-        r.kernel = resident_kernel(&s->p, ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, lat.zc, lat.nblocks});
+        r.kernel = resident_kernel(&s->p, ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, lat.zc, lat.nblocks}, false);
         r.blocks = lat.nblocks;
         r.threads = kBlock + 64;
     }
@@ -359,7 +356,7 @@ ce_launch default_launch(const ce_params *p, int cus)
         // leave no more groups of four than it has blocks
         for (int rows = 1; rows <= 16; rows *= 2) {
             const ce_launch r{CE_KERNEL_STREAM2D, 4, 64, kBlock, rows, 0};
-            if (stream2d_fits(2, p->N, rows) && resident_kernel(p, r)) return r;
+            if (stream2d_fits(2, p->N, rows) && resident_kernel(p, r, false)) return r;
         }
         // rows per unit: the tallest (up to 64) that still gives every
         // compute unit a group of four units
@@ -424,7 +421,7 @@ ce_launch default_launch(const ce_params *p, int cus)
         for (int z = 1; z <= 8 && p->N >= 64; z *= 2) {
             if (p->N % z || !tiled_fits(3, p->N, v, l, bs, z) || tiled_tiles(p->N, v, l, bs, z) > kSyncRows) continue;
             const ce_launch r{CE_KERNEL_TILED3D, v, l, bs, z, 0};
-            if (resident_kernel(p, r)) return r;
+            if (resident_kernel(p, r, false)) return r;
         }
     }
     if (p->N >= 64) {

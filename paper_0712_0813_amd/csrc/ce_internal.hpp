@@ -80,7 +80,7 @@ struct Lattice {
     unsigned int *ticket;  // last-block counter, then the tiled pass's tile counters; 0 between launches
     int slots;             // entries per sum in `partials` (at least kMaxBlocks)
     ce_energy *ring;       // [kLogCap]
-    unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords]
+    unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords], the last step's tag
     void *columns;         // resident passes: edge columns of the tiles or units (the staging chunk, idle during steps)
     int nblocks;           // blocks of the step launch (fixed per lattice)
     int kind;              // kDirect or kTiled3d
@@ -132,25 +132,26 @@ template <int MODEL>
 int stream2d_batched_resident_model(const Lattice &proto, int precision);
 // Kernel of the resident direct pass (vb consecutive blocks of the direct
 // launch per block), nullptr where that is not built.  Arguments: Lattice,
-// int src, int steps, unsigned epoch; 256 vb + 64 threads.
+// int src, int steps; 256 vb + 64 threads.
 template <int MODEL>
 const void *resident_direct_model(int precision, int dims, int nf, int vb);
 // The same of the tiled 3-D pass (tiles of `planes` whole planes, one per
-// block; bs + 64 threads).
+// block; bs + 64 threads), and of its batched form: arguments const Lattice
+// *lats, int lattices, int tiles of each, int steps.
 template <int MODEL>
-const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs, int planes);
+const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs, int planes, bool batched);
 // The same of the 2-D streaming pass (units of `rows` rows, a group of four per
-// block; 320 threads).
+// block; 320 threads) and its batched form.
 template <int MODEL>
-const void *resident_stream2d_model(int precision, int nf, int rows);
+const void *resident_stream2d_model(int precision, int nf, int rows, bool batched);
 #define CE_DECLARE_MODEL_ENTRIES(M)                                                                             \
     template <> hipError_t launch_direct_model<M>(const Lattice &, int, int, Mode, hipStream_t);                \
     template <> hipError_t launch_batched_direct_model<M>(const Lattice *, const int *, int, int, const Lattice &, \
                                                           int, hipStream_t);                                     \
     template <> int direct_batched_resident_model<M>(const Lattice &, int);                                     \
     template <> const void *resident_direct_model<M>(int, int, int, int);                                       \
-    template <> const void *resident_tiled_model<M>(int, int, int, int, int, int);                              \
-    template <> const void *resident_stream2d_model<M>(int, int, int);                                          \
+    template <> const void *resident_tiled_model<M>(int, int, int, int, int, int, bool);                        \
+    template <> const void *resident_stream2d_model<M>(int, int, int, bool);                                    \
     template <> hipError_t launch_tiled_model<M>(const Lattice &, int, int, Mode, hipStream_t);                 \
     template <> hipError_t launch_batched_tiled_model<M>(const Lattice *, const int *, int, int, const Lattice &, \
                                                          int, hipStream_t);                                      \

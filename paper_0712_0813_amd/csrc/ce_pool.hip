@@ -54,6 +54,10 @@ struct ClassTable {
     int grid = 0;                // hardware blocks of the batched launch
     std::vector<Member *> mems;  // the member of each descriptor
     long long *d_rem = nullptr;  // step budgets for the next block (quotas)
+    // resident form (nullptr: none): a block's steps in one launch of
+    // res_grid blocks, res_tiles to a member
+    const void *res_kernel = nullptr;
+    int res_grid = 0, res_tiles = 0;
 };
 
 }  // namespace
@@ -129,6 +133,17 @@ namespace {
 ce_launch member_launch(const ce_params *p)
 {
     ce_launch c{CE_KERNEL_DIRECT, 0, 0, 0, 0, pass_blocks(p->dims, p->N)};
+    // FP32 planes that a resident pass can take: units of sixteen rows, of
+    // eight up to 256^2, where a member has few units, and where sixteen do not
+    // fit (us a pool step with 8 and 16 rows, and 64 in the batched pass: 128 x
+    // 256^2 x 2: 35, 30, 82; 8 x 256^2 x 2: 9, 15; 64 x 512^2 x 2: 80, 71, 121;
+    // 32 x 1024^2 x 2: 165, 145, 230)
+    for (int a = 0; a < 2 && p->dims == 2; a++) {
+        const int rows = (p->N > 256) == (a == 0) ? 16 : 8;
+        const ce_launch r{CE_KERNEL_STREAM2D, 4, 64, kBlock, rows, (int)std::min<long long>(
+                              stream2d_fits(2, p->N, rows) ? stream2d_groups(p->N, rows) : 0, kMaxBlocks)};
+        if (r.grid > 0 && resident_kernel(p, r, true)) return r;
+    }
     if (p->dims == 2 && stream2d_fits(2, p->N, 8)) {
         // one group of four units per block; the tallest units (up to 64
         // rows) that still give the member two blocks
@@ -143,6 +158,20 @@ ce_launch member_launch(const ce_params *p)
         return c;
     }
     if (p->dims != 3) return c;
+    // small FP32 lattices that a resident pass can take: tiles of eight planes,
+    // of four with three fields (whose state then fits).  Taller tiles
+    // exchange less (us a pool step with 8 and 4 planes, and whole columns in
+    // the batched pass: 256 x 64^3 x 2: 297, 455, 492; x 3: 623, 561, 677; 16 x
+    // 64^3 x 2: 19, 29, 148; 16 x 32^3 x 2: 9, 7, 71; 32 x 128^3 x 2: 342 with
+    // eight, 484 on columns).
+    for (int a = 0; a < 2; a++)
+        for (int b = 0; b < 2; b++) {
+            const int z = (p->nfields <= 2) == (b == 0) ? 8 : 4, l = 16 >> a;
+            if (p->N % z || !tiled_fits(3, p->N, 4, l, 256, z)) continue;
+            const long long tiles = tiled_tiles(p->N, 4, l, 256, z);
+            const ce_launch r{CE_KERNEL_TILED3D, 4, l, 256, z, (int)tiles};
+            if (tiles <= kSyncRows && resident_kernel(p, r, true)) return r;
+        }
     const int shapes[3][3] = {{4, 64, 256}, {4, 16, 256}, {4, 8, 256}};
     for (int a = 0; a < 3; a++) {
         const int v = shapes[a][0], l = shapes[a][1], bs = shapes[a][2];
@@ -202,6 +231,35 @@ ce_status trim_cache(ce_pool *pl, size_t want)
     return CE_OK;
 }
 
+// The resident form of a class, if it has one and it pays: every member the
+// same tiles, and enough members that their tiles fill half the compute units
+// or nothing else to run beside them (resident launches of different classes
+// follow one another).
+void plan_resident_class(ClassTable &t, int cus, bool only)
+{
+    const Lattice &p = t.proto;
+    if (p.kind == kDirect) return;
+    const long long tiles =
+        p.kind == kTiled3d ? tiled_tiles(p.N, p.vec, p.lpr, p.bs, p.zc) : stream2d_groups(p.N, p.zc);
+    for (const Lattice &L : t.lats)
+        // (the streaming pass sums per block: one group of units each)
+        if (L.N != p.N || L.zc != p.zc || (p.kind == kStream2d && L.nblocks != tiles)) return;
+    const ce_launch c{p.kind == kTiled3d ? CE_KERNEL_TILED3D : CE_KERNEL_STREAM2D, p.vec, p.lpr, p.bs, p.zc, 0};
+    const void *kernel = resident_kernel(&t.mems[0]->sim->p, c, true);
+    if (!kernel) return;
+    int per = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, p.bs + 64, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    const long long fit = (long long)per * cus / tiles;   // members at a time
+    const long long n = (long long)t.lats.size();
+    if (fit < 1 || !(only || n * tiles >= cus / 2)) return;
+    t.res_kernel = kernel;
+    t.res_tiles = (int)tiles;
+    t.res_grid = (int)(std::min(fit, n) * tiles);
+}
+
 // Rebuild the per-class launch tables for the members with steps left.
 ce_status ensure_lanes(ce_pool *pl)
 {
@@ -255,6 +313,7 @@ ce_status rebuild(ce_pool *pl)
         long long g = std::min<long long>(total, (long long)per * cus);
         if (g >= 8) g = g / 8 * 8;
         t.grid = (int)g;
+        plan_resident_class(t, cus, by_class.size() == 1);
     }
     {
         const ce_status st = ensure_lanes(pl);
@@ -314,9 +373,27 @@ ce_status rebuild(ce_pool *pl)
     return CE_OK;
 }
 
+// k steps of a class: one resident launch, or k batched ones.
+hipError_t launch_class_steps(const ClassTable &t, hipStream_t st, int k);
+
 hipError_t launch_class(const ClassTable &t, hipStream_t st)
 {
     return launch_batched(t.d_lats, t.d_blk, (int)t.blk_lat.size(), t.grid, t.proto, t.precision, st);
+}
+
+hipError_t launch_class_steps(const ClassTable &t, hipStream_t st, int k)
+{
+    if (t.res_kernel && k > 1) {
+        const Lattice *lats = t.d_lats;
+        int n = (int)t.lats.size(), tiles = t.res_tiles;
+        void *args[] = {&lats, &n, &tiles, &k};
+        return hipLaunchCooperativeKernel(t.res_kernel, dim3(t.res_grid), dim3(t.proto.bs + 64), args, 0, st);
+    }
+    for (int i = 0; i < k; i++) {
+        const hipError_t e = launch_class(t, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // k steps of every class, ordered after the work already on `st` and ahead of
@@ -325,18 +402,12 @@ hipError_t launch_class(const ClassTable &t, hipStream_t st)
 hipError_t launch_block(ce_pool *pl, hipStream_t st, int k)
 {
     const int nc = (int)pl->classes.size();
-    if (nc == 1) {
-        for (int i = 0; i < k; i++) {
-            const hipError_t e = launch_class(pl->classes[0], st);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
-    }
+    if (nc == 1) return launch_class_steps(pl->classes[0], st, k);
     const int nl = std::min(nc, ce_pool::kLanes);
     hipError_t e = hipEventRecord(pl->fork_ev, st);
     for (int l = 0; l < nl && e == hipSuccess; l++) e = hipStreamWaitEvent(pl->lanes[l], pl->fork_ev, 0);
     for (int c = 0; c < nc && e == hipSuccess; c++)
-        for (int i = 0; i < k && e == hipSuccess; i++) e = launch_class(pl->classes[c], pl->lanes[pl->lane_of[c]]);
+        e = launch_class_steps(pl->classes[c], pl->lanes[pl->lane_of[c]], k);
     for (int l = 0; l < nl && e == hipSuccess; l++) {
         e = hipEventRecord(pl->join_ev[l], pl->lanes[l]);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, pl->join_ev[l], 0);
@@ -649,8 +720,11 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
     // A capture is attempted only while no admission is running on another
     // thread (its HIP calls could invalidate the capture); a failed capture
     // falls back to launching the block directly.
+    // Resident classes take a block in one launch and are not captured.
     hipGraphExec_t graph = nullptr;
-    if (k > 1 && pl->blocks_since_rebuild > 0) {
+    bool resident = false;
+    for (const ClassTable &t : pl->classes) resident |= t.res_kernel != nullptr;
+    if (k > 1 && pl->blocks_since_rebuild > 0 && !resident) {
         auto it = T.graphs.find(k);
         if (it != T.graphs.end()) {
             graph = it->second;

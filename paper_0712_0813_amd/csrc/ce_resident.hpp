@@ -254,6 +254,13 @@ __device__ __forceinline__ void next_coef(PassCoef<T, NF> &c, const PassScalars<
     }
 }
 
+// The tag of the last step a resident pass took, after the totals.  Block 0
+// writes it when it has every block's last step, so every block has read it.
+__device__ __forceinline__ unsigned long long *last_tag(const Lattice &lat)
+{
+    return lat.sync + (long long)2 * (2 * kMaxSums * kSyncRows + kTotalCopies * kTotalWords);
+}
+
 // Word j of copy c of the totals of step `tag`, after the rows.
 __device__ __forceinline__ unsigned long long *total_word(const Lattice &lat, int c, int j, unsigned tag)
 {
@@ -294,7 +301,8 @@ __device__ __forceinline__ double sum_rows(const Lattice &lat, int q, int nblk, 
 // One wavefront: the totals over every block's row of step `tag`; lane q
 // receives sum q.
 template <int NQ>
-__device__ __forceinline__ double collect_totals(const Lattice &lat, int nblk, unsigned tag, double *scratch, bool &alive)
+__device__ __forceinline__ double collect_totals(const Lattice &lat, int rank, int nblk, unsigned tag, double *scratch,
+                                                 bool &alive)
 {
     const int lane = __lane_id();
     const int q = min(lane, NQ - 1);
@@ -315,16 +323,16 @@ __device__ __forceinline__ double collect_totals(const Lattice &lat, int nblk, u
         return tot;
     }
     const unsigned long long t = (unsigned long long)tag << 32;
-    if ((int)blockIdx.x < NQ) {
-        const long long bits = __double_as_longlong(sum_rows(lat, blockIdx.x, nblk, tag, alive));
+    if (rank < NQ) {
+        const long long bits = __double_as_longlong(sum_rows(lat, rank, nblk, tag, alive));
         if (lane < 2 * kTotalCopies)
-            __hip_atomic_store(total_word(lat, lane >> 1, 2 * blockIdx.x + (lane & 1), tag),
+            __hip_atomic_store(total_word(lat, lane >> 1, 2 * rank + (lane & 1), tag),
                                t | ((lane & 1) ? (unsigned)(bits >> 32) : (unsigned)(bits & 0xffffffffLL)),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     unsigned long long lo = t, hi = t;
     bool seen = false;
-    const int copy = blockIdx.x % kTotalCopies;
+    const int copy = rank % kTotalCopies;
     for (int spin = 0; alive && !seen && spin < kSpinLimit; spin++) {
         lo = __hip_atomic_load(total_word(lat, copy, 2 * q, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         hi = __hip_atomic_load(total_word(lat, copy, 2 * q + 1, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -342,18 +350,19 @@ __device__ __forceinline__ double collect_totals(const Lattice &lat, int nblk, u
 // waves' sums are in red and their boundary stores have arrived, (3; several
 // blocks) every block has published the step, so its boundary may be read, (4)
 // the next pass's coefficients are in `next`.
+// The block is the `rank`-th of the nblk that work the lattice.
 template <typename T, int NF, int GROUPS, int WAVES>
-__device__ __forceinline__ void service_wave(const Lattice &lat, int steps, unsigned epoch, int row,
+__device__ __forceinline__ void service_wave(const Lattice &lat, int steps, int rank, int nblk, int row,
                                              const double (*red)[kMaxSums], PassScalars<T> &next)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     __shared__ double scratch[2 * kMaxSums];
     const int lane = threadIdx.x & 63;
     const int q = min(lane, NQ - 1);
-    const int nblk = gridDim.x;
     bool alive = true;
     LaneTail<T, NF> tail;
     tail.load(lat);
+    const unsigned epoch = (unsigned)*last_tag(lat);
     for (int step = 0; step < steps; step++) {
         const unsigned tag = epoch + (unsigned)step + 1u;
         tail.prepare(lat);
@@ -369,18 +378,40 @@ __device__ __forceinline__ void service_wave(const Lattice &lat, int steps, unsi
         }
         if (nblk > 1) {
             publish_row<NQ>(lat, tot, row, tag);
-            tot = collect_totals<NQ>(lat, nblk, tag, scratch, alive);
+            tot = collect_totals<NQ>(lat, rank, nblk, tag, scratch, alive);
             __syncthreads();   // (3)
         }
         tail.solve(lat, tot, scratch);
         tail.next_pass(lat, next);
         __syncthreads();   // (4)
-        if (blockIdx.x == 0) tail.record(lat);
+        if (rank == 0) tail.record(lat);
         tail.advance();
     }
-    if (blockIdx.x == 0) {
+    if (rank == 0) {
         tail.store(lat);
-        if (lane == 0) lat.sc->cur ^= steps & 1;
+        if (lane == 0) {
+            lat.sc->cur ^= steps & 1;
+            if (lat.sc->remaining > 0) lat.sc->remaining -= min((long long)steps, lat.sc->remaining);
+            *last_tag(lat) = epoch + (unsigned)steps;
+        }
+    }
+}
+
+// A pool's resident launch: up to k steps of each of n lattices that nblk
+// blocks work.  The grid's blocks form groups of nblk; group g takes lattices
+// g, g + groups, ... one after the other, each for all its steps.
+template <typename Body>
+__device__ __forceinline__ void run_members(const Lattice *lats, int n, int nblk, int k, Body body)
+{
+    const int rank = blockIdx.x % nblk, groups = gridDim.x / nblk;
+    for (int l = blockIdx.x / nblk; l < n; l += groups) {
+        const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
+        // the steps left and the buffer change only when every block of the
+        // group has published the last step, so all read the same
+        const int steps = (int)min((long long)k, lat.sc->remaining);
+        if (steps <= 0) continue;
+        body(lat, lat.sc->cur, steps, rank, nblk);
+        __syncthreads();   // the next lattice takes over the block's LDS
     }
 }
 

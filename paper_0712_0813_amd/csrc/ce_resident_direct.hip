@@ -26,8 +26,7 @@ namespace {
 using namespace dev;
 
 template <typename T, int D, int NF, int MODEL, int VB>
-__global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattice lat, int src, int steps,
-                                                                         unsigned epoch)
+__global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattice lat, int src, int steps)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     constexpr int Q = kBlock * VB;
@@ -38,7 +37,7 @@ __global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattic
 
     const int t = threadIdx.x, wave = t >> 6;
     if (t >= Q) {
-        service_wave<T, NF, VB, 4>(lat, steps, epoch, blockIdx.x, red, next);
+        service_wave<T, NF, VB, 4>(lat, steps, blockIdx.x, gridDim.x, blockIdx.x, red, next);
         return;
     }
     const int N = lat.N;

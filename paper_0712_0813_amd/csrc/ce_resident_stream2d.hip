@@ -26,8 +26,9 @@ using namespace dev;
 
 constexpr int kSeg = 256;   // x sites per unit
 
+// The block is the `rank`-th of the nblk that work the lattice.
 template <typename T, int NF, int MODEL, int R>
-__global__ __launch_bounds__(kBlock + 64) void resident_stream2d_kernel(Lattice lat, int src, int steps, unsigned epoch)
+__device__ __forceinline__ void resident_stream2d_body(const Lattice &lat, int src, int steps, int rank, int nblk)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     constexpr int WAVES = kBlock / 64;
@@ -40,14 +41,14 @@ __global__ __launch_bounds__(kBlock + 64) void resident_stream2d_kernel(Lattice 
     __shared__ PassScalars<T> next;
 
     if (threadIdx.x >= kBlock) {
-        service_wave<T, NF, 1, WAVES>(lat, steps, epoch, blockIdx.x, red, next);
+        service_wave<T, NF, 1, WAVES>(lat, steps, rank, nblk, rank, red, next);
         return;
     }
     const int N = lat.N;
     const int nseg = N / kSeg, nrow = N / R;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int unit = (int)xcd_item(blockIdx.x, 0, gridDim.x, gridDim.x) * WAVES + wave;
+    const int unit = (int)xcd_item(rank, 0, nblk, nblk) * WAVES + wave;
     const bool active = unit < nseg * nrow;
     const int seg = unit % nseg, ur = unit / nseg;
     const int y0 = ur * R;
@@ -247,11 +248,26 @@ __global__ __launch_bounds__(kBlock + 64) void resident_stream2d_kernel(Lattice 
         }
         stores_arrived();
         __syncthreads();   // (2)
-        if (gridDim.x > 1) __syncthreads();   // (3)
+        if (nblk > 1) __syncthreads();   // (3)
         if (!last) load_halo(out, true);      // while the service wave runs the tail
         __syncthreads();   // (4)
         next_coef<T, NF, MODEL>(c, next);
     }
+}
+
+template <typename T, int NF, int MODEL, int R>
+__global__ __launch_bounds__(kBlock + 64) void resident_stream2d_kernel(Lattice lat, int src, int steps)
+{
+    resident_stream2d_body<T, NF, MODEL, R>(lat, src, steps, blockIdx.x, gridDim.x);
+}
+
+// Up to k steps of each of n lattices; see run_members.
+template <typename T, int NF, int MODEL, int R>
+__global__ __launch_bounds__(kBlock + 64) void resident_stream2d_batched(const Lattice *lats, int n, int nblk, int k)
+{
+    run_members(lats, n, nblk, k, [](const Lattice &lat, int src, int steps, int rank, int blocks) {
+        resident_stream2d_body<T, NF, MODEL, R>(lat, src, steps, rank, blocks);
+    });
 }
 
 // Built where p and the halo stay in registers (a block of five waves has 256
@@ -262,29 +278,37 @@ constexpr bool built()
     return 4 * R * NF * (int)sizeof(T) / 4 <= 128 && R * NF * kSeg * 4 * (int)sizeof(T) <= 150 * 1024;
 }
 
-template <typename T, int NF, int MODEL>
-const void *kernel_rows(int rows)
+template <typename T, int NF, int MODEL, int R>
+const void *kernel_if_built(bool batched)
 {
-    if (rows == 1)
-        if constexpr (built<T, NF, 1>()) return (const void *)resident_stream2d_kernel<T, NF, MODEL, 1>;
-    if (rows == 2)
-        if constexpr (built<T, NF, 2>()) return (const void *)resident_stream2d_kernel<T, NF, MODEL, 2>;
-    if (rows == 4)
-        if constexpr (built<T, NF, 4>()) return (const void *)resident_stream2d_kernel<T, NF, MODEL, 4>;
-    if (rows == 8)
-        if constexpr (built<T, NF, 8>()) return (const void *)resident_stream2d_kernel<T, NF, MODEL, 8>;
-    if (rows == 16)
-        if constexpr (built<T, NF, 16>()) return (const void *)resident_stream2d_kernel<T, NF, MODEL, 16>;
+    if constexpr (built<T, NF, R>()) {
+        if (!batched) return (const void *)resident_stream2d_kernel<T, NF, MODEL, R>;
+        // pools: FP32 units of eight or sixteen rows (see member_launch)
+        if constexpr (sizeof(T) == 4 && R >= 8) return (const void *)resident_stream2d_batched<T, NF, MODEL, R>;
+    }
     return nullptr;
 }
 
+template <typename T, int NF, int MODEL>
+const void *kernel_rows(int rows, bool batched)
+{
+    switch (rows) {
+    case 1: return kernel_if_built<T, NF, MODEL, 1>(batched);
+    case 2: return kernel_if_built<T, NF, MODEL, 2>(batched);
+    case 4: return kernel_if_built<T, NF, MODEL, 4>(batched);
+    case 8: return kernel_if_built<T, NF, MODEL, 8>(batched);
+    case 16: return kernel_if_built<T, NF, MODEL, 16>(batched);
+    default: return nullptr;
+    }
+}
+
 template <typename T, int MODEL>
-const void *kernel_nf(int nf, int rows)
+const void *kernel_nf(int nf, int rows, bool batched)
 {
     switch (nf) {
-    case 1: return kernel_rows<T, 1, MODEL>(rows);
-    case 2: return kernel_rows<T, 2, MODEL>(rows);
-    case 3: return kernel_rows<T, 3, MODEL>(rows);
+    case 1: return kernel_rows<T, 1, MODEL>(rows, batched);
+    case 2: return kernel_rows<T, 2, MODEL>(rows, batched);
+    case 3: return kernel_rows<T, 3, MODEL>(rows, batched);
     default: return nullptr;
     }
 }
@@ -295,9 +319,10 @@ const void *kernel_nf(int nf, int rows)
 constexpr int kUnit = CE_UNIT_MODEL;
 
 template <>
-const void *resident_stream2d_model<kUnit>(int precision, int nf, int rows)
+const void *resident_stream2d_model<kUnit>(int precision, int nf, int rows, bool batched)
 {
-    return precision == CE_FP64 ? kernel_nf<double, kUnit>(nf, rows) : kernel_nf<float, kUnit>(nf, rows);
+    return precision == CE_FP64 ? kernel_nf<double, kUnit>(nf, rows, batched)
+                                : kernel_nf<float, kUnit>(nf, rows, batched);
 }
 
 }  // namespace ce

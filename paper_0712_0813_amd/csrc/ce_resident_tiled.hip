@@ -24,8 +24,9 @@ namespace {
 
 using namespace dev;
 
+// The block is the `rank`-th of the nblk that work the lattice.
 template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
-__global__ __launch_bounds__(BS + 64) void resident_tiled_kernel(Lattice lat, int src, int steps, unsigned epoch)
+__device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src, int steps, int rank, int nblk)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     constexpr int TX = VEC * LPR, TY = BS / LPR;
@@ -42,10 +43,10 @@ __global__ __launch_bounds__(BS + 64) void resident_tiled_kernel(Lattice lat, in
     const int N = lat.N;
     const int ntx = N / TX, nty = N / TY, nz = N / ZP;
     // neighbouring tiles on one XCD, as in the tiled pass
-    const int tile = (int)xcd_item(blockIdx.x, 0, gridDim.x, gridDim.x);
+    const int tile = (int)xcd_item(rank, 0, nblk, nblk);
     const int t = threadIdx.x;
     if (t >= BS) {
-        service_wave<T, NF, 1, BS / 64>(lat, steps, epoch, tile, red, next);
+        service_wave<T, NF, 1, BS / 64>(lat, steps, rank, nblk, tile, red, next);
         return;
     }
     const int wave = t >> 6;
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(BS + 64) void resident_tiled_kernel(Lattice lat, in
     Vec<T, VEC> zd[2][NF], zp[2][NF], yd[HY][NF], yp[HY][NF];
     T xd[HX][NF], xp[HX][NF];
     const __amdgpu_buffer_rsrc_t cols = agent_buffer(lat.columns);
-    const unsigned csize = gridDim.x * 2 * CSTRIDE;   // of one buffer's columns
+    const unsigned csize = nblk * 2 * CSTRIDE;   // of one buffer's columns
     auto load_halo = [&](int buf, bool packed) {
 #pragma unroll
         for (int i = 0; i < NF; i++) {
@@ -270,11 +271,36 @@ __global__ __launch_bounds__(BS + 64) void resident_tiled_kernel(Lattice lat, in
         }
         stores_arrived();
         __syncthreads();   // (2)
-        if (gridDim.x > 1) __syncthreads();   // (3)
-        if (!last) load_halo(out, true);            // while the service wave runs the tail
+        if (nblk > 1) __syncthreads();   // (3)
+        if (!last) load_halo(out, true); // while the service wave runs the tail
         __syncthreads();   // (4)
         next_coef<T, NF, MODEL>(c, next);
     }
+}
+
+// Waves per SIMD aimed at: three leave 168 registers, and two blocks of a pool
+// on a compute unit, one working its sites while the other exchanges its sums.
+template <typename T, int NF, int BS, int ZP>
+constexpr int waves_wanted()
+{
+    return BS == 256 && sizeof(T) == 4 && NF <= 2 && NF * ZP <= 8 ? 3 : 1;
+}
+
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
+__global__ __launch_bounds__(BS + 64, (waves_wanted<T, NF, BS, ZP>())) void resident_tiled_kernel(Lattice lat, int src,
+                                                                                                int steps)
+{
+    resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP>(lat, src, steps, blockIdx.x, gridDim.x);
+}
+
+// Up to k steps of each of n lattices; see run_members.
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
+__global__ __launch_bounds__(BS + 64, (waves_wanted<T, NF, BS, ZP>())) void
+resident_tiled_batched(const Lattice *lats, int n, int nblk, int k)
+{
+    run_members(lats, n, nblk, k, [](const Lattice &lat, int src, int steps, int rank, int blocks) {
+        resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP>(lat, src, steps, rank, blocks);
+    });
 }
 
 // Built where p and the halo stay in registers (a block of five waves has 256
@@ -287,46 +313,52 @@ constexpr bool built()
            ZP * NF * tile * (int)sizeof(T) <= 150 * 1024;
 }
 
-template <typename T, int NF, int MODEL, int VEC, int LPR, int BS>
-const void *kernel_planes(int planes)
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
+const void *kernel_if_built(bool batched)
 {
-    if (planes == 1)
-        if constexpr (built<T, NF, VEC, LPR, BS, 1>())
-            return (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, 1>;
-    if (planes == 2)
-        if constexpr (built<T, NF, VEC, LPR, BS, 2>())
-            return (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, 2>;
-    if (planes == 4)
-        if constexpr (built<T, NF, VEC, LPR, BS, 4>())
-            return (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, 4>;
-    if (planes == 8)
-        if constexpr (built<T, NF, VEC, LPR, BS, 8>())
-            return (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, 8>;
+    if constexpr (built<T, NF, VEC, LPR, BS, ZP>()) {
+        if (!batched) return (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, ZP>;
+        // pools: FP32 tiles of four or eight planes (see member_launch)
+        if constexpr (sizeof(T) == 4 && ZP >= 4)
+            return (const void *)resident_tiled_batched<T, NF, MODEL, VEC, LPR, BS, ZP>;
+    }
     return nullptr;
+}
+
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS>
+const void *kernel_planes(int planes, bool batched)
+{
+    switch (planes) {
+    case 1: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 1>(batched);
+    case 2: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 2>(batched);
+    case 4: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 4>(batched);
+    case 8: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 8>(batched);
+    default: return nullptr;
+    }
 }
 
 // FP32: four sites per thread, tiles of 64 x 16 and 32 x 32 sites.  FP64: two
 // sites per thread on twice the threads, the same tiles; four spilled.
 template <typename T, int NF, int MODEL>
-const void *kernel_shape(int vec, int lpr, int bs, int planes)
+const void *kernel_shape(int vec, int lpr, int bs, int planes, bool batched)
 {
     if constexpr (sizeof(T) == 4) {
-        if (vec == 4 && lpr == 16 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 16, 256>(planes);
-        if (vec == 4 && lpr == 8 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 8, 256>(planes);
+        if (vec == 4 && lpr == 16 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 16, 256>(planes, batched);
+        if (vec == 4 && lpr == 8 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 8, 256>(planes, batched);
     } else {
-        if (vec == 2 && lpr == 32 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 32, 512>(planes);
-        if (vec == 2 && lpr == 16 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 16, 512>(planes);
+        if (vec == 2 && lpr == 32 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 32, 512>(planes, batched);
+        if (vec == 2 && lpr == 16 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 16, 512>(planes, batched);
     }
     return nullptr;
 }
 
 template <typename T, int MODEL>
-const void *kernel_nf(int nf, int vec, int lpr, int bs, int planes)
+const void *kernel_nf(int nf, int vec, int lpr, int bs, int planes, bool batched)
 {
     switch (nf) {
-    case 1: return kernel_shape<T, 1, MODEL>(vec, lpr, bs, planes);
-    case 2: return kernel_shape<T, 2, MODEL>(vec, lpr, bs, planes);
-    case 3: return kernel_shape<T, 3, MODEL>(vec, lpr, bs, planes);
+    case 1: return kernel_shape<T, 1, MODEL>(vec, lpr, bs, planes, batched);
+    case 2: return kernel_shape<T, 2, MODEL>(vec, lpr, bs, planes, batched);
+    case 3: return kernel_shape<T, 3, MODEL>(vec, lpr, bs, planes, batched);
     default: return nullptr;
     }
 }
@@ -337,10 +369,10 @@ const void *kernel_nf(int nf, int vec, int lpr, int bs, int planes)
 constexpr int kUnit = CE_UNIT_MODEL;
 
 template <>
-const void *resident_tiled_model<kUnit>(int precision, int nf, int vec, int lpr, int bs, int planes)
+const void *resident_tiled_model<kUnit>(int precision, int nf, int vec, int lpr, int bs, int planes, bool batched)
 {
-    return precision == CE_FP64 ? kernel_nf<double, kUnit>(nf, vec, lpr, bs, planes)
-                                : kernel_nf<float, kUnit>(nf, vec, lpr, bs, planes);
+    return precision == CE_FP64 ? kernel_nf<double, kUnit>(nf, vec, lpr, bs, planes, batched)
+                                : kernel_nf<float, kUnit>(nf, vec, lpr, bs, planes, batched);
 }
 
 }  // namespace ce

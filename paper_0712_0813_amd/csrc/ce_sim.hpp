@@ -58,13 +58,11 @@ struct ce_sim {
     ce_launch launch{CE_KERNEL_DIRECT, 0, 0, 0, 0, 0};
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // step block starting from buffer 0 / 1
     int graph_k = 0;
-    // resident pass for the current launch (kernel nullptr: none), and the tag
-    // of the last step taken by one
+    // resident pass for the current launch (kernel nullptr: none)
     struct Resident {
         const void *kernel = nullptr;
         int blocks = 0, threads = 0, min_steps = 0;
     } resident;
-    unsigned epoch = 0;
 };
 
 namespace ce {
@@ -76,6 +74,9 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg);
 // the recorded field maxima and queue the start-up half step.
 ce_status start_run(ce_sim *s);
 void drop_graphs(ce_sim *s);
+// Kernel of the resident pass of a tiled or 2-D streaming launch with one tile
+// or group of units per block (batched: of its pool form), nullptr if none.
+const void *resident_kernel(const ce_params *p, const ce_launch &c, bool batched);
 
 }  // namespace host
 }  // namespace ce
