@@ -18,10 +18,16 @@ __device__ inline double2 cmulc(double2 w, double2 b)  // conj(w) * b
     return make_double2(w.x * b.x + w.y * b.y, w.x * b.y - w.y * b.x);
 }
 
+// LDS place of value i of a line: one value of padding after every 16, so that
+// the power-of-two strides of the stages and of the bit reversal spread over
+// the 64 banks instead of meeting in a few.  A line takes line_stride(N).
+__device__ inline int padded(int i) { return i + (i >> 4); }
+__host__ __device__ inline int line_stride(int N) { return N + (N >> 4); }
+
 __device__ inline int bitrev(int p, int logN) { return (int)(__brev((unsigned)p) >> (32 - logN)); }
 
 // In-place DFT of `lines` lines of N values (N = 2^logN) held bit-reversed in
-// LDS: sum_p v_p e^{s 2 pi i p x / N}, s = +1 (inverse, kForward false) or -1,
+// LDS (value i of line l at l line_stride(N) + padded(i)): sum_p v_p e^{s 2 pi i p x / N}, s = +1 (inverse, kForward false) or -1,
 // no normalisation.  tw[q] = e^{2 pi i q/N} for q < N/2.  Every thread of the
 // block must call it (it synchronises after each pass).
 //
@@ -44,19 +50,20 @@ __device__ void lds_fft(double2 *buf, int N, int logN, int lines, const double2 
             const int b = idx & (quarterN - 1);
             const int j = b & (half - 1);
             const int i0 = ((b >> s) << (s + 2)) + j;
-            double2 *x = buf + line * N;
-            const double2 x0 = x[i0], x1 = x[i0 + half], x2 = x[i0 + 2 * half], x3 = x[i0 + 3 * half];
+            double2 *x = buf + line * line_stride(N);
+            const int a0 = padded(i0), a1 = padded(i0 + half), a2 = padded(i0 + 2 * half), a3 = padded(i0 + 3 * half);
+            const double2 x0 = x[a0], x1 = x[a1], x2 = x[a2], x3 = x[a3];
             const double2 w = tw[j << sh0];
             double2 t = twiddled(w, x1);
             const double2 y0 = cadd(x0, t), y1 = csub(x0, t);
             t = twiddled(w, x3);
             const double2 y2 = cadd(x2, t), y3 = csub(x2, t);
             t = twiddled(tw[j << sh1], y2);
-            x[i0] = cadd(y0, t);
-            x[i0 + 2 * half] = csub(y0, t);
+            x[a0] = cadd(y0, t);
+            x[a2] = csub(y0, t);
             t = twiddled(tw[(j + half) << sh1], y3);
-            x[i0 + half] = cadd(y1, t);
-            x[i0 + 3 * half] = csub(y1, t);
+            x[a1] = cadd(y1, t);
+            x[a3] = csub(y1, t);
         }
         __syncthreads();
     }
@@ -67,11 +74,11 @@ __device__ void lds_fft(double2 *buf, int N, int logN, int lines, const double2 
         for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
             const int line = idx >> (logN - 1);
             const int j = idx & (halfN - 1);
-            double2 *x = buf + line * N;
-            const double2 t = twiddled(tw[j], x[j + half]);
-            const double2 a = x[j];
-            x[j] = cadd(a, t);
-            x[j + half] = csub(a, t);
+            double2 *x = buf + line * line_stride(N);
+            const double2 t = twiddled(tw[j], x[padded(j + half)]);
+            const double2 a = x[padded(j)];
+            x[padded(j)] = cadd(a, t);
+            x[padded(j + half)] = csub(a, t);
         }
         __syncthreads();
     }

@@ -9,8 +9,8 @@
 //   3-D: modes (n0 in [-K,K], n1 in [-K,K], m in [0,K])
 //        -> axis 0 (generated on the fly)  Y[x0][n1][m]
 //        -> axis 1, in chunks of x0 rows   Z[x0][x1][m]
-//        -> last axis, real part, weights 1 (m = 0) and 2 (m > 0), stored
-//           straight into the storage arrays;
+//        -> last axis, two rows to a transform, stored straight into the
+//           storage arrays;
 //   2-D: the same without the middle axis; 1-D: the last axis only.
 // Each line transform is an in-place radix-2 FFT in LDS (ce_fft.hpp) with a
 // table of N/2 FP64 twiddles.  Only the band (N/2 + 1 of N inputs per line)
@@ -131,13 +131,13 @@ __global__ __launch_bounds__(kGenThreads) void gen_axis0_kernel(GrfArgs g, const
             }
             v = hermitian_mode(g, n);
         }
-        lds[l * N + bitrev(p, g.logN)] = v;
+        lds[l * line_stride(N) + padded(bitrev(p, g.logN))] = v;
     }
     __syncthreads();
     lds_fft<false>(lds, N, g.logN, lpw, tw);
     for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
         const int l = idx % lpw, x0 = idx / lpw;
-        if (l < nl) Y[(long long)x0 * lines + first + l] = lds[l * N + x0];
+        if (l < nl) Y[(long long)x0 * lines + first + l] = lds[l * line_stride(N) + padded(x0)];
     }
 }
 
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kGenThreads) void axis1_kernel(GrfArgs g, const dou
             const int r = line / M, m = line % M;
             v = Y[((long long)(r0 + r) * W + (n1 + K)) * M + m];
         }
-        lds[l * N + bitrev(p, g.logN)] = v;
+        lds[l * line_stride(N) + padded(bitrev(p, g.logN))] = v;
     }
     __syncthreads();
     lds_fft<false>(lds, N, g.logN, lpw, tw);
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kGenThreads) void axis1_kernel(GrfArgs g, const dou
         if (l < nl) {
             const int line = first + l;
             const int r = line / M, m = line % M;
-            Z[((long long)r * N + x1) * M + m] = lds[l * N + x1];
+            Z[((long long)r * N + x1) * M + m] = lds[l * line_stride(N) + padded(x1)];
         }
     }
 }
@@ -178,6 +178,11 @@ __global__ __launch_bounds__(kGenThreads) void axis1_kernel(GrfArgs g, const dou
 // Last axis: row r of Z (K+1 values, or the generated 1-D modes when Z is
 // NULL) -> out[(row0 + r) * N + x] = (T)(Re sum + store_shift); the largest
 // |Re sum + phys_shift| (NaN as +inf) goes to *maxabs_bits.
+//
+// The result of a row is real, so one complex transform does two rows a and b:
+// with the Hermitian modes H_a + i H_b its real part is row a and its
+// imaginary part row b (one row per transform took 120 us for 256^3, of which
+// the transforms were most).  `lpw` transforms per block, 2 lpw rows.
 template <typename T>
 __global__ __launch_bounds__(kGenThreads) void last_axis_kernel(GrfArgs g, const double2 *__restrict__ tw,
                                                                const double2 *__restrict__ Z, int rows,
@@ -188,29 +193,38 @@ __global__ __launch_bounds__(kGenThreads) void last_axis_kernel(GrfArgs g, const
     extern __shared__ double2 lds[];
     __shared__ float red[kGenThreads / 64];
     const int N = g.N, K = g.K, M = K + 1;
-    const int first = blockIdx.x * lpw;
-    const int nl = min(lpw, rows - first);
+    const int first = blockIdx.x * 2 * lpw;
+    const int nl = min(2 * lpw, rows - first);
+    auto mode = [&](int row, int p) {
+        if (row >= nl) return make_double2(0.0, 0.0);
+        if (Z) return Z[(long long)(first + row) * M + p];
+        int n[1] = {p};
+        return hermitian_mode(g, n);
+    };
+    // p = 0..K, and its mirror image N - p; the modes between are zero
     for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
         const int l = idx >> g.logN, p = idx & (N - 1);
-        double2 v = make_double2(0.0, 0.0);
-        if (l < nl && p <= K) {
-            if (Z) {
-                v = Z[(long long)(first + l) * M + p];
-            } else {
-                int n[1] = {p};
-                v = hermitian_mode(g, n);
-            }
-            if (p > 0) v = make_double2(2.0 * v.x, 2.0 * v.y);
+        if (p > K && p < N - K) lds[l * line_stride(N) + padded(bitrev(p, g.logN))] = make_double2(0.0, 0.0);
+    }
+    for (int idx = threadIdx.x; idx < lpw * M; idx += blockDim.x) {
+        const int l = idx / M, p = idx - l * M;
+        const double2 a = mode(2 * l, p), b = mode(2 * l + 1, p);
+        double2 *x = lds + l * line_stride(N);
+        if (p == 0) {
+            x[0] = make_double2(a.x, b.x);   // only the real parts enter a row
+        } else {
+            x[padded(bitrev(p, g.logN))] = make_double2(a.x - b.y, a.y + b.x);
+            x[padded(bitrev(N - p, g.logN))] = make_double2(a.x + b.y, b.x - a.y);
         }
-        lds[l * N + bitrev(p, g.logN)] = v;
     }
     __syncthreads();
     lds_fft<false>(lds, N, g.logN, lpw, tw);
     float mx = 0.0f;
-    for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
+    for (int idx = threadIdx.x; idx < 2 * lpw * N; idx += blockDim.x) {
         const int l = idx >> g.logN, x = idx & (N - 1);
         if (l < nl) {
-            const double v = lds[l * N + x].x;
+            const double2 w = lds[(l >> 1) * line_stride(N) + padded(x)];
+            const double v = (l & 1) ? w.y : w.x;
             out[(row0 + first + l) * N + x] = (T)(v + store_shift);
             const double ph = v + phys_shift;
             mx = fmaxf(mx, isnan(ph) ? INFINITY : (float)fabs(ph));
@@ -229,7 +243,7 @@ __global__ __launch_bounds__(kGenThreads) void last_axis_kernel(GrfArgs g, const
 
 int lines_per_group(int N) { return std::max(1, kLdsLines / N); }
 
-size_t lds_bytes(int N) { return (size_t)lines_per_group(N) * N * sizeof(double2); }
+size_t lds_bytes(int N) { return (size_t)lines_per_group(N) * line_stride(N) * sizeof(double2); }
 
 struct Region {
     char *p;
@@ -247,7 +261,7 @@ ce_status generate_array(ce_sim *s, const GrfArgs &g, const double2 *tw, Region 
     hipStream_t st = s->stream;
     const bool fp64 = s->p.precision == CE_FP64;
     auto last = [&](const double2 *Zp, int rows, long long row0) {
-        const dim3 grd((rows + lpw - 1) / lpw);
+        const dim3 grd((rows + 2 * lpw - 1) / (2 * lpw));
         if (fp64)
             hipLaunchKernelGGL(last_axis_kernel<double>, grd, blk, lds, st, g, tw, Zp, rows, row0,
                                static_cast<double *>(dst), store_shift, phys_shift, maxabs, lpw);

@@ -61,24 +61,31 @@ int nbins_of(int dims, int N)
     return (int)r + 1;
 }
 
-// The transform buffer: rows [0, rows_a) of kc values in one free block,
-// the rest in a second one.
+// The transform buffer: rows [0, rows_a) of kc values, `stride` apart, in one
+// free block, the rest in a second one.  Where they fit, rows start on whole
+// 128-byte lines: the strided axes read eight neighbouring lines' values of a
+// row together, which are one such line then and parts of two otherwise.
 struct ZBuf {
     double2 *a, *b;
     long long rows_a;
-    int kc;
-    __device__ double2 *row(long long r) const { return r < rows_a ? a + r * kc : b + (r - rows_a) * kc; }
+    int kc, stride;
+    __device__ double2 *row(long long r) const { return r < rows_a ? a + r * stride : b + (r - rows_a) * stride; }
 };
 
-__device__ inline int isqrt_ll(long long v)
+// floor(sqrt(v)), v < 2^24 (at most 3 (N/2)^2 here): a float holds v exactly.
+static_assert(3LL * (kMaxSpecN / 2) * (kMaxSpecN / 2) < 1 << 24, "squared wave numbers fit a float");
+__device__ inline int isqrt(int v)
 {
-    long long r = (long long)sqrt((double)v);
+    int r = (int)sqrtf((float)v);
     while (r * r > v) r--;
     while ((r + 1) * (r + 1) <= v) r++;
-    return (int)r;
+    return r;
 }
 
 // Last axis.  Row r of the field (N consecutive sites) -> Z[r * kc + k - k0].
+// The rows are real, so one complex transform does two of them, a + i b, and
+// the conjugate-symmetric and antisymmetric parts of the result are theirs.
+// `lpw` transforms per block, 2 lpw rows.
 template <typename T>
 __global__ __launch_bounds__(kSpecThreads) void spec_rows_kernel(const T *__restrict__ d, const T *__restrict__ p,
                                                                 const Scalars *sc, int field, int which, int started,
@@ -87,8 +94,8 @@ __global__ __launch_bounds__(kSpecThreads) void spec_rows_kernel(const T *__rest
 {
     extern __shared__ double2 lds[];
     const int kc = Z.kc;
-    const long long first = (long long)blockIdx.x * lpw;
-    const int nl = (int)min((long long)lpw, rows - first);
+    const long long first = (long long)blockIdx.x * 2 * lpw;
+    const int nl = (int)min((long long)2 * lpw, rows - first);
     const double m = sc->m[field];
     FieldCoef<T> c;
     const double beta = started ? sc->beta : 0.0;
@@ -96,24 +103,28 @@ __global__ __launch_bounds__(kSpecThreads) void spec_rows_kernel(const T *__rest
     c.bm = (T)(beta * m);
     c.r = (T)0;
     c.m1 = (T)0;
+    auto site = [&](int row, int x) {
+        if (row >= nl) return 0.0;
+        const long long s = (first + row) * N + x;
+        const T dv = d[s];
+        if (which == 0) return m + (double)dv;
+        return started ? (double)fdot_of(dv, p[s], c) : (double)p[s];
+    };
     for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
         const int l = idx >> logN, x = idx & (N - 1);
-        double v = 0.0;
-        if (l < nl) {
-            const long long s = (first + l) * N + x;
-            const T dv = d[s];
-            if (which == 0)
-                v = m + (double)dv;
-            else
-                v = started ? (double)fdot_of(dv, p[s], c) : (double)p[s];
-        }
-        lds[l * N + bitrev(x, logN)] = make_double2(v, 0.0);
+        lds[l * line_stride(N) + padded(bitrev(x, logN))] = make_double2(site(2 * l, x), site(2 * l + 1, x));
     }
     __syncthreads();
     lds_fft<true>(lds, N, logN, lpw, tw);
-    for (int idx = threadIdx.x; idx < lpw * kc; idx += blockDim.x) {
+    for (int idx = threadIdx.x; idx < 2 * lpw * kc; idx += blockDim.x) {
         const int l = idx / kc, kk = idx - l * kc;
-        if (l < nl) Z.row(first + l)[kk] = lds[l * N + k0 + kk];
+        if (l < nl) {
+            const int k = k0 + kk;
+            const double2 *x = lds + (l >> 1) * line_stride(N);
+            const double2 u = x[padded(k)], v = x[padded((N - k) & (N - 1))];
+            Z.row(first + l)[kk] = (l & 1) ? make_double2(0.5 * (u.y + v.y), 0.5 * (v.x - u.x))
+                                           : make_double2(0.5 * (u.x + v.x), 0.5 * (u.y - v.y));
+        }
     }
 }
 
@@ -134,7 +145,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_mid_kernel(int N, int logN,
             const long long x0 = line / kc, kk = line % kc;
             v = Z.row(x0 * N + x1)[kk];
         }
-        lds[l * N + bitrev(x1, logN)] = v;
+        lds[l * line_stride(N) + padded(bitrev(x1, logN))] = v;
     }
     __syncthreads();
     lds_fft<true>(lds, N, logN, lpw, tw);
@@ -143,7 +154,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_mid_kernel(int N, int logN,
         if (l < nl) {
             const long long line = first + l;
             const long long x0 = line / kc, kk = line % kc;
-            Z.row(x0 * N + n1)[kk] = lds[l * N + n1];
+            Z.row(x0 * N + n1)[kk] = lds[l * line_stride(N) + padded(n1)];
         }
     }
 }
@@ -171,43 +182,53 @@ __device__ inline void bin_add(int key, double v, unsigned w, double *hp, unsign
     }
 }
 
-// Adds one transformed line (first-axis values x[0..N), natural order) to the
-// histograms: the wavefront wv < nwb bins its contiguous part of the line's
-// walk, whose elements come in order of |n0| (0, 1, -1, 2, -2, ..., -N/2) so
-// that the bins are non-decreasing along it.  dims 3: line = n1 kc + kk;
-// dims 2: line = kk.
+// Adds one transformed line (first-axis values x[0..N), natural order, padded)
+// to the histograms.  n0 and -n0 share their bin, so an element of the walk is
+// such a pair, in order of |n0|: the bins are non-decreasing along it.  The
+// wavefront wv < nwb bins its contiguous part of |n0| < N/2, the last one also
+// -N/2.  dims 3: line = n1 kc + kk; dims 2: line = kk.
 __device__ inline void bin_line(const double2 *x, long long line, int dims, int N, int k0, int kc, int nwb, int wv,
                                 double inv_norm, double *hp, unsigned *hc)
 {
     const int halfN = N / 2;
-    long long base2;
-    int klast;
+    int base2, klast;
     if (dims == 3) {
         const int n1i = (int)(line / kc);
         const int n1 = n1i < halfN ? n1i : n1i - N;
         klast = k0 + (int)(line % kc);
-        base2 = (long long)n1 * n1 + (long long)klast * klast;
+        base2 = n1 * n1 + klast * klast;
     } else {
         klast = k0 + (int)line;
-        base2 = (long long)klast * klast;
+        base2 = klast * klast;
     }
     const unsigned wt = (klast == 0 || klast == halfN) ? 1u : 2u;
-    const int seg = N / nwb;   // this wavefront's part of the walk
+    const int lane = threadIdx.x & 63;
+    const int seg = halfN / nwb;   // this wavefront's part of the walk
     const int e_end = (wv + 1) * seg;
     for (int e0 = wv * seg; e0 < e_end; e0 += 64) {
-        const int e = e0 + (int)(threadIdx.x & 63);
+        const int e = e0 + lane;
         int key = -1;   // lanes past the part's end add nothing
         double v = 0.0;
         unsigned w = 0u;
         if (e < e_end) {
-            const int pidx = e == 0 ? 0 : ((e & 1) ? (e + 1) >> 1 : N - (e >> 1));
-            const int n0 = pidx < halfN ? pidx : pidx - N;
-            const double2 X = x[pidx];
-            key = isqrt_ll((long long)n0 * n0 + base2);
-            v = (double)wt * (X.x * X.x + X.y * X.y) * inv_norm;
+            const double2 X = x[padded(e)];
+            double s = X.x * X.x + X.y * X.y;
             w = wt;
+            if (e > 0) {
+                const double2 Y = x[padded(N - e)];
+                s += Y.x * Y.x + Y.y * Y.y;
+                w = 2 * wt;
+            }
+            key = isqrt(e * e + base2);
+            v = (double)wt * s * inv_norm;
         }
         bin_add(key, v, w, hp, hc);
+    }
+    if (wv == nwb - 1 && lane == 0) {
+        const double2 X = x[padded(halfN)];
+        const int key = isqrt(halfN * halfN + base2);
+        hp[key] += (double)wt * (X.x * X.x + X.y * X.y) * inv_norm;
+        hc[key] += wt;
     }
 }
 
@@ -230,7 +251,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_final_kernel(int dims, int 
 {
     const int kc = Z.kc;
     extern __shared__ double2 lds[];
-    double *hp_all = reinterpret_cast<double *>(lds + lpw * N);   // [nwb][nb]
+    double *hp_all = reinterpret_cast<double *>(lds + lpw * line_stride(N));   // [nwb][nb]
     unsigned *hc_all = reinterpret_cast<unsigned *>(hp_all + nwb * nb);  // [nwb][nb]
     for (int j = threadIdx.x; j < nwb * nb; j += blockDim.x) {
         hp_all[j] = 0.0;
@@ -285,13 +306,13 @@ __global__ __launch_bounds__(kSpecThreads) void spec_final_kernel(int dims, int 
                     const long long line = first + l;
                     val = dims == 3 ? Z.row((long long)x0 * N + line / kc)[line % kc] : Z.row(x0)[line];
                 }
-                lds[l * N + bitrev(x0, logN)] = val;
+                lds[l * line_stride(N) + padded(bitrev(x0, logN))] = val;
             }
             __syncthreads();
             lds_fft<true>(lds, N, logN, lpw, tw);
             if (wv < nwb)
                 for (int l = 0; l < nl; l++)
-                    bin_line(lds + l * N, first + l, dims, N, k0, kc, nwb, wv, inv_norm, hp, hc);
+                    bin_line(lds + l * line_stride(N), first + l, dims, N, k0, kc, nwb, wv, inv_norm, hp, hc);
             __syncthreads();
         }
     }
@@ -323,7 +344,18 @@ __global__ __launch_bounds__(kReduceThreads) void spec_reduce_kernel(const doubl
     const int g0 = min(groups, wv * per), g1 = min(groups, g0 + per);
     double acc = 0.0;
     if (j < 2 * nb)
-        for (int g = g0; g < g1; g++) acc += partial[(size_t)g * 2 * nb + j];
+        for (int g = g0; g < g1;) {
+            // sixteen loads in flight (one after the other they were most of
+            // the 39 us this took for 2048 blocks), added in order
+            double v[16];
+            const int c = min(16, g1 - g);
+#pragma unroll
+            for (int k = 0; k < 16; k++) v[k] = k < c ? partial[(size_t)(g + k) * 2 * nb + j] : 0.0;
+#pragma unroll
+            for (int k = 0; k < 16; k++)
+                if (k < c) acc += v[k];
+            g += c;
+        }
     red[wv][lane] = acc;
     __syncthreads();
     if (wv == 0 && j < 2 * nb) {
@@ -380,17 +412,24 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
     const long long rows_a_m = (long long)(block / row_bytes_m);
     const bool split = rows_a_m + (long long)(block / row_bytes_m) >= rows &&
                        staging_bytes >= (size_t)2 * nb * sizeof(double);
-    int kc;
+    int kc, stride;
     long long rows_a;
     double *partial;
     size_t stage_bytes;
     if (split) {
-        kc = M;
+        kc = stride = M;
         rows_a = std::min(rows_a_m, rows);
+        const int whole = (M + 7) / 8 * 8;
+        const long long fit = (long long)(block / ((size_t)whole * sizeof(double2)));
+        if (2 * fit >= rows) {
+            stride = whole;
+            rows_a = std::min(fit, rows);
+        }
         partial = s->staging;
         stage_bytes = staging_bytes;
     } else {
         kc = (int)std::min<long long>(M, (long long)(block / ((size_t)rows * sizeof(double2))));
+        stride = kc;
         rows_a = rows;
         const bool partial_in_block = block > staging_bytes;
         partial = partial_in_block ? reinterpret_cast<double *>(zb) : s->staging;
@@ -403,27 +442,27 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
     if (G < 1) return fail(CE_EINVAL, "lattice too small for the spectrum scratch");
     if (dims == 1) G = 1;
     static_assert(kOutOffset >= (size_t)kMaxSpecN / 2 * sizeof(double2), "twiddles fit below the result");
-    if (kOutOffset + (size_t)2 * nbins_of(3, kMaxSpecN) * sizeof(double) >
+    if (kOutOffset + (size_t)4 * nbins_of(3, kMaxSpecN) * sizeof(double) >
         (size_t)kMaxBlocks * kMaxSums * sizeof(double))
         return fail(CE_EDEVICE, "spectrum result does not fit the partial-sum buffer");
     char *pbase = reinterpret_cast<char *>(s->lat.partials);
     double2 *tw = reinterpret_cast<double2 *>(pbase + kTwOffset);
     double *out = reinterpret_cast<double *>(pbase + kOutOffset);
     hipStream_t st = s->stream;
-    const size_t lds_line = (size_t)lpw * N * sizeof(double2);
-    const size_t lds_mid = (size_t)lpw_mid * N * sizeof(double2);
+    const size_t lds_line = (size_t)lpw * line_stride(N) * sizeof(double2);
+    const size_t lds_mid = (size_t)lpw_mid * line_stride(N) * sizeof(double2);
     // as many binning wavefronts (2 or 1) as leave the block within 40 KiB of
     // LDS, so that four blocks fit a compute unit (1024^3: 8.4 ms per
     // first-axis pass, against 10.9 ms with four wavefronts at two blocks per
     // unit and 10.3 ms with one at six)
     int nwb = 1;
     for (int w = 2; w >= 1; w /= 2)
-        if ((size_t)lpw_final * N * sizeof(double2) + (size_t)w * nb * (sizeof(double) + sizeof(unsigned)) <= 40960) {
+        if ((size_t)lpw_final * line_stride(N) * sizeof(double2) + (size_t)w * nb * (sizeof(double) + sizeof(unsigned)) <= 40960) {
             nwb = w;
             break;
         }
     const size_t lds_final =
-        (size_t)lpw_final * N * sizeof(double2) + (size_t)nwb * nb * (sizeof(double) + sizeof(unsigned));
+        (size_t)lpw_final * line_stride(N) * sizeof(double2) + (size_t)nwb * nb * (sizeof(double) + sizeof(unsigned));
     const double inv_norm = 1.0 / pow((double)N, 2.0 * dims);
     const bool fp64 = s->p.precision == CE_FP64;
 
@@ -439,8 +478,9 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
             Z.b = zb;
             Z.rows_a = rows_a;
             Z.kc = kcc;
+            Z.stride = split ? stride : kcc;
             const dim3 blk(kSpecThreads);
-            const dim3 grows((unsigned)((rows + lpw - 1) / lpw));
+            const dim3 grows((unsigned)((rows + 2 * lpw - 1) / (2 * lpw)));
             if (fp64)
                 hipLaunchKernelGGL(spec_rows_kernel<double>, grows, blk, lds_line, st,
                                    static_cast<const double *>(s->lat.d[s->cur][field]),
@@ -463,12 +503,20 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
             CE_HIP(hipGetLastError());
         }
         hipLaunchKernelGGL(spec_reduce_kernel, dim3((2 * nb + 63) / 64), dim3(kReduceThreads), 0, st, partial, G, nb,
-                           out);
+                           out + which * 2 * nb);
         CE_HIP(hipGetLastError());
-        if (dst) CE_HIP(hipMemcpyAsync(dst, out, (size_t)nb * sizeof(double), hipMemcpyDeviceToHost, st));
-        if (which == 0 && count)
-            CE_HIP(hipMemcpyAsync(count, out + nb, (size_t)nb * sizeof(double), hipMemcpyDeviceToHost, st));
+    }
+    // power_f, count, power_fdot: one copy and one wait for both spectra
+    constexpr int kMost = 2048;
+    static_assert(3 * (kMaxSpecN / 2) * (kMaxSpecN / 2) < (long long)kMost * kMost, "every bin has its place");
+    double host[3 * kMost];
+    const int from = power_f || count ? 0 : 2 * nb, to = power_fdot ? 3 * nb : 2 * nb;
+    if (to > from) {
+        CE_HIP(hipMemcpyAsync(host + from, out + from, (size_t)(to - from) * sizeof(double), hipMemcpyDeviceToHost, st));
         CE_HIP(hipStreamSynchronize(st));
+        if (power_f) memcpy(power_f, host, (size_t)nb * sizeof(double));
+        if (count) memcpy(count, host + nb, (size_t)nb * sizeof(double));
+        if (power_fdot) memcpy(power_fdot, host + 2 * nb, (size_t)nb * sizeof(double));
     }
     return CE_OK;
 }
