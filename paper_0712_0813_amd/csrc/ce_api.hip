@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <new>
 
 #include "ce_sim.hpp"
@@ -17,6 +18,26 @@ using namespace ce::host;
 
 namespace {
 thread_local char g_err[512] = "";
+
+// Memory kept from destroyed simulations, oldest first (see device_memory).
+struct Kept {
+    void *mem;
+    size_t bytes;
+    int device;
+};
+std::mutex g_kept_mu;
+Kept g_kept[kKeptBlocks];
+int g_kept_n = 0;
+size_t g_kept_bytes = 0;
+
+Kept take_kept(int at)   // g_kept_mu held
+{
+    const Kept k = g_kept[at];
+    for (int i = at + 1; i < g_kept_n; i++) g_kept[i - 1] = g_kept[i];
+    g_kept_n--;
+    g_kept_bytes -= k.bytes;
+    return k;
+}
 }  // namespace
 
 namespace ce {
@@ -31,6 +52,46 @@ ce_status fail(ce_status st, const char *fmt, ...)
     return st;
 }
 
+
+void give_back_kept_memory()
+{
+    std::lock_guard<std::mutex> g(g_kept_mu);
+    while (g_kept_n > 0) (void)hipFree(take_kept(0).mem);
+}
+
+hipError_t device_memory(size_t bytes, void **out)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> g(g_kept_mu);
+        for (int i = g_kept_n - 1; i >= 0; i--)
+            if (g_kept[i].bytes == bytes && g_kept[i].device == dev) {
+                *out = take_kept(i).mem;
+                return hipSuccess;
+            }
+    }
+    e = hipMalloc(out, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        give_back_kept_memory();
+        e = hipMalloc(out, bytes);
+    }
+    return e;
+}
+
+void release_device_memory(void *mem, size_t bytes, int device)
+{
+    if (bytes > kKeptBytes) {
+        (void)hipFree(mem);
+        return;
+    }
+    std::lock_guard<std::mutex> g(g_kept_mu);
+    while (g_kept_n == kKeptBlocks || g_kept_bytes + bytes > kKeptBytes) (void)hipFree(take_kept(0).mem);
+    g_kept[g_kept_n++] = Kept{mem, bytes, device};
+    g_kept_bytes += bytes;
+}
 
 long long sites_of(const ce_params *p)
 {
@@ -530,7 +591,10 @@ ce_status ce_create(const ce_params *p, ce_sim **out)
         }
         s->base = static_cast<char *>(p->arena);
     } else {
-        hipError_t e = hipMalloc(&s->base, L.total);
+        void *mem = nullptr;
+        hipError_t e = device_memory(L.total, &mem);
+        if (e == hipSuccess) e = hipGetDevice(&s->device);
+        s->base = static_cast<char *>(mem);
         if (e != hipSuccess) {
             delete s;
             (void)hipGetLastError();
@@ -955,11 +1019,17 @@ ce_status ce_read_sites(ce_sim *s, int32_t field, int64_t count, const int64_t *
 void ce_destroy(ce_sim *s)
 {
     if (!s) return;
-    if (s->stream) (void)hipStreamSynchronize(s->stream);
+    // memory is kept only if everything that used it is known to have ended
+    const bool idle = s->stream && hipStreamSynchronize(s->stream) == hipSuccess;
     drop_graphs(s);
     if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
-    if (s->own_mem && s->base) (void)hipFree(s->base);
+    if (s->own_mem && s->base) {
+        if (idle)
+            release_device_memory(s->base, s->lay.total, s->device);
+        else
+            (void)hipFree(s->base);
+    }
     delete s;
 }
 

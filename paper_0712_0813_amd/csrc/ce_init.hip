@@ -423,7 +423,11 @@ ce_status generate(ce_sim *s, const ce_init_spec *spec, bool noalloc)
         if (dims >= 2 && !yreg.p) {
             // lattices too small to hold the scratch in their own buffers
             const size_t zb = dims == 3 ? rowbytes * N : 0;
-            CE_HIP(hipMalloc(&temp, ybytes + zb));
+            if (hipMalloc(&temp, ybytes + zb) != hipSuccess) {
+                (void)hipGetLastError();
+                give_back_kept_memory();
+                CE_HIP(hipMalloc(&temp, ybytes + zb));
+            }
             yreg = Region{temp, ybytes};
             zreg = Region{temp + ybytes, zb};
             zrows = N;

@@ -330,7 +330,11 @@ ce_status rebuild(ce_pool *pl)
         T.d = nullptr;
         T.bytes = 0;
         const size_t want = std::max<size_t>(need * 2, 1 << 20);
-        CE_HIP(hipMalloc(&T.d, want));
+        if (hipMalloc(&T.d, want) != hipSuccess) {
+            (void)hipGetLastError();
+            give_back_kept_memory();
+            CE_HIP(hipMalloc(&T.d, want));
+        }
         T.bytes = want;
     }
     size_t off = 0;
@@ -546,6 +550,8 @@ static ce_status admit(ce_pool *pl, const ce_params *p, const ce_launch *cfg, co
             std::lock_guard<std::mutex> g(pl->mu);
             st = trim_cache(pl, pl->budget);  // drop the whole cache, then try once more
         }
+        (void)hipGetLastError();
+        give_back_kept_memory();
         if (st != CE_OK || hipMalloc(&mem, bytes) != hipSuccess) {
             give_back(nullptr);
             return st != CE_OK ? st : fail(CE_ENOMEM, "member allocation of %zu bytes failed", bytes);
