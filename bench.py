@@ -52,7 +52,7 @@ def measured_traffic(launch):
     return prof.get("hbm_bytes_per_launch")
 
 
-STEP_KERNEL = "tiled3d_kernel<float, 2, 0, 0, 4, 64, 256>"
+STEP_KERNEL = "tiled3d_kernel<float, 2, 0, 0, 4, 64, 256, false>"
 
 
 def _counter_rows(path):

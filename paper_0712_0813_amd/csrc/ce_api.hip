@@ -254,19 +254,20 @@ ce_status device_cus(int *cus)
     return CE_OK;
 }
 
-const void *resident_kernel(const ce_params *p, const ce_launch &c, bool batched)
+const void *resident_kernel(const ce_params *p, const ce_launch &c, bool ragged, bool batched)
 {
     if (c.kernel == CE_KERNEL_STREAM2D)
         return stream2d_groups(p->N, c.planes) > kSyncRows ? nullptr
                : p->model == kPoly ? resident_stream2d_model<kPoly>(p->precision, p->nfields, c.planes, batched)
                                    : resident_stream2d_model<kQuartic>(p->precision, p->nfields, c.planes, batched);
-    if (p->N % c.planes != 0 ||
+    if ((!ragged && p->N % c.planes != 0) ||
         tiled_tiles(p->N, c.sites_per_thread, c.lanes_per_row, c.block, c.planes) > kSyncRows)
         return nullptr;
     return p->model == kPoly ? resident_tiled_model<kPoly>(p->precision, p->nfields, c.sites_per_thread,
-                                                           c.lanes_per_row, c.block, c.planes, batched)
+                                                           c.lanes_per_row, c.block, c.planes, ragged, batched)
                              : resident_tiled_model<kQuartic>(p->precision, p->nfields, c.sites_per_thread,
-                                                              c.lanes_per_row, c.block, c.planes, batched);
+                                                              c.lanes_per_row, c.block, c.planes, ragged,
+                                                              batched);
 }
 
 // The resident pass that takes the same steps as s's launch, if there is one:
@@ -287,13 +288,13 @@ void plan_resident(ce_sim *s)
         r.threads = kBlock * vb + 64;
     } else if (lat.kind == kTiled3d) {
         const ce_launch c{CE_KERNEL_TILED3D, lat.vec, lat.lpr, lat.bs, lat.zc, 0};
-        r.kernel = resident_kernel(&s->p, c, false);
+        r.kernel = resident_kernel(&s->p, c, lat.ragged != 0, false);
         r.blocks = (int)tiled_tiles(lat.N, lat.vec, lat.lpr, lat.bs, lat.zc);
         r.threads = lat.bs + 64;
     } else if (lat.kind == kStream2d) {
         // the streaming pass sums per block: one group of units each
         if (stream2d_groups(lat.N, lat.zc) != lat.nblocks) return;
-        r.kernel = resident_kernel(&s->p, ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, lat.zc, lat.nblocks}, false);
+        r.kernel = resident_kernel(&s->p, ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, lat.zc, lat.nblocks}, false, false);
         r.blocks = lat.nblocks;
         r.threads = kBlock + 64;
     }
@@ -322,9 +323,23 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
     if (cfg.grid < 0 || cfg.grid > kMaxBlocks) return fail(CE_EINVAL, "grid must be 0..%d", kMaxBlocks);
     if (cfg.kernel == CE_KERNEL_DIRECT) {
         int g = cfg.grid ? cfg.grid : pass_blocks(s->p.dims, s->p.N);
-        lat.kind = kDirect;
-        lat.vec = lat.lpr = lat.bs = lat.zc = 0;
-        lat.nblocks = g;
+        s->grid = g;
+        RaggedTiling r;
+        if (ragged_tiling(s->p.precision, s->p.dims, s->p.N, &r)) {
+            // summed per tile, so the result does not depend on the blocks
+            lat.kind = kTiled3d;
+            lat.ragged = 1;
+            lat.vec = 4;
+            lat.lpr = r.lpr;
+            lat.bs = kBlock;
+            lat.zc = r.planes;
+            lat.nblocks = std::min(g, r.tiles);
+        } else {
+            lat.kind = kDirect;
+            lat.ragged = 0;
+            lat.vec = lat.lpr = lat.bs = lat.zc = 0;
+            lat.nblocks = g;
+        }
     } else if (cfg.kernel == CE_KERNEL_TILED3D) {
         if (!tiled_shape_built(cfg.sites_per_thread, cfg.lanes_per_row, cfg.block))
             return fail(CE_EINVAL, "tiled shape (sites_per_thread=%d, lanes_per_row=%d, block=%d) is not built",
@@ -355,11 +370,12 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
             g = (int)want;
         }
         lat.kind = kTiled3d;
+        lat.ragged = 0;
         lat.vec = cfg.sites_per_thread;
         lat.lpr = cfg.lanes_per_row;
         lat.bs = cfg.block;
         lat.zc = cfg.planes;
-        lat.nblocks = g;
+        lat.nblocks = s->grid = g;
     } else if (cfg.kernel == CE_KERNEL_STREAM2D) {
         if (!stream2d_fits(s->p.dims, s->p.N, cfg.planes))
             return fail(CE_EINVAL, "2-D streaming launch (rows=%d) does not fit dims=%d N=%d", cfg.planes,
@@ -384,7 +400,8 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
         lat.lpr = 64;
         lat.bs = kBlock;
         lat.zc = cfg.planes;
-        lat.nblocks = g;
+        lat.ragged = 0;
+        lat.nblocks = s->grid = g;
         // the shape is fixed: report it whatever the caller passed
         s->launch = ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, cfg.planes, cfg.grid};
         drop_graphs(s);
@@ -417,7 +434,7 @@ ce_launch default_launch(const ce_params *p, int cus)
         // leave no more groups of four than it has blocks
         for (int rows = 1; rows <= 16; rows *= 2) {
             const ce_launch r{CE_KERNEL_STREAM2D, 4, 64, kBlock, rows, 0};
-            if (stream2d_fits(2, p->N, rows) && resident_kernel(p, r, false)) return r;
+            if (stream2d_fits(2, p->N, rows) && resident_kernel(p, r, false, false)) return r;
         }
         // rows per unit: the tallest (up to 64) that still gives every
         // compute unit a group of four units
@@ -482,7 +499,7 @@ ce_launch default_launch(const ce_params *p, int cus)
         for (int z = 1; z <= 8 && p->N >= 64; z *= 2) {
             if (p->N % z || !tiled_fits(3, p->N, v, l, bs, z) || tiled_tiles(p->N, v, l, bs, z) > kSyncRows) continue;
             const ce_launch r{CE_KERNEL_TILED3D, v, l, bs, z, 0};
-            if (resident_kernel(p, r, false)) return r;
+            if (resident_kernel(p, r, false, false)) return r;
         }
     }
     if (p->N >= 64) {
@@ -541,7 +558,7 @@ ce_status ce_get_launch(const ce_sim *s, ce_launch *out)
 {
     if (!s || !out) return fail(CE_EINVAL, "NULL argument");
     *out = s->launch;
-    out->grid = s->lat.nblocks;
+    out->grid = s->grid;
     return CE_OK;
 }
 
@@ -551,8 +568,10 @@ ce_status ce_set_launch(ce_sim *s, const ce_launch *cfg)
     const ce_launch old = s->launch;
     const Lattice saved = s->lat;
     const ce_sim::Resident resident = s->resident;
+    const int grid = s->grid;
     ce_status st = apply_launch(s, *cfg);
     if (st != CE_OK) {
+        s->grid = grid;
         s->launch = old;
         s->lat = saved;
         s->resident = resident;

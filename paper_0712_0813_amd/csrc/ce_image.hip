@@ -136,7 +136,7 @@ ce_status ce_save_image(ce_sim *s, void *buf, size_t bytes)
     for (int t = 0; t < p.nterms; t++) h.terms[t] = p.terms[t];
     h.step = s->step;
     h.launch = s->launch;
-    h.launch.grid = s->lat.nblocks;
+    h.launch.grid = s->grid;
     h.state_bytes = sizeof(Scalars);
     h.ring_bytes = (uint64_t)kLogCap * sizeof(ce_energy);
     h.field_bytes = array_bytes(p);
@@ -192,8 +192,10 @@ ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes)
     const ce_launch old = s->launch;
     const Lattice saved = s->lat;
     const ce_sim::Resident resident = s->resident;
+    const int grid = s->grid;
     st = apply_launch(s, h.launch);
     if (st != CE_OK) {
+        s->grid = grid;
         s->launch = old;
         s->lat = saved;
         s->resident = resident;

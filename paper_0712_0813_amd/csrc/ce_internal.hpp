@@ -87,6 +87,7 @@ struct Lattice {
     int vec;               // tiled: consecutive x sites per thread (2 or 4)
     int lpr;               // tiled: threads per tile row (tile is vec*lpr x bs/lpr sites)
     int bs;                // tiled: threads per block
+    int ragged;            // tiled: tiles at the ends of rows and columns are cut short
     int zc;                // tiled: planes streamed per tile; 2-D streaming: rows per unit
     int first_block;       // batched launches: this lattice's first block
 };
@@ -139,7 +140,8 @@ const void *resident_direct_model(int precision, int dims, int nf, int vb);
 // block; bs + 64 threads), and of its batched form: arguments const Lattice
 // *lats, int lattices, int tiles of each, int steps.
 template <int MODEL>
-const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs, int planes, bool batched);
+const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs, int planes, bool ragged,
+                                 bool batched);
 // The same of the 2-D streaming pass (units of `rows` rows, a group of four per
 // block; 320 threads) and its batched form.
 template <int MODEL>
@@ -150,7 +152,7 @@ const void *resident_stream2d_model(int precision, int nf, int rows, bool batche
                                                           int, hipStream_t);                                     \
     template <> int direct_batched_resident_model<M>(const Lattice &, int);                                     \
     template <> const void *resident_direct_model<M>(int, int, int, int);                                       \
-    template <> const void *resident_tiled_model<M>(int, int, int, int, int, int, bool);                        \
+    template <> const void *resident_tiled_model<M>(int, int, int, int, int, int, bool, bool);                  \
     template <> const void *resident_stream2d_model<M>(int, int, int, bool);                                    \
     template <> hipError_t launch_tiled_model<M>(const Lattice &, int, int, Mode, hipStream_t);                 \
     template <> hipError_t launch_batched_tiled_model<M>(const Lattice *, const int *, int, int, const Lattice &, \
@@ -172,6 +174,13 @@ int pass_blocks(int dims, int N);
 bool tiled_shape_built(int vec, int lpr, int bs);
 bool tiled_fits(int dims, int N, int vec, int lpr, int bs, int zc);
 long long tiled_tiles(int N, int vec, int lpr, int bs, int zc);
+// The tiling a direct launch of a lattice that no tile divides runs on, if any
+// (4 sites per thread, 256 threads).
+struct RaggedTiling {
+    int lpr, planes;
+    int tiles;
+};
+bool ragged_tiling(int precision, int dims, int N, RaggedTiling *out);
 int tiled_resident_blocks(int model, int precision, int nf, int vec, int lpr, int bs);
 hipError_t launch_tiled(const Lattice &lat, int precision, int src, Mode mode, hipStream_t st);
 

@@ -35,12 +35,12 @@ struct Member {
 };
 
 // Members that can share one launch: same kernel instance.
-// model, precision, dims, nf, kind, vec, lpr, bs
-using ClassKey = std::tuple<int, int, int, int, int, int, int, int>;
+// model, precision, dims, nf, kind, ragged, vec, lpr, bs
+using ClassKey = std::tuple<int, int, int, int, int, int, int, int, int>;
 
 ClassKey class_of(const ce_sim *s)
 {
-    return ClassKey(s->p.model, s->p.precision, s->p.dims, s->p.nfields, s->lat.kind, s->lat.vec, s->lat.lpr,
+    return ClassKey(s->p.model, s->p.precision, s->p.dims, s->p.nfields, s->lat.kind, s->lat.ragged, s->lat.vec, s->lat.lpr,
                     s->lat.bs);
 }
 
@@ -142,7 +142,7 @@ ce_launch member_launch(const ce_params *p)
         const int rows = (p->N > 256) == (a == 0) ? 16 : 8;
         const ce_launch r{CE_KERNEL_STREAM2D, 4, 64, kBlock, rows, (int)std::min<long long>(
                               stream2d_fits(2, p->N, rows) ? stream2d_groups(p->N, rows) : 0, kMaxBlocks)};
-        if (r.grid > 0 && resident_kernel(p, r, true)) return r;
+        if (r.grid > 0 && resident_kernel(p, r, false, true)) return r;
     }
     if (p->dims == 2 && stream2d_fits(2, p->N, 8)) {
         // one group of four units per block; the tallest units (up to 64
@@ -170,7 +170,7 @@ ce_launch member_launch(const ce_params *p)
             if (p->N % z || !tiled_fits(3, p->N, 4, l, 256, z)) continue;
             const long long tiles = tiled_tiles(p->N, 4, l, 256, z);
             const ce_launch r{CE_KERNEL_TILED3D, 4, l, 256, z, (int)tiles};
-            if (tiles <= kSyncRows && resident_kernel(p, r, true)) return r;
+            if (tiles <= kSyncRows && resident_kernel(p, r, false, true)) return r;
         }
     const int shapes[3][3] = {{4, 64, 256}, {4, 16, 256}, {4, 8, 256}};
     for (int a = 0; a < 3; a++) {
@@ -238,14 +238,14 @@ ce_status trim_cache(ce_pool *pl, size_t want)
 void plan_resident_class(ClassTable &t, int cus, bool only)
 {
     const Lattice &p = t.proto;
-    if (p.kind == kDirect) return;
+    if (p.kind == kDirect || p.ragged) return;
     const long long tiles =
         p.kind == kTiled3d ? tiled_tiles(p.N, p.vec, p.lpr, p.bs, p.zc) : stream2d_groups(p.N, p.zc);
     for (const Lattice &L : t.lats)
         // (the streaming pass sums per block: one group of units each)
         if (L.N != p.N || L.zc != p.zc || (p.kind == kStream2d && L.nblocks != tiles)) return;
     const ce_launch c{p.kind == kTiled3d ? CE_KERNEL_TILED3D : CE_KERNEL_STREAM2D, p.vec, p.lpr, p.bs, p.zc, 0};
-    const void *kernel = resident_kernel(&t.mems[0]->sim->p, c, true);
+    const void *kernel = resident_kernel(&t.mems[0]->sim->p, c, false, true);
     if (!kernel) return;
     int per = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, p.bs + 64, 0) != hipSuccess) {

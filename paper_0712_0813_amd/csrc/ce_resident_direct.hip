@@ -215,22 +215,23 @@ __global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattic
     }
 }
 
-// Largest VB built for a state size: the quads of the four y and z
-// neighbours stay in registers beside the state.
-template <typename T, int NF>
+// Largest VB built: the quads of the four y and z neighbours stay in registers
+// beside the state, and a larger block has fewer (68^3 x 3 fields on two blocks
+// as one: 17.1 us a step spilled, 14.8 plain).
+template <typename T, int D, int NF>
 constexpr int max_vb()
 {
     constexpr int words = NF * (int)sizeof(T) / 4;
-    return words <= 2 ? 3 : words <= 4 ? 2 : 1;
+    return D == 3 ? (words == 1 ? 3 : words == 2 ? 2 : 1) : words <= 2 ? 3 : words <= 4 ? 2 : 1;
 }
 
 template <typename T, int D, int NF, int MODEL>
 const void *kernel_vb(int vb)
 {
     if (vb == 1) return (const void *)resident_direct_kernel<T, D, NF, MODEL, 1>;
-    if constexpr (max_vb<T, NF>() >= 2)
+    if constexpr (max_vb<T, D, NF>() >= 2)
         if (vb == 2) return (const void *)resident_direct_kernel<T, D, NF, MODEL, 2>;
-    if constexpr (max_vb<T, NF>() >= 3)
+    if constexpr (max_vb<T, D, NF>() >= 3)
         if (vb == 3) return (const void *)resident_direct_kernel<T, D, NF, MODEL, 3>;
     return nullptr;
 }

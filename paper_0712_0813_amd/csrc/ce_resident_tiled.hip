@@ -24,8 +24,10 @@ namespace {
 
 using namespace dev;
 
-// The block is the `rank`-th of the nblk that work the lattice.
-template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
+// The block is the `rank`-th of the nblk that work the lattice.  RAGGED: a tile
+// at the end of a row or column holds vx x vy sites, and every tile zlen <= ZP
+// planes (see the tiled pass).
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP, bool RAGGED>
 __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src, int steps, int rank, int nblk)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
@@ -41,7 +43,8 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
     __shared__ PassScalars<T> next;
 
     const int N = lat.N;
-    const int ntx = N / TX, nty = N / TY, nz = N / ZP;
+    const int ntx = RAGGED ? (N + TX - 1) / TX : N / TX, nty = RAGGED ? (N + TY - 1) / TY : N / TY;
+    const int nz = RAGGED ? (N + lat.zc - 1) / lat.zc : N / ZP;
     // neighbouring tiles on one XCD, as in the tiled pass
     const int tile = (int)xcd_item(rank, 0, nblk, nblk);
     const int t = threadIdx.x;
@@ -51,15 +54,18 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
     }
     const int wave = t >> 6;
     const int tx = tile % ntx, ty = tile / ntx % nty, tz = tile / (ntx * nty);
-    const int x0 = tx * TX, y0 = ty * TY, z0 = tz * ZP;
+    const int x0 = tx * TX, y0 = ty * TY, z0 = RAGGED ? tz * N / nz : tz * ZP;
+    const int vx = RAGGED ? min(TX, N - x0) : TX, vy = RAGGED ? min(TY, N - y0) : TY;
+    const int zlen = RAGGED ? (tz + 1) * N / nz - z0 : ZP;
     const int q = t % LPR, y = t / LPR;
     const unsigned NN = (unsigned)N * N;
     const bool wrap = ntx == 1;   // a tile row is a lattice row: its ends are neighbours
 
     // element offsets in an array, and in a plane of LDS
-    const unsigned own_xy = (unsigned)((y0 + y) * N + x0 + VEC * q);
+    const bool ok = !RAGGED || (VEC * q < vx && y < vy);   // the thread has sites
+    const unsigned own_xy = ok ? (unsigned)((y0 + y) * N + x0 + VEC * q) : (unsigned)(y0 * N + x0);
     const unsigned own = (unsigned)z0 * NN + own_xy;
-    const unsigned zoff[2] = {(unsigned)((z0 + N - 1) % N) * NN + own_xy, (unsigned)((z0 + ZP) % N) * NN + own_xy};
+    const unsigned zoff[2] = {(unsigned)((z0 + N - 1) % N) * NN + own_xy, (unsigned)((z0 + zlen) % N) * NN + own_xy};
     unsigned yoff[HY], xoff[HX], cread[HX];
     int yslot[HY], xslot[HX];
     bool ydo[HY], xdo[HX];
@@ -67,27 +73,29 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
     for (int m = 0; m < HY; m++) {
         const int h = t + m * BS;
         const int side = h / (ZP * LPR), k = h / LPR % ZP, g = h % LPR;
-        ydo[m] = h < NY;
-        yoff[m] = (unsigned)(z0 + k) * NN + (unsigned)(((side ? y0 + TY : y0 + N - 1) % N) * N + x0 + VEC * g);
-        yslot[m] = k * (NF * FSTRIDE) + (side ? (TY + 1) * TX : 0) + VEC * g;
+        ydo[m] = h < NY && (!RAGGED || (k < zlen && VEC * g < vx));
+        yoff[m] = (unsigned)(z0 + k) * NN + (unsigned)(((side ? y0 + vy : y0 + N - 1) % N) * N + x0 + VEC * g);
+        yslot[m] = k * (NF * FSTRIDE) + (side ? (vy + 1) * TX : 0) + VEC * g;
     }
 #pragma unroll
     for (int m = 0; m < HX; m++) {
         const int h = t + m * BS;
         const int side = h / (ZP * TY), k = h / TY % ZP, r = h % TY;
-        xdo[m] = h < NX && !wrap;
-        xoff[m] = (unsigned)(z0 + k) * NN + (unsigned)((y0 + r) * N + (side ? x0 + TX : x0 + N - 1) % N);
+        xdo[m] = h < NX && !wrap && (!RAGGED || (k < zlen && r < vy));
+        xoff[m] = (unsigned)(z0 + k) * NN + (unsigned)((y0 + r) * N + (side ? x0 + vx : x0 + N - 1) % N);
         xslot[m] = k * (NF * FSTRIDE) + PLANE + side * TY + r;
         // the left neighbour's right column is this tile's left one
         const int from = side ? tile + (tx == ntx - 1 ? 1 - ntx : 1) : tile + (tx == 0 ? ntx - 1 : -1);
         cread[m] = (unsigned)(from * 2 + 1 - side) * CSTRIDE + (unsigned)(k * TY + r);
     }
     T *const all = &lds[0][0][0];
-    const int left = wrap ? (y + 1) * TX + TX - 1 : PLANE + y;        // the site left of the row
+    const int left = wrap ? (y + 1) * TX + vx - 1 : PLANE + y;        // the site left of the row
     const int right = wrap ? (y + 1) * TX : PLANE + TY + y;           // and right of it
-    const bool edge = y == 0 || y == TY - 1;
-    const bool column = !wrap && (q == 0 || q == LPR - 1);
-    const unsigned cwrite = (unsigned)(tile * 2 + (q != 0)) * CSTRIDE + (unsigned)y;
+    const bool row_end = RAGGED ? VEC * (q + 1) == vx : q == LPR - 1;
+    const bool edge = y == 0 || y == vy - 1;
+    // (a ragged tile may be one thread wide: its sites are both columns)
+    const bool column[2] = {ok && !wrap && q == 0, ok && !wrap && row_end};
+    const unsigned cwrite = (unsigned)tile * 2 * CSTRIDE + (unsigned)y;
 
     PassCoef<T, NF> c = make_coef<T, NF, MODEL, kStep>(lat);
 
@@ -96,10 +104,10 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
     for (int k = 0; k < ZP; k++)
 #pragma unroll
         for (int i = 0; i < NF; i++) {
-            const unsigned o = (own + k * NN) * (unsigned)sizeof(T);
+            const unsigned o = (own + (RAGGED ? min(k, zlen - 1) : k) * NN) * (unsigned)sizeof(T);
             const Vec<T, VEC> dq = agent_load_vec<T, VEC>(agent_buffer(lat.d[src][i]), o);
             const Vec<T, VEC> pq = agent_load_vec<T, VEC>(agent_buffer(lat.p[src][i]), o);
-            store_lds(&lds[k][i][(y + 1) * TX + VEC * q], dq.v);
+            if (ok) store_lds(&lds[k][i][(y + 1) * TX + VEC * q], dq.v);
 #pragma unroll
             for (int e = 0; e < VEC; e++) p[k][i][e] = pq.v[e];
         }
@@ -159,7 +167,7 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
                     d[e] = d1;
                     p[k][i][e] = fdot;
                 }
-                store_lds(&lds[k][i][at], d);
+                if (ok) store_lds(&lds[k][i][at], d);
             }
 #pragma unroll
             for (int s = 0; s < 2; s++)
@@ -192,6 +200,8 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
 #pragma unroll
         for (int k = 0; k < ZP; k++) {
             __builtin_amdgcn_sched_barrier(0);
+            if (RAGGED && k >= zlen) break;
+            const bool top_plane = RAGGED ? k + 1 == zlen : k + 1 == ZP;
             T lap[VEC][NF];
 #pragma unroll
             for (int i = 0; i < NF; i++) {
@@ -199,11 +209,11 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
                 T xl = lane_from_left(cur[i][VEC - 1]);
                 T xr = lane_from_right(cur[i][0]);
                 if (q == 0) xl = P[left];
-                if (q == LPR - 1) xr = P[right];
+                if (row_end) xr = P[right];
                 T up[VEC], dn[VEC];
                 load_lds(&P[at - TX], up);
                 load_lds(&P[at + TX], dn);
-                if (k + 1 < ZP) {
+                if (!top_plane) {
                     load_lds(&lds[k + 1 < ZP ? k + 1 : k][i][at], above[i]);
                 } else {
 #pragma unroll
@@ -231,13 +241,13 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
 #pragma unroll
                 for (int i = 0; i < NF; i++) p[k][i][e] = pn[i];
             }
-            flush_sums(part, acc);
+            if (ok) flush_sums(part, acc);
             // add them now: left to itself the compiler sinks every plane's
             // additions to the last one and holds the parts until then (30
             // registers a plane with two FP32 fields)
 #pragma unroll
             for (int j = 0; j < NQ; j++) asm volatile("" : "+v"(acc[j]));
-            if (last || edge || k == 0 || k == ZP - 1) {
+            if (ok && (last || edge || k == 0 || top_plane)) {
                 const unsigned o = (own + k * NN) * (unsigned)sizeof(T);
 #pragma unroll
                 for (int i = 0; i < NF; i++) {
@@ -245,17 +255,16 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
                     agent_store(agent_buffer(lat.p[out][i]), o, p[k][i]);
                 }
             }
-            if (column) {
 #pragma unroll
-                for (int i = 0; i < NF; i++) {
-                    const unsigned o = out * csize + cwrite + (i * 2 * ZP + k) * TY;
-                    // values, not a choice between two array elements, which
-                    // would put the arrays in scratch memory
-                    const T dl = cur[i][0], dr = cur[i][VEC - 1], pl = p[k][i][0], pr = p[k][i][VEC - 1];
-                    agent_store(cols, o * (unsigned)sizeof(T), q == 0 ? dl : dr);
-                    agent_store(cols, (o + ZP * TY) * (unsigned)sizeof(T), q == 0 ? pl : pr);
+            for (int side = 0; side < 2; side++)
+                if (column[side]) {
+#pragma unroll
+                    for (int i = 0; i < NF; i++) {
+                        const unsigned o = out * csize + cwrite + side * CSTRIDE + (i * 2 * ZP + k) * TY;
+                        agent_store(cols, o * (unsigned)sizeof(T), cur[i][side ? VEC - 1 : 0]);
+                        agent_store(cols, (o + ZP * TY) * (unsigned)sizeof(T), p[k][i][side ? VEC - 1 : 0]);
+                    }
                 }
-            }
 #pragma unroll
             for (int i = 0; i < NF; i++)
 #pragma unroll
@@ -286,11 +295,11 @@ constexpr int waves_wanted()
     return BS == 256 && sizeof(T) == 4 && NF <= 2 && NF * ZP <= 8 ? 3 : 1;
 }
 
-template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP, bool RAGGED>
 __global__ __launch_bounds__(BS + 64, (waves_wanted<T, NF, BS, ZP>())) void resident_tiled_kernel(Lattice lat, int src,
                                                                                                 int steps)
 {
-    resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP>(lat, src, steps, blockIdx.x, gridDim.x);
+    resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP, RAGGED>(lat, src, steps, blockIdx.x, gridDim.x);
 }
 
 // Up to k steps of each of n lattices; see run_members.
@@ -299,7 +308,7 @@ __global__ __launch_bounds__(BS + 64, (waves_wanted<T, NF, BS, ZP>())) void
 resident_tiled_batched(const Lattice *lats, int n, int nblk, int k)
 {
     run_members(lats, n, nblk, k, [](const Lattice &lat, int src, int steps, int rank, int blocks) {
-        resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP>(lat, src, steps, rank, blocks);
+        resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP, false>(lat, src, steps, rank, blocks);
     });
 }
 
@@ -314,10 +323,17 @@ constexpr bool built()
 }
 
 template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
-const void *kernel_if_built(bool batched)
+const void *kernel_if_built(bool ragged, bool batched)
 {
     if constexpr (built<T, NF, VEC, LPR, BS, ZP>()) {
-        if (!batched) return (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, ZP>;
+        // ragged tiles: FP32, eight planes (see ragged_tiling)
+        if (ragged) {
+            if constexpr (sizeof(T) == 4 && ZP == 8)
+                return batched ? nullptr
+                               : (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, ZP, true>;
+            return nullptr;
+        }
+        if (!batched) return (const void *)resident_tiled_kernel<T, NF, MODEL, VEC, LPR, BS, ZP, false>;
         // pools: FP32 tiles of four or eight planes (see member_launch)
         if constexpr (sizeof(T) == 4 && ZP >= 4)
             return (const void *)resident_tiled_batched<T, NF, MODEL, VEC, LPR, BS, ZP>;
@@ -326,13 +342,14 @@ const void *kernel_if_built(bool batched)
 }
 
 template <typename T, int NF, int MODEL, int VEC, int LPR, int BS>
-const void *kernel_planes(int planes, bool batched)
+const void *kernel_planes(int planes, bool ragged, bool batched)
 {
+    if (ragged) planes = planes <= 8 ? 8 : 0;   // at most that many
     switch (planes) {
-    case 1: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 1>(batched);
-    case 2: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 2>(batched);
-    case 4: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 4>(batched);
-    case 8: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 8>(batched);
+    case 1: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 1>(ragged, batched);
+    case 2: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 2>(ragged, batched);
+    case 4: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 4>(ragged, batched);
+    case 8: return kernel_if_built<T, NF, MODEL, VEC, LPR, BS, 8>(ragged, batched);
     default: return nullptr;
     }
 }
@@ -340,25 +357,25 @@ const void *kernel_planes(int planes, bool batched)
 // FP32: four sites per thread, tiles of 64 x 16 and 32 x 32 sites.  FP64: two
 // sites per thread on twice the threads, the same tiles; four spilled.
 template <typename T, int NF, int MODEL>
-const void *kernel_shape(int vec, int lpr, int bs, int planes, bool batched)
+const void *kernel_shape(int vec, int lpr, int bs, int planes, bool ragged, bool batched)
 {
     if constexpr (sizeof(T) == 4) {
-        if (vec == 4 && lpr == 16 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 16, 256>(planes, batched);
-        if (vec == 4 && lpr == 8 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 8, 256>(planes, batched);
+        if (vec == 4 && lpr == 16 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 16, 256>(planes, ragged, batched);
+        if (vec == 4 && lpr == 8 && bs == 256) return kernel_planes<T, NF, MODEL, 4, 8, 256>(planes, ragged, batched);
     } else {
-        if (vec == 2 && lpr == 32 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 32, 512>(planes, batched);
-        if (vec == 2 && lpr == 16 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 16, 512>(planes, batched);
+        if (vec == 2 && lpr == 32 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 32, 512>(planes, ragged, batched);
+        if (vec == 2 && lpr == 16 && bs == 512) return kernel_planes<T, NF, MODEL, 2, 16, 512>(planes, ragged, batched);
     }
     return nullptr;
 }
 
 template <typename T, int MODEL>
-const void *kernel_nf(int nf, int vec, int lpr, int bs, int planes, bool batched)
+const void *kernel_nf(int nf, int vec, int lpr, int bs, int planes, bool ragged, bool batched)
 {
     switch (nf) {
-    case 1: return kernel_shape<T, 1, MODEL>(vec, lpr, bs, planes, batched);
-    case 2: return kernel_shape<T, 2, MODEL>(vec, lpr, bs, planes, batched);
-    case 3: return kernel_shape<T, 3, MODEL>(vec, lpr, bs, planes, batched);
+    case 1: return kernel_shape<T, 1, MODEL>(vec, lpr, bs, planes, ragged, batched);
+    case 2: return kernel_shape<T, 2, MODEL>(vec, lpr, bs, planes, ragged, batched);
+    case 3: return kernel_shape<T, 3, MODEL>(vec, lpr, bs, planes, ragged, batched);
     default: return nullptr;
     }
 }
@@ -369,10 +386,10 @@ const void *kernel_nf(int nf, int vec, int lpr, int bs, int planes, bool batched
 constexpr int kUnit = CE_UNIT_MODEL;
 
 template <>
-const void *resident_tiled_model<kUnit>(int precision, int nf, int vec, int lpr, int bs, int planes, bool batched)
+const void *resident_tiled_model<kUnit>(int precision, int nf, int vec, int lpr, int bs, int planes, bool ragged, bool batched)
 {
-    return precision == CE_FP64 ? kernel_nf<double, kUnit>(nf, vec, lpr, bs, planes, batched)
-                                : kernel_nf<float, kUnit>(nf, vec, lpr, bs, planes, batched);
+    return precision == CE_FP64 ? kernel_nf<double, kUnit>(nf, vec, lpr, bs, planes, ragged, batched)
+                                : kernel_nf<float, kUnit>(nf, vec, lpr, bs, planes, ragged, batched);
 }
 
 }  // namespace ce

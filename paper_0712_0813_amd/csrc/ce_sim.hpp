@@ -69,6 +69,7 @@ struct ce_sim {
     int step_block = 32;
     double m_host[CE_MAX_FIELDS] = {0, 0, 0};  // homogeneous references at load time
     ce_launch launch{CE_KERNEL_DIRECT, 0, 0, 0, 0, 0};
+    int grid = 0;           // blocks of the launch as reported (a ragged tiling may use fewer)
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // step block starting from buffer 0 / 1
     int graph_k = 0;
     // resident pass for the current launch (kernel nullptr: none)
@@ -87,9 +88,10 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg);
 // the recorded field maxima and queue the start-up half step.
 ce_status start_run(ce_sim *s);
 void drop_graphs(ce_sim *s);
-// Kernel of the resident pass of a tiled or 2-D streaming launch with one tile
-// or group of units per block (batched: of its pool form), nullptr if none.
-const void *resident_kernel(const ce_params *p, const ce_launch &c, bool batched);
+// Kernel of the resident pass of a tiled (ragged: on ragged tiles) or 2-D
+// streaming launch with one tile or group of units per block (batched: of its
+// pool form), nullptr if none.
+const void *resident_kernel(const ce_params *p, const ce_launch &c, bool ragged, bool batched);
 
 }  // namespace host
 }  // namespace ce

@@ -141,7 +141,11 @@ struct WavesHint {
 // pending load of the other branch writes (which would serialise the row
 // threads' halo loads behind their own-site loads, one memory round trip
 // each).
-template <typename T, int NF, int MODEL, int MODE, int VEC, int LPR, int BS, bool DYN>
+//
+// RAGGED: N need not be a multiple of the tile; a tile at the end of a row or
+// column holds vx x vy sites, its halo row and column lie next to those, and
+// threads beyond them load a site of the tile in vain and do nothing else.
+template <typename T, int NF, int MODEL, int MODE, int VEC, int LPR, int BS, bool DYN, bool RAGGED>
 __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b, int grid)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
@@ -158,7 +162,7 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
 
     const int N = lat.N;
     const int zc = lat.zc;
-    const int ntx = N / TX, nty = N / TY;
+    const int ntx = RAGGED ? (N + TX - 1) / TX : N / TX, nty = RAGGED ? (N + TY - 1) / TY : N / TY;
     // the z column is cut into nz chunks of near-equal length (zc planes
     // each when zc divides N)
     const int nz = (N + zc - 1) / zc;
@@ -180,14 +184,6 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
         pout[i] = as_global<T>(lat.p[src ^ 1][i]);
     }
 
-    // halo duties: one group of threads per side of the ring
-    const bool top = t < LPR;                          // row y0-1, group t
-    const bool bottom = t >= G4 && t < G4 + LPR;       // row y0+TY, group t-G4
-    const bool left = t >= 2 * G4 && t < 2 * G4 + TY;  // column x0-1, row t-2G4
-    const bool right = t >= 3 * G4 && t < 3 * G4 + TY; // column x0+TX, row t-3G4
-    const bool hrow = top || bottom;
-    const bool hcol = left || right;
-    const bool hduty = hrow || hcol;
 
     double acc[NQ];
 #pragma unroll
@@ -228,21 +224,31 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
         const int z0 = chunk * N / nz;
         const int zlen = (chunk + 1) * N / nz - z0;
         const int x0 = tx * TX, y0 = ty * TY;
+        const int vx = RAGGED ? min(TX, N - x0) : TX, vy = RAGGED ? min(TY, N - y0) : TY;
+        const bool ok = !RAGGED || (VEC * q < vx && y < vy);   // the thread has sites
+        // halo duties: one group of threads per side of the ring
+        const bool top = t < LPR && (!RAGGED || VEC * t < vx);                            // row y0-1, group t
+        const bool bottom = t >= G4 && t < G4 + LPR && (!RAGGED || VEC * (t - G4) < vx);  // row y0+vy, group t-G4
+        const bool left = t >= 2 * G4 && t < 2 * G4 + vy;                                 // column x0-1, row t-2G4
+        const bool right = t >= 3 * G4 && t < 3 * G4 + vy;                                // column x0+vx, row t-3G4
+        const bool hrow = top || bottom;
+        const bool hcol = left || right;
+        const bool hduty = hrow || hcol;
         // offsets within one plane (< N^2, 32 bits); plane bases are uniform
-        const unsigned own_xy = (unsigned)((y0 + y) * N + x0 + VEC * q);
+        const unsigned own_xy = ok ? (unsigned)((y0 + y) * N + x0 + VEC * q) : (unsigned)(y0 * N + x0);
         unsigned halo_xy = 0;
         int halo_slot = 0;  // LDS offset of this thread's halo value(s)
         if (top) {
             halo_xy = (unsigned)(((y0 + N - 1) % N) * N + x0 + VEC * t);
             halo_slot = VEC * t;
         } else if (bottom) {
-            halo_xy = (unsigned)(((y0 + TY) % N) * N + x0 + VEC * (t - G4));
-            halo_slot = (TY + 1) * TX + VEC * (t - G4);
+            halo_xy = (unsigned)(((y0 + vy) % N) * N + x0 + VEC * (t - G4));
+            halo_slot = (vy + 1) * TX + VEC * (t - G4);
         } else if (left) {
             halo_xy = (unsigned)((y0 + t - 2 * G4) * N + (x0 + N - VEC) % N);
             halo_slot = PLANE + (t - 2 * G4);
         } else if (right) {
-            halo_xy = (unsigned)((y0 + t - 3 * G4) * N + (x0 + TX) % N);
+            halo_xy = (unsigned)((y0 + t - 3 * G4) * N + (x0 + vx) % N);
             halo_slot = PLANE + TY + (t - 3 * G4);
         }
 
@@ -267,7 +273,7 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
                 const Vec<T, VEC> pq = gload<T, VEC>(pin[i] + base, own_xy);
 #pragma unroll
                 for (int e = 0; e < VEC; e++) own_drift<T, NF, MODE>(c, i, dq.v[e], pq.v[e], fcur[i][e], dcur[i][e]);
-                lds_store<T, VEC>(&lds[0][i][(y + 1) * TX + VEC * q], dcur[i]);
+                if (ok) lds_store<T, VEC>(&lds[0][i][(y + 1) * TX + VEC * q], dcur[i]);
                 if (hduty) {
                     const Vec<T, VEC> hd = gload<T, VEC>(din[i] + base, halo_xy);
                     const Vec<T, VEC> hp = gload<T, VEC>(pin[i] + base, halo_xy);
@@ -310,7 +316,7 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
                 T xl = lane_from_left(dcur[i][VEC - 1]);
                 T xr = lane_from_right(dcur[i][0]);
                 if (q == 0) xl = P[PLANE + y];
-                if (q == LPR - 1) xr = P[PLANE + TY + y];
+                if (RAGGED ? VEC * (q + 1) == vx : q == LPR - 1) xr = P[PLANE + TY + y];
                 const Vec<T, VEC> up = lds_load<T, VEC>(&P[y * TX + VEC * q]);
                 const Vec<T, VEC> dn = lds_load<T, VEC>(&P[(y + 2) * TX + VEC * q]);
 #pragma unroll
@@ -327,7 +333,7 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
 #pragma unroll
                 for (int e = 0; e < VEC; e++) own_drift<T, NF, MODE>(c, i, nd[i].v[e], np[i].v[e], fn1[i][e], dn1[i][e]);
                 if (more) {
-                    lds_store<T, VEC>(&lds[nb][i][(y + 1) * TX + VEC * q], dn1[i]);
+                    if (ok) lds_store<T, VEC>(&lds[nb][i][(y + 1) * TX + VEC * q], dn1[i]);
                     if (hrow) {
                         T hv[VEC];
 #pragma unroll
@@ -357,10 +363,11 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
 #pragma unroll
                 for (int i = 0; i < NF; i++) fcur[i][e] = pn[i];  // reuse: new stored derivative
             }
-            flush_sums(part, acc);
+            if (ok) flush_sums(part, acc);
 #pragma unroll
             for (int i = 0; i < NF; i++) {
-                if (MODE == kStep) {
+                if (!ok) {
+                } else if (MODE == kStep) {
                     gstore<T, VEC>(dout[i] + obase, own_xy, dcur[i]);
                     gstore<T, VEC>(pout[i] + obase, own_xy, fcur[i]);
                 } else {
@@ -392,15 +399,15 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
     finish_pass<T, NF, MODE, (NQ <= 13 ? 4 : 2)>(lat, grid, per_tile ? (int)ntiles : grid, red);
 }
 
-template <typename T, int NF, int MODEL, int MODE, int VEC, int LPR, int BS>
+template <typename T, int NF, int MODEL, int MODE, int VEC, int LPR, int BS, bool RAGGED>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WavesHint<T, NF, MODEL, VEC>::value, 8))) void
 tiled3d_kernel(Lattice lat, int src)
 {
-    tiled3d_body<T, NF, MODEL, MODE, VEC, LPR, BS, true>(lat, src, blockIdx.x, gridDim.x);
+    tiled3d_body<T, NF, MODEL, MODE, VEC, LPR, BS, true, RAGGED>(lat, src, blockIdx.x, gridDim.x);
 }
 
 // Step pass over many lattices of one class; see pass_batched.
-template <typename T, int NF, int MODEL, int VEC, int LPR, int BS>
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, bool RAGGED>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WavesHint<T, NF, MODEL, VEC>::value, 8))) void
 tiled3d_batched(const Lattice *lats, const int *blk_lat, int total)
 {
@@ -409,7 +416,7 @@ tiled3d_batched(const Lattice *lats, const int *blk_lat, int total)
         const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
         if (lat.sc->remaining <= 0) continue;
         const int src = lat.sc->cur;
-        tiled3d_body<T, NF, MODEL, kStep, VEC, LPR, BS, false>(lat, src, v - lat.first_block, lat.nblocks);
+        tiled3d_body<T, NF, MODEL, kStep, VEC, LPR, BS, false, RAGGED>(lat, src, v - lat.first_block, lat.nblocks);
     }
 }
 
@@ -428,22 +435,22 @@ constexpr bool lds_fits()
     return 3 * NF * ((TY + 2) * TX + 2 * TY) * (int)sizeof(T) + (BS / 64) * kMaxSums * 8 <= 160 * 1024;
 }
 
-template <typename T, int NF, int MODEL, int MODE, int VEC, int LPR, int BS>
+template <typename T, int NF, int MODEL, int MODE, int VEC, int LPR, int BS, bool RAGGED = false>
 hipError_t launch_one(const Lattice &lat, int src, hipStream_t st)
 {
-    if constexpr (lds_fits<T, NF, VEC, LPR, BS>()) {
-        hipLaunchKernelGGL((tiled3d_kernel<T, NF, MODEL, MODE, VEC, LPR, BS>), dim3(lat.nblocks), dim3(BS), 0, st, lat, src);
+    if constexpr (lds_fits<T, NF, VEC, LPR, BS>() && (!RAGGED || sizeof(T) == 4)) {
+        hipLaunchKernelGGL((tiled3d_kernel<T, NF, MODEL, MODE, VEC, LPR, BS, RAGGED>), dim3(lat.nblocks), dim3(BS), 0, st, lat, src);
         return hipGetLastError();
     } else {
         return hipErrorInvalidConfiguration;
     }
 }
 
-template <typename T, int NF, int MODEL, int VEC, int LPR, int BS>
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, bool RAGGED = false>
 hipError_t batched_one(const Lattice *lats, const int *blk_lat, int total, int grid, hipStream_t st)
 {
-    if constexpr (lds_fits<T, NF, VEC, LPR, BS>()) {
-        hipLaunchKernelGGL((tiled3d_batched<T, NF, MODEL, VEC, LPR, BS>), dim3(grid), dim3(BS), 0, st, lats, blk_lat,
+    if constexpr (lds_fits<T, NF, VEC, LPR, BS>() && (!RAGGED || sizeof(T) == 4)) {
+        hipLaunchKernelGGL((tiled3d_batched<T, NF, MODEL, VEC, LPR, BS, RAGGED>), dim3(grid), dim3(BS), 0, st, lats, blk_lat,
                            total);
         return hipGetLastError();
     } else {
@@ -451,12 +458,12 @@ hipError_t batched_one(const Lattice *lats, const int *blk_lat, int total, int g
     }
 }
 
-template <typename T, int NF, int MODEL, int VEC, int LPR, int BS>
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, bool RAGGED = false>
 int resident_batched_one()
 {
-    if constexpr (lds_fits<T, NF, VEC, LPR, BS>()) {
+    if constexpr (lds_fits<T, NF, VEC, LPR, BS>() && (!RAGGED || sizeof(T) == 4)) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled3d_batched<T, NF, MODEL, VEC, LPR, BS>, BS, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled3d_batched<T, NF, MODEL, VEC, LPR, BS, RAGGED>, BS, 0) !=
             hipSuccess)
             return 0;
         return n;
@@ -470,7 +477,7 @@ int resident_one()
 {
     if constexpr (lds_fits<T, NF, VEC, LPR, BS>()) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled3d_kernel<T, NF, MODEL, kStep, VEC, LPR, BS>, BS, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tiled3d_kernel<T, NF, MODEL, kStep, VEC, LPR, BS, false>, BS, 0) !=
             hipSuccess)
             return 0;
         return n;
@@ -486,6 +493,9 @@ struct ByShape {
     static hipError_t launch(const Lattice &lat, int src, hipStream_t st)
     {
         const int v = lat.vec, l = lat.lpr, b = lat.bs;
+        if (lat.ragged)   // the shapes ragged_tiling chooses from
+            return l == 16 ? launch_one<T, NF, MODEL, MODE, 4, 16, 256, true>(lat, src, st)
+                           : launch_one<T, NF, MODEL, MODE, 4, 8, 256, true>(lat, src, st);
         if (v == 4 && l == 16 && b == 256) return launch_one<T, NF, MODEL, MODE, 4, 16, 256>(lat, src, st);
         if (v == 4 && l == 8 && b == 256) return launch_one<T, NF, MODEL, MODE, 4, 8, 256>(lat, src, st);
         if (v == 2 && l == 32 && b == 256) return launch_one<T, NF, MODEL, MODE, 2, 32, 256>(lat, src, st);
@@ -497,8 +507,11 @@ struct ByShape {
         return hipErrorInvalidValue;
     }
     static hipError_t batched(const Lattice *lats, const int *blk_lat, int total, int grid, int v, int l, int b,
-                              hipStream_t st)
+                              bool ragged, hipStream_t st)
     {
+        if (ragged)
+            return l == 16 ? batched_one<T, NF, MODEL, 4, 16, 256, true>(lats, blk_lat, total, grid, st)
+                           : batched_one<T, NF, MODEL, 4, 8, 256, true>(lats, blk_lat, total, grid, st);
         if (v == 4 && l == 16 && b == 256) return batched_one<T, NF, MODEL, 4, 16, 256>(lats, blk_lat, total, grid, st);
         if (v == 4 && l == 8 && b == 256) return batched_one<T, NF, MODEL, 4, 8, 256>(lats, blk_lat, total, grid, st);
         if (v == 2 && l == 32 && b == 256) return batched_one<T, NF, MODEL, 2, 32, 256>(lats, blk_lat, total, grid, st);
@@ -521,8 +534,11 @@ struct ByShape {
         if (v == 4 && l == 64 && b == 512) return resident_one<T, NF, MODEL, 4, 64, 512>();
         return 0;
     }
-    static int resident_batched(int v, int l, int b)
+    static int resident_batched(int v, int l, int b, bool ragged)
     {
+        if (ragged)
+            return l == 16 ? resident_batched_one<T, NF, MODEL, 4, 16, 256, true>()
+                           : resident_batched_one<T, NF, MODEL, 4, 8, 256, true>();
         if (v == 4 && l == 16 && b == 256) return resident_batched_one<T, NF, MODEL, 4, 16, 256>();
         if (v == 4 && l == 8 && b == 256) return resident_batched_one<T, NF, MODEL, 4, 8, 256>();
         if (v == 2 && l == 32 && b == 256) return resident_batched_one<T, NF, MODEL, 2, 32, 256>();
@@ -553,9 +569,9 @@ template <typename T, int MODEL>
 hipError_t batched_t(const Lattice *lats, const int *blk_lat, int total, int grid, const Lattice &p, hipStream_t st)
 {
     switch (p.nf) {
-    case 1: return ByShape<T, 1, MODEL>::batched(lats, blk_lat, total, grid, p.vec, p.lpr, p.bs, st);
-    case 2: return ByShape<T, 2, MODEL>::batched(lats, blk_lat, total, grid, p.vec, p.lpr, p.bs, st);
-    case 3: return ByShape<T, 3, MODEL>::batched(lats, blk_lat, total, grid, p.vec, p.lpr, p.bs, st);
+    case 1: return ByShape<T, 1, MODEL>::batched(lats, blk_lat, total, grid, p.vec, p.lpr, p.bs, p.ragged != 0, st);
+    case 2: return ByShape<T, 2, MODEL>::batched(lats, blk_lat, total, grid, p.vec, p.lpr, p.bs, p.ragged != 0, st);
+    case 3: return ByShape<T, 3, MODEL>::batched(lats, blk_lat, total, grid, p.vec, p.lpr, p.bs, p.ragged != 0, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -564,9 +580,9 @@ template <typename T, int MODEL>
 int resident_batched_t(const Lattice &p)
 {
     switch (p.nf) {
-    case 1: return ByShape<T, 1, MODEL>::resident_batched(p.vec, p.lpr, p.bs);
-    case 2: return ByShape<T, 2, MODEL>::resident_batched(p.vec, p.lpr, p.bs);
-    default: return ByShape<T, 3, MODEL>::resident_batched(p.vec, p.lpr, p.bs);
+    case 1: return ByShape<T, 1, MODEL>::resident_batched(p.vec, p.lpr, p.bs, p.ragged != 0);
+    case 2: return ByShape<T, 2, MODEL>::resident_batched(p.vec, p.lpr, p.bs, p.ragged != 0);
+    default: return ByShape<T, 3, MODEL>::resident_batched(p.vec, p.lpr, p.bs, p.ragged != 0);
     }
 }
 
@@ -633,7 +649,26 @@ bool tiled_fits(int dims, int N, int vec, int lpr, int bs, int zc)
 long long tiled_tiles(int N, int vec, int lpr, int bs, int zc)
 {
     const int TX = vec * lpr, TY = bs / lpr;
-    return (long long)(N / TX) * (N / TY) * ((N + zc - 1) / zc);
+    return (long long)((N + TX - 1) / TX) * ((N + TY - 1) / TY) * ((N + zc - 1) / zc);
+}
+
+// The direct pass covers a lattice that no tile divides with one quad per
+// thread, and a resident pass takes that up to 80^3 (two of its blocks as one).
+// Beyond, up to kSyncRows tiles of eight planes, it runs on ragged tiles, of
+// the two shapes the one that leaves fewer threads without sites (100^3 x 2
+// fields: 11.8 us a step resident, 25.3 direct).  Larger lattices stay on the
+// direct pass: rows that do not start on whole cache lines cost 64-wide tiles
+// as much as the direct pass's neighbour reads (200^3: 102 us ragged, 88
+// direct).  FP32, which the resident pass is built for.
+bool ragged_tiling(int precision, int dims, int N, RaggedTiling *out)
+{
+    if (precision != CE_FP32 || dims != 3 || N <= 80 || N % 32 == 0) return false;
+    auto cols = [N](int lpr) { return ((N + 4 * lpr - 1) / (4 * lpr)) * ((N + kBlock / lpr - 1) / (kBlock / lpr)); };
+    out->lpr = cols(8) < cols(16) ? 8 : 16;   // tiles of either shape hold 1024 sites a plane
+    const int nz = (N + 7) / 8;
+    out->planes = (N + nz - 1) / nz;
+    out->tiles = cols(out->lpr) * ((N + out->planes - 1) / out->planes);
+    return out->tiles <= kSyncRows;
 }
 
 int tiled_resident_blocks(int model, int precision, int nf, int vec, int lpr, int bs)

@@ -29,7 +29,9 @@ SIZES = [
     (3, 32, 2, (T3, 4, 8, 256, 1, 0)), (3, 32, 3, (T3, 4, 8, 256, 4, 8)), (3, 64, 2, (T3, 4, 16, 256, 1, 0)),
     (3, 64, 3, (T3, 4, 16, 256, 2, 0)), (3, 64, 1, (T3, 4, 8, 256, 8, 7)), (3, 64, 2, (T3, 4, 8, 256, 4, 0)),
     (3, 96, 2, (T3, 4, 8, 256, 8, 0)), (3, 128, 2, (T3, 4, 16, 256, 8, 0)), (3, 128, 1, (T3, 4, 8, 256, 8, 0)),
-    (3, 60, 1, None), (3, 76, 2, None), (3, 100, 2, None),
+    # two blocks of the direct launch as one; ragged tiles
+    (3, 68, 2, None), (3, 80, 1, None), (3, 84, 3, None), (3, 92, 2, None), (3, 124, 1, None),
+    (3, 60, 1, None), (3, 100, 2, None),
 ]
 
 
