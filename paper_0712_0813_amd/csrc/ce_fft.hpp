@@ -84,6 +84,25 @@ __device__ void lds_fft(double2 *buf, int N, int logN, int lines, const double2 
     }
 }
 
+// Elements 0..total of a block's lines from memory to LDS or back: element idx
+// goes through v = load(idx), store(idx, v), with kInFlight loads of a thread
+// under way before its first store.  (One after the other, each waits a whole
+// memory round trip: of the 78 us of the middle axis of a 256^3 spectrum, which
+// moves 270 MB, the eight trips of a block were most.)  load must take
+// any idx < total.
+template <int kThreads, int kInFlight, typename Load, typename Store>
+__device__ inline void staged(int total, Load load, Store store)
+{
+    for (int base = threadIdx.x; base < total; base += kThreads * kInFlight) {
+        decltype(load(0)) v[kInFlight];
+#pragma unroll
+        for (int k = 0; k < kInFlight; k++) v[k] = load(min(base + k * kThreads, total - 1));
+#pragma unroll
+        for (int k = 0; k < kInFlight; k++)
+            if (base + k * kThreads < total) store(base + k * kThreads, v[k]);
+    }
+}
+
 // Blocks are dealt round-robin over the 8 XCDs (block b on XCD b % 8), each
 // with its own L2.  Renumbering so that every XCD's blocks take one
 // contiguous range keeps neighbouring lines (which share cache lines when a

@@ -152,27 +152,32 @@ __global__ __launch_bounds__(kGenThreads) void axis1_kernel(GrfArgs g, const dou
     const int lines = rows * M;
     const int first = (int)xcd_contiguous(blockIdx.x, gridDim.x) * lpw;
     const int nl = min(lpw, lines - first);
-    for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
-        const int l = idx % lpw, p = idx / lpw;
-        double2 v = make_double2(0.0, 0.0);
-        const int n1 = p <= N / 2 ? p : p - N;
-        if (l < nl && n1 >= -K && n1 <= K) {
-            const int line = first + l;
-            const int r = line / M, m = line % M;
-            v = Y[((long long)(r0 + r) * W + (n1 + K)) * M + m];
-        }
-        lds[l * line_stride(N) + padded(bitrev(p, g.logN))] = v;
-    }
+    // lpw is a power of two that divides the block: every element of this
+    // thread is of one line; lines past the last read the last one again and
+    // are not written
+    const int log_lpw = __ffs(lpw) - 1;
+    const int l = threadIdx.x & (lpw - 1);
+    const int line = first + min(l, nl - 1);
+    const int r = line / M, m = line % M;
+    const double2 *y = Y + (long long)(r0 + r) * W * M + m;
+    double2 *z = Z + (long long)r * N * M + m;
+    double2 *x = lds + l * line_stride(N);
+    staged<kGenThreads, 8>(
+        lpw * N,
+        [&](int idx) {
+            const int p = idx >> log_lpw;
+            const int n1 = p <= N / 2 ? p : p - N;
+            double2 v = make_double2(0.0, 0.0);
+            if (n1 >= -K && n1 <= K) v = y[(long long)(n1 + K) * M];
+            return v;
+        },
+        [&](int idx, double2 v) { x[padded(bitrev(idx >> log_lpw, g.logN))] = v; });
     __syncthreads();
     lds_fft<false>(lds, N, g.logN, lpw, tw);
-    for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
-        const int l = idx % lpw, x1 = idx / lpw;
-        if (l < nl) {
-            const int line = first + l;
-            const int r = line / M, m = line % M;
-            Z[((long long)r * N + x1) * M + m] = lds[l * line_stride(N) + padded(x1)];
-        }
-    }
+    if (l < nl)
+        staged<kGenThreads, 8>(
+            lpw * N, [&](int idx) { return x[padded(idx >> log_lpw)]; },
+            [&](int idx, double2 v) { z[(long long)(idx >> log_lpw) * M] = v; });
 }
 
 // Last axis: row r of Z (K+1 values, or the generated 1-D modes when Z is
@@ -206,17 +211,25 @@ __global__ __launch_bounds__(kGenThreads) void last_axis_kernel(GrfArgs g, const
         const int l = idx >> g.logN, p = idx & (N - 1);
         if (p > K && p < N - K) lds[l * line_stride(N) + padded(bitrev(p, g.logN))] = make_double2(0.0, 0.0);
     }
-    for (int idx = threadIdx.x; idx < lpw * M; idx += blockDim.x) {
-        const int l = idx / M, p = idx - l * M;
-        const double2 a = mode(2 * l, p), b = mode(2 * l + 1, p);
-        double2 *x = lds + l * line_stride(N);
-        if (p == 0) {
-            x[0] = make_double2(a.x, b.x);   // only the real parts enter a row
-        } else {
-            x[padded(bitrev(p, g.logN))] = make_double2(a.x - b.y, a.y + b.x);
-            x[padded(bitrev(N - p, g.logN))] = make_double2(a.x + b.y, b.x - a.y);
-        }
-    }
+    struct Modes {
+        double2 a, b;
+    };
+    staged<kGenThreads, 2>(
+        lpw * M,
+        [&](int idx) {
+            const int l = idx / M, p = idx - l * M;
+            return Modes{mode(2 * l, p), mode(2 * l + 1, p)};
+        },
+        [&](int idx, Modes v) {
+            const int l = idx / M, p = idx - l * M;
+            double2 *x = lds + l * line_stride(N);
+            if (p == 0) {
+                x[0] = make_double2(v.a.x, v.b.x);   // only the real parts enter a row
+            } else {
+                x[padded(bitrev(p, g.logN))] = make_double2(v.a.x - v.b.y, v.a.y + v.b.x);
+                x[padded(bitrev(N - p, g.logN))] = make_double2(v.a.x + v.b.y, v.b.x - v.a.y);
+            }
+        });
     __syncthreads();
     lds_fft<false>(lds, N, g.logN, lpw, tw);
     float mx = 0.0f;
@@ -241,7 +254,9 @@ __global__ __launch_bounds__(kGenThreads) void last_axis_kernel(GrfArgs g, const
     }
 }
 
-int lines_per_group(int N) { return std::max(1, kLdsLines / N); }
+// lines of a block: at most one a thread, so that a thread's elements are all
+// of one line
+int lines_per_group(int N) { return std::min(kGenThreads, std::max(1, kLdsLines / N)); }
 
 size_t lds_bytes(int N) { return (size_t)lines_per_group(N) * line_stride(N) * sizeof(double2); }
 

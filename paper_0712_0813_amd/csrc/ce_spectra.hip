@@ -14,6 +14,12 @@
 //   final kernel  first axis (2-D and 3-D), then |F|^2 into radial bins
 //   reduce kernel per-block partial bins summed in a fixed order
 //
+// 256^3, one FP32 field, both spectra: 475 us (1.21 GB moved at the least, 229
+// us at a copy's rate); 565 with each thread's loads one after the other, the
+// line of every element found by a 64-bit division and the run sums through
+// LDS shuffles; 728 with one row a transform.  64^3 133 -> 91 us.  What is
+// left is the LDS round trips of the stages (57-68 us a kernel).
+//
 // Binning is deterministic: one wavefront per block walks each line's
 // elements in order of increasing |n_0| (the bin is then non-decreasing),
 // sums runs of equal bins with a segmented scan across the wavefront and adds
@@ -49,8 +55,9 @@ int spec_lines(int N) { return std::max(1, kSpecLines / N); }
 // lines of 1024 per block were slower than one)
 int spec_final_lines(int N) { return spec_lines(N); }
 // the middle axis: two line buffers per block (1024^3: 6.4 ms per pass
-// against 7.6 ms with one; the rows are faster with one, 6.6 against 8.4 ms)
-int spec_mid_lines(int N) { return std::max(1, 2 * kSpecLines / N); }
+// against 7.6 ms with one; the rows are faster with one, 6.6 against 8.4 ms).
+// Never more lines than threads: a thread's elements are all of one line.
+int spec_mid_lines(int N) { return std::min(kSpecThreads, std::max(1, 2 * kSpecLines / N)); }
 
 int nbins_of(int dims, int N)
 {
@@ -103,17 +110,23 @@ __global__ __launch_bounds__(kSpecThreads) void spec_rows_kernel(const T *__rest
     c.bm = (T)(beta * m);
     c.r = (T)0;
     c.m1 = (T)0;
+    // rows past the last are zero (and read the last one)
     auto site = [&](int row, int x) {
-        if (row >= nl) return 0.0;
-        const long long s = (first + row) * N + x;
+        const long long s = (first + min(row, nl - 1)) * N + x;
         const T dv = d[s];
-        if (which == 0) return m + (double)dv;
-        return started ? (double)fdot_of(dv, p[s], c) : (double)p[s];
+        double v = m + (double)dv;
+        if (which) v = started ? (double)fdot_of(dv, p[s], c) : (double)p[s];
+        return row < nl ? v : 0.0;
     };
-    for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
-        const int l = idx >> logN, x = idx & (N - 1);
-        lds[l * line_stride(N) + padded(bitrev(x, logN))] = make_double2(site(2 * l, x), site(2 * l + 1, x));
-    }
+    staged<kSpecThreads, 4>(
+        lpw * N,
+        [&](int idx) {
+            const int l = idx >> logN, x = idx & (N - 1);
+            return make_double2(site(2 * l, x), site(2 * l + 1, x));
+        },
+        [&](int idx, double2 v) {
+            lds[(idx >> logN) * line_stride(N) + padded(bitrev(idx & (N - 1), logN))] = v;
+        });
     __syncthreads();
     lds_fft<true>(lds, N, logN, lpw, tw);
     for (int idx = threadIdx.x; idx < 2 * lpw * kc; idx += blockDim.x) {
@@ -133,50 +146,62 @@ __global__ __launch_bounds__(kSpecThreads) void spec_mid_kernel(int N, int logN,
                                                                ZBuf Z, int lpw)
 {
     extern __shared__ double2 lds[];
-    const int kc = Z.kc;
-    const long long lines = (long long)N * kc;
-    const long long first = xcd_contiguous(blockIdx.x, gridDim.x) * lpw;
-    const int nl = (int)min((long long)lpw, lines - first);
-    for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
-        const int l = idx % lpw, x1 = idx / lpw;
-        double2 v = make_double2(0.0, 0.0);
-        if (l < nl) {
-            const long long line = first + l;
-            const long long x0 = line / kc, kk = line % kc;
-            v = Z.row(x0 * N + x1)[kk];
-        }
-        lds[l * line_stride(N) + padded(bitrev(x1, logN))] = v;
-    }
+    const unsigned kc = Z.kc;
+    const int lines = N * (int)kc;   // < 2^22
+    const int first = (int)xcd_contiguous(blockIdx.x, gridDim.x) * lpw;
+    const int nl = min(lpw, lines - first);
+    // lpw is a power of two that divides the block, so every element of this
+    // thread is of one line (the divisions for it, once, are as many
+    // instructions as the rest of an element's load); lines past the last
+    // read the last one again and are not written
+    const int log_lpw = __ffs(lpw) - 1;
+    const int l = threadIdx.x & (lpw - 1);
+    const unsigned line = (unsigned)(first + min(l, nl - 1));
+    const unsigned row0 = line / kc * N, kk = line % kc;
+    double2 *x = lds + l * line_stride(N);
+    staged<kSpecThreads, 8>(
+        lpw * N, [&](int idx) { return Z.row(row0 + (idx >> log_lpw))[kk]; },
+        [&](int idx, double2 v) { x[padded(bitrev(idx >> log_lpw, logN))] = v; });
     __syncthreads();
     lds_fft<true>(lds, N, logN, lpw, tw);
-    for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
-        const int l = idx % lpw, n1 = idx / lpw;
-        if (l < nl) {
-            const long long line = first + l;
-            const long long x0 = line / kc, kk = line % kc;
-            Z.row(x0 * N + n1)[kk] = lds[l * line_stride(N) + padded(n1)];
-        }
-    }
+    if (l < nl)
+        staged<kSpecThreads, 8>(
+            lpw * N, [&](int idx) { return x[padded(idx >> log_lpw)]; },
+            [&](int idx, double2 v) { Z.row(row0 + (idx >> log_lpw))[kk] = v; });
 }
 
 // Segmented inclusive sums over the wavefront of runs of equal (non-
-// decreasing) keys; the last lane of each run adds the run's totals to the
-// histograms.  Called by all 64 lanes of one wavefront.
+// decreasing, -1 in lanes past the last) keys; the last lane of each run adds
+// the run's totals to the histograms.  Called by all 64 lanes of one wavefront.
+// Inclusive sums by lane moves in the vector unit: shifts by 1, 2, 4 and 8
+// within a row of 16 lanes, then the last lane of a row to the next row and
+// lane 31 to the upper half.  Equal keys at both ends of a move are one run.
+// (As shuffles through LDS the 24 moves of a call, and not the transform,
+// were what the first-axis kernel waited for.)
+template <int kMove, int kRows>
+__device__ inline void run_step(int key, double &v, unsigned &w)
+{
+    constexpr int kNone = -2;   // lanes without a source
+    const int ko = __builtin_amdgcn_update_dpp(kNone, key, kMove, kRows, 0xf, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kMove, kRows, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kMove, kRows, 0xf, false);
+    const int wo = __builtin_amdgcn_update_dpp(0, (int)w, kMove, kRows, 0xf, false);
+    if (ko == key) {
+        v += __hiloint2double(hi, lo);
+        w += (unsigned)wo;
+    }
+}
+
 __device__ inline void bin_add(int key, double v, unsigned w, double *hp, unsigned *hc)
 {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int ko = __shfl_up(key, off, 64);
-        const double vo = __shfl_up(v, off, 64);
-        const unsigned wo = __shfl_up(w, off, 64);
-        if (lane >= off && ko == key) {
-            v += vo;
-            w += wo;
-        }
-    }
-    const int kn = __shfl_down(key, 1, 64);
-    if (key >= 0 && (lane == 63 || kn != key)) {
+    run_step<0x111, 0xf>(key, v, w);   // row_shr:1
+    run_step<0x112, 0xf>(key, v, w);
+    run_step<0x114, 0xf>(key, v, w);
+    run_step<0x118, 0xf>(key, v, w);
+    run_step<0x142, 0xa>(key, v, w);   // row_bcast:15, into rows 1 and 3
+    run_step<0x143, 0xc>(key, v, w);   // row_bcast:31, into rows 2 and 3
+    const int kn = __builtin_amdgcn_update_dpp(-2, key, 0x130, 0xf, 0xf, false);   // wave_shl:1
+    if (key >= 0 && kn != key) {
         hp[key] += v;
         hc[key] += w;
     }
@@ -184,11 +209,11 @@ __device__ inline void bin_add(int key, double v, unsigned w, double *hp, unsign
 
 // Adds one transformed line (first-axis values x[0..N), natural order, padded)
 // to the histograms.  n0 and -n0 share their bin, so an element of the walk is
-// such a pair, in order of |n0|: the bins are non-decreasing along it.  The
-// wavefront wv < nwb bins its contiguous part of |n0| < N/2, the last one also
-// -N/2.  dims 3: line = n1 kc + kk; dims 2: line = kk.
-__device__ inline void bin_line(const double2 *x, long long line, int dims, int N, int k0, int kc, int nwb, int wv,
-                                double inv_norm, double *hp, unsigned *hc)
+// such a pair, in order of |n0|: the bins are non-decreasing along it.  Part
+// part < nparts of it is a contiguous part of |n0| < N/2, the last one also
+// has -N/2.  dims 3: line = n1 kc + kk; dims 2: line = kk.
+__device__ inline void bin_line(const double2 *x, unsigned line, int dims, int N, int k0, unsigned kc, int nparts,
+                                int part, double inv_norm, double *hp, unsigned *hc)
 {
     const int halfN = N / 2;
     int base2, klast;
@@ -203,9 +228,9 @@ __device__ inline void bin_line(const double2 *x, long long line, int dims, int 
     }
     const unsigned wt = (klast == 0 || klast == halfN) ? 1u : 2u;
     const int lane = threadIdx.x & 63;
-    const int seg = halfN / nwb;   // this wavefront's part of the walk
-    const int e_end = (wv + 1) * seg;
-    for (int e0 = wv * seg; e0 < e_end; e0 += 64) {
+    const int seg = halfN / nparts;
+    const int e_end = (part + 1) * seg;
+    for (int e0 = part * seg; e0 < e_end; e0 += 64) {
         const int e = e0 + lane;
         int key = -1;   // lanes past the part's end add nothing
         double v = 0.0;
@@ -224,7 +249,7 @@ __device__ inline void bin_line(const double2 *x, long long line, int dims, int 
         }
         bin_add(key, v, w, hp, hc);
     }
-    if (wv == nwb - 1 && lane == 0) {
+    if (part == nparts - 1 && lane == 0) {
         const double2 X = x[padded(halfN)];
         const int key = isqrt(halfN * halfN + base2);
         hp[key] += (double)wt * (X.x * X.x + X.y * X.y) * inv_norm;
@@ -235,9 +260,10 @@ __device__ inline void bin_line(const double2 *x, long long line, int dims, int 
 // First axis and binning.  dims 3: line (n1, kk), element x0 at
 // Z[(x0 N + n1) kc + kk]; dims 2: line kk, element x0 at Z[x0 kc + kk];
 // dims 1: the kc values of Z are the spectrum itself (no transform).
-// partial[g][0..nb) accumulates the power, partial[g][nb..2nb) the counts.
-// nwb wavefronts bin each line, wavefront w the w-th contiguous part of the
-// line's walk, each into its own histogram; the block adds them in order.
+// partial[g][0..nb) takes the power, partial[g][nb..2nb) the counts, added to
+// what is there when `add`.  nwb wavefronts bin, each into its own histogram,
+// which the block adds in order: nparts of them share a line, part by part of
+// its walk, and nwb / nparts lines are binned at a time.
 //
 // Order of the lines: an element read is 16 bytes of a 128-byte line of Z,
 // whose other bytes belong to the neighbouring lines.  Each XCD (block b runs
@@ -247,9 +273,9 @@ __device__ inline void bin_line(const double2 *x, long long line, int dims, int 
 __global__ __launch_bounds__(kSpecThreads) void spec_final_kernel(int dims, int N, int logN, int k0, int nb,
                                                                  double inv_norm, const double2 *__restrict__ tw,
                                                                  ZBuf Z, double *__restrict__ partial, int lpw,
-                                                                 int nwb)
+                                                                 int nwb, int nparts, int add)
 {
-    const int kc = Z.kc;
+    const unsigned kc = Z.kc;
     extern __shared__ double2 lds[];
     double *hp_all = reinterpret_cast<double *>(lds + lpw * line_stride(N));   // [nwb][nb]
     unsigned *hc_all = reinterpret_cast<unsigned *>(hp_all + nwb * nb);  // [nwb][nb]
@@ -265,12 +291,12 @@ __global__ __launch_bounds__(kSpecThreads) void spec_final_kernel(int dims, int 
     if (dims == 1) {
         // one line: k_last = k0 + kk, increasing
         if (blockIdx.x == 0 && threadIdx.x < 64) {
-            for (int base = 0; base < kc; base += 64) {
+            for (int base = 0; base < (int)kc; base += 64) {
                 const int kk = base + (int)threadIdx.x;
                 int key = -1;
                 double v = 0.0;
                 unsigned w = 0u;
-                if (kk < kc) {
+                if (kk < (int)kc) {
                     const int k = k0 + kk;
                     const unsigned wt = (k == 0 || k == halfN) ? 1u : 2u;
                     const double2 X = Z.row(0)[kk];
@@ -282,37 +308,39 @@ __global__ __launch_bounds__(kSpecThreads) void spec_final_kernel(int dims, int 
             }
         }
     } else {
-        const long long lines = dims == 3 ? (long long)N * kc : (long long)kc;
-        const long long groups = (lines + lpw - 1) / lpw;
+        const int lines = dims == 3 ? N * (int)kc : (int)kc;   // < 2^22
+        const int groups = (lines + lpw - 1) / lpw;
         // this XCD's blocks: nx of them, the first at position vx of the
         // XCD-contiguous numbering; this block is the i-th
-        const long long nblk = gridDim.x, nq = nblk / 8, nr = nblk % 8;
-        const long long x = blockIdx.x % 8, i = blockIdx.x / 8;
-        const long long nx = nq + (x < nr ? 1 : 0);
-        const long long vx = x * nq + (x < nr ? x : nr);
+        const int nblk = gridDim.x, nq = nblk / 8, nr = nblk % 8;
+        const int x = blockIdx.x % 8, i = blockIdx.x / 8;
+        const int nx = nq + (x < nr ? 1 : 0);
+        const int vx = x * nq + (x < nr ? x : nr);
         // groups split over the blocks in XCD-contiguous order; the XCD's
         // range is the union of its blocks' shares
-        const long long per = groups / nblk, extra = groups % nblk;
-        auto start_of = [&](long long v) { return v * per + (v < extra ? v : extra); };
-        const long long g0 = start_of(vx), g1 = start_of(vx + nx);
-        for (long long q = g0 + i; q < g1; q += nx) {
-            const long long first = q * lpw;
-            const int nl = (int)min((long long)lpw, lines - first);
-            for (int idx = threadIdx.x; idx < lpw * N; idx += blockDim.x) {
-                const int l = idx % lpw, x0 = idx / lpw;
-                double2 val = make_double2(0.0, 0.0);
-                if (l < nl) {
-                    // 3-D: line = n1 kc + kk, element x0 in row x0 N + n1; 2-D: line kk, row x0
-                    const long long line = first + l;
-                    val = dims == 3 ? Z.row((long long)x0 * N + line / kc)[line % kc] : Z.row(x0)[line];
-                }
-                lds[l * line_stride(N) + padded(bitrev(x0, logN))] = val;
-            }
+        const int per = groups / nblk, extra = groups % nblk;
+        auto start_of = [&](int v) { return v * per + (v < extra ? v : extra); };
+        const int g0 = start_of(vx), g1 = start_of(vx + nx);
+        // every element of this thread is of one line, as on the middle axis
+        const int log_lpw = __ffs(lpw) - 1;
+        const int l = threadIdx.x & (lpw - 1);
+        double2 *xl = lds + l * line_stride(N);
+        const unsigned rstep = dims == 3 ? N : 1;
+        for (int q = g0 + i; q < g1; q += nx) {
+            const int first = q * lpw;
+            const int nl = min(lpw, lines - first);
+            // 3-D: line = n1 kc + kk, element x0 in row x0 N + n1; 2-D: line kk, row x0
+            const unsigned line = (unsigned)(first + min(l, nl - 1));
+            const unsigned row0 = dims == 3 ? line / kc : 0, kk = dims == 3 ? line % kc : line;
+            staged<kSpecThreads, 4>(
+                lpw * N, [&](int idx) { return Z.row(row0 + (idx >> log_lpw) * rstep)[kk]; },
+                [&](int idx, double2 v) { xl[padded(bitrev(idx >> log_lpw, logN))] = v; });
             __syncthreads();
             lds_fft<true>(lds, N, logN, lpw, tw);
             if (wv < nwb)
-                for (int l = 0; l < nl; l++)
-                    bin_line(lds + l * line_stride(N), first + l, dims, N, k0, kc, nwb, wv, inv_norm, hp, hc);
+                for (int b = wv / nparts; b < nl; b += nwb / nparts)
+                    bin_line(lds + b * line_stride(N), first + b, dims, N, k0, kc, nparts, wv % nparts, inv_norm, hp,
+                             hc);
             __syncthreads();
         }
     }
@@ -325,8 +353,8 @@ __global__ __launch_bounds__(kSpecThreads) void spec_final_kernel(int dims, int 
             pw += hp_all[w * nb + j];
             cnt += hc_all[w * nb + j];
         }
-        mine[j] += pw;
-        mine[nb + j] += (double)cnt;
+        mine[j] = add ? mine[j] + pw : pw;
+        mine[nb + j] = add ? mine[nb + j] + (double)cnt : (double)cnt;
     }
 }
 
@@ -451,18 +479,20 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
     hipStream_t st = s->stream;
     const size_t lds_line = (size_t)lpw * line_stride(N) * sizeof(double2);
     const size_t lds_mid = (size_t)lpw_mid * line_stride(N) * sizeof(double2);
-    // as many binning wavefronts (2 or 1) as leave the block within 40 KiB of
-    // LDS, so that four blocks fit a compute unit (1024^3: 8.4 ms per
+    // as many binning wavefronts (4, 2 or 1) as leave the block within 40 KiB
+    // of LDS, so that four blocks fit a compute unit (1024^3: 8.4 ms per
     // first-axis pass, against 10.9 ms with four wavefronts at two blocks per
-    // unit and 10.3 ms with one at six)
+    // unit and 10.3 ms with one at six); a part of a line's walk is no less
+    // than 64 elements, one for each lane
     int nwb = 1;
-    for (int w = 2; w >= 1; w /= 2)
+    for (int w = kSpecThreads / 64; w >= 1; w /= 2)
         if ((size_t)lpw_final * line_stride(N) * sizeof(double2) + (size_t)w * nb * (sizeof(double) + sizeof(unsigned)) <= 40960) {
             nwb = w;
             break;
         }
     const size_t lds_final =
         (size_t)lpw_final * line_stride(N) * sizeof(double2) + (size_t)nwb * nb * (sizeof(double) + sizeof(unsigned));
+    const int nparts = std::min(nwb, std::max(1, N / 128));
     const double inv_norm = 1.0 / pow((double)N, 2.0 * dims);
     const bool fp64 = s->p.precision == CE_FP64;
 
@@ -470,7 +500,6 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
     for (int which = 0; which < 2; which++) {
         double *dst = which == 0 ? power_f : power_fdot;
         if (!dst && !(which == 0 && count)) continue;
-        CE_HIP(hipMemsetAsync(partial, 0, (size_t)G * 2 * nb * sizeof(double), st));
         for (int k0 = 0; k0 < M; k0 += kc) {
             const int kcc = std::min(kc, M - k0);
             ZBuf Z;
@@ -499,7 +528,7 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
                 CE_HIP(hipGetLastError());
             }
             hipLaunchKernelGGL(spec_final_kernel, dim3(G), blk, lds_final, st, dims, N, logN, k0, nb, inv_norm,
-                               tw, Z, partial, lpw_final, nwb);
+                               tw, Z, partial, lpw_final, nwb, nparts, k0 > 0 ? 1 : 0);
             CE_HIP(hipGetLastError());
         }
         hipLaunchKernelGGL(spec_reduce_kernel, dim3((2 * nb + 63) / 64), dim3(kReduceThreads), 0, st, partial, G, nb,
