@@ -420,12 +420,12 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
 // widest tile that divides N (256 x 4 sites, 4 per thread, then 64 x 16,
 // then 32 x 32): wide tiles keep the x halo to 2 of every 8 cache lines.
 // Large lattices keep every resident block busy with the longest chunks that
-// give every block the same whole number (>= 2) of tiles (three of 342, 342
-// and 340 planes at 1024^3); medium ones (N >= 64) get one tile per compute
-// unit with the tallest chunks
-// that allow it; smaller ones take the tallest chunks that leave three tiles
-// per compute unit, or the direct kernel when they cannot give one tile per
-// compute unit.
+// give every block the same whole number of tiles (three chunks of 342, 342
+// and 340 planes at 1024^3, four tiles a block); lattices that a resident pass
+// can take are cut into up to 256 tiles; medium ones get two tiles or so per
+// compute unit, else one (N >= 64) with the tallest chunks that allow it;
+// smaller ones take the tallest chunks that leave three tiles per compute
+// unit, or the direct kernel when they cannot give one tile per compute unit.
 ce_launch default_launch(const ce_params *p, int cus)
 {
     ce_launch c{CE_KERNEL_DIRECT, 0, 0, 0, 0, 0};
@@ -464,6 +464,25 @@ ce_launch default_launch(const ce_params *p, int cus)
         if (resident > kMaxBlocks) resident = kMaxBlocks;
         if (resident >= 8) resident = resident / 8 * 8;
         const long long cols = tiled_tiles(p->N, v, l, bs, p->N);
+        // A lattice whose columns divide the resident blocks (up to three a
+        // compute unit) has one tile for each, with no second start and the
+        // fewest halo planes (512^3, ms a step with one tile a block and with
+        // the rule below: one field 0.378 and 0.447, two 0.799 and 0.834,
+        // three 1.21 and 1.22; FP64, two 1.82 and 1.85.  A single chunk, the
+        // whole column, gains nothing: FP64, three, 2.78 and 2.75).
+        const long long one = std::min<long long>(resident, 3LL * cus);
+        if (one > cols && one % cols == 0 && p->N / (one / cols) >= 64) {
+            const int nz = (int)(one / cols), planes = (p->N + nz - 1) / nz;
+            if ((p->N + planes - 1) / planes == nz) {
+                c.kernel = CE_KERNEL_TILED3D;
+                c.sites_per_thread = v;
+                c.lanes_per_row = l;
+                c.block = bs;
+                c.planes = planes;
+                c.grid = (int)one;
+                return c;
+            }
+        }
         for (int nz = 1; nz <= p->N / 64 && resident > 0; nz++) {
             const long long tiles = cols * nz;
             const int planes = (p->N + nz - 1) / nz;  // nz chunks of near-equal length
@@ -501,6 +520,29 @@ ce_launch default_launch(const ce_params *p, int cus)
             const ce_launch r{CE_KERNEL_TILED3D, v, l, bs, z, 0};
             if (resident_kernel(p, r, false, false)) return r;
         }
+    }
+    // Medium lattices: all tiles resident at once, two to a compute unit, two
+    // and a half of the 256-site ones where three fit (us a step, and with the
+    // rule below: 192^3 x 2 fields 57 and 63, FP64 108 and 117; 224^3 x 2 112
+    // and 122; 256^3 x 2 115 and 120, FP64 229 and 283, one field 60 and 69;
+    // 288^3 x 2 210 and 215; three tiles a unit were 4% behind two at 192^3,
+    // one 41%).  Chunks of at most 64 planes: with 88, 352^3 x 2 took 399 us
+    // against 362.
+    for (int a = 0; a < 3; a++) {
+        const int v = shapes[a][0], l = shapes[a][1], bs = shapes[a][2];
+        if (!tiled_fits(3, p->N, v, l, bs, p->N)) continue;
+        const int fit = tiled_resident_blocks(p->model, p->precision, p->nfields, v, l, bs);
+        if (fit < 2) break;
+        const long long cols = tiled_tiles(p->N, v, l, bs, p->N);
+        const int nz = (int)((l == 64 && fit >= 3 ? 5LL * cus / 2 : 2LL * cus) / cols);
+        if (nz < 4 || p->N / nz < 8 || p->N > 64 * nz) break;
+        c.kernel = CE_KERNEL_TILED3D;
+        c.sites_per_thread = v;
+        c.lanes_per_row = l;
+        c.block = bs;
+        c.planes = (p->N + nz - 1) / nz;
+        c.grid = 0;
+        return c;
     }
     if (p->N >= 64) {
         // Medium lattices (64^3 .. 256^3 and the like): one tile per compute
