@@ -272,7 +272,10 @@ ce_status ce_get_launch(const ce_sim *s, ce_launch *out);
  * Allowed at any time; captured step blocks are rebuilt. */
 ce_status ce_set_launch(ce_sim *s, const ce_launch *cfg);
 
-/* Steps per captured hipGraph inside ce_step (0 = plain launches).  Default 32. */
+/* Steps per captured hipGraph inside ce_step (0 = plain launches, one a step).
+ * Default 32.  Unless it is 0 or the stream is being captured, a lattice whose
+ * state fits the chip takes up to 256 steps of a call in one launch instead of
+ * a graph, with bitwise the same results. */
 ce_status ce_set_step_block(ce_sim *s, int32_t k);
 
 /* Advance nsteps steps like ce_step and return, in *ms, the time between two
@@ -369,8 +372,9 @@ ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes);
  * Batched ensembles and serving.  Every admitted lattice (a "member") keeps
  * its state on the device between step blocks; a step advances every member
  * that still has steps left with one kernel launch per class of members
- * (same precision, dimension, field count and kernel shape), so many small
- * lattices fill the GPU that one alone cannot.  Each member is computed by
+ * (same precision, dimension, field count and kernel shape; a class whose
+ * members each fit the chip takes a whole block of steps in one launch), so
+ * many small lattices fill the GPU that one alone cannot.  Each member is computed by
  * the same blocks and in the same reduction order as a lone simulation
  * launched with ce_pool_launch_for's configuration, so its results do not
  * depend on what else is in the pool (bitwise).  Member state counts against

@@ -166,7 +166,9 @@ def tune(dims: int, N: int, nfields: int, precision: int = ce.CE_FP32, steps: in
                                      background=lat.background)
             s.load(phi, phid)
             del phi, phid
-        s.set_step_block(0)
+        # no graph is captured (every timed call is shorter than a step block),
+        # and launches whose steps can stay on the chip are timed that way
+        s.set_step_block(max(steps, warmup, final_steps) + 1)
         default = s.get_launch().as_tuple()
         screen = []
         for cfg in candidates(dims, N):
@@ -223,7 +225,7 @@ def member_candidates(dims: int, N: int) -> List[Tuple[int, ...]]:
             tx, ty = v * l, b // l
             if N % tx or N % ty:
                 continue
-            z = 16
+            z = 4
             while z <= N:
                 tiles = (N // tx) * (N // ty) * (N // z)
                 if N % z == 0 and tiles <= 4096:

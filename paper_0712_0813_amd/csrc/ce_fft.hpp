@@ -87,9 +87,8 @@ __device__ void lds_fft(double2 *buf, int N, int logN, int lines, const double2 
 // Elements 0..total of a block's lines from memory to LDS or back: element idx
 // goes through v = load(idx), store(idx, v), with kInFlight loads of a thread
 // under way before its first store.  (One after the other, each waits a whole
-// memory round trip: of the 78 us of the middle axis of a 256^3 spectrum, which
-// moves 270 MB, the eight trips of a block were most.)  load must take
-// any idx < total.
+// memory round trip: the middle axis of a 256^3 spectrum, which moves 270 MB,
+// takes 78 us that way and 64 this way.)  load must take any idx < total.
 template <int kThreads, int kInFlight, typename Load, typename Store>
 __device__ inline void staged(int total, Load load, Store store)
 {

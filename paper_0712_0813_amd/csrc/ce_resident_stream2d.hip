@@ -13,6 +13,11 @@
 // a site and the sums' order (rows in turn, lane tree, waves in order, blocks
 // in order) are those of the streaming pass, so a step taken here is bitwise a
 // step taken there.
+//
+// Two FP32 fields, us a step, here and with one launch a step: 256^2 4.2 and
+// 9.2, 512^2 4.7 and 11.9, 1024^2 7.7 and 17.0, 2048^2 17.7 and 36.1.
+// The small ones are the exchange (2.1 us) and the tail (0.7); 2048^2 is bound
+// by the sites' instructions at one block of four wavefronts a compute unit.
 #include "ce_resident.hpp"
 
 #ifndef CE_UNIT_MODEL

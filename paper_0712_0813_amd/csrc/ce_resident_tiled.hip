@@ -1,5 +1,6 @@
 // Resident form of the tiled 3-D pass: many steps in one launch of a lattice
-// whose tiles (VEC LPR x BS/LPR sites by ZP planes) are at most kSyncRows.  See ce_resident.hpp for the exchange between blocks.
+// whose tiles (VEC LPR x BS/LPR sites by ZP planes) are at most kSyncRows.  See
+// ce_resident.hpp for the exchange between blocks.
 //
 // A block owns one tile; a thread owns the VEC sites of its (x, y) place in every
 // plane of it.  d stays in LDS, where neighbours read it, p in registers (both
@@ -13,6 +14,11 @@
 // fields: 13.1 us a step before, 5 us of it loading the halo).  The arithmetic of a site and the sums' order (the planes in
 // turn, lane tree, waves in order, tile rows in order) are those of the tiled
 // pass, so a step taken here is bitwise a step taken there.
+//
+// Two FP32 fields, us a step, here and with one launch a step: 64^3 4.9 and
+// 13.4, 96^3 8.1 and 19.4, 128^3 10.5 and 29.3.  Of 10.5, the sites take 6.9 (bound by
+// their instructions, as many as two wavefronts a SIMD can issue), exchange and
+// tail the rest.
 #include "ce_resident.hpp"
 
 #ifndef CE_UNIT_MODEL
