@@ -373,7 +373,8 @@ ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes);
  * its state on the device between step blocks; a step advances every member
  * that still has steps left with one kernel launch per class of members
  * (same precision, dimension, field count and kernel shape; a class whose
- * members each fit the chip takes a whole block of steps in one launch), so
+ * members each fit the chip takes a whole block of steps in one launch, as
+ * long as one thread makes the pool's admissions and runs its blocks), so
  * many small lattices fill the GPU that one alone cannot.  Each member is computed by
  * the same blocks and in the same reduction order as a lone simulation
  * launched with ce_pool_launch_for's configuration, so its results do not

@@ -275,6 +275,7 @@ const void *resident_kernel(const ce_params *p, const ce_launch &c, bool ragged,
 void plan_resident(ce_sim *s)
 {
     s->resident = ce_sim::Resident{};
+    s->resident_planned = true;
     const Lattice &lat = s->lat;
     ce_sim::Resident r;
     if (lat.kind == kDirect) {
@@ -318,7 +319,9 @@ void plan_resident(ce_sim *s)
 // Validate cfg for the lattice and fill the kernel-facing fields of lat.
 ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
 {
+    // planned by the first call that steps: pool members never do
     s->resident = ce_sim::Resident{};
+    s->resident_planned = false;
     Lattice &lat = s->lat;
     if (cfg.grid < 0 || cfg.grid > kMaxBlocks) return fail(CE_EINVAL, "grid must be 0..%d", kMaxBlocks);
     if (cfg.kernel == CE_KERNEL_DIRECT) {
@@ -405,14 +408,12 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg)
         // the shape is fixed: report it whatever the caller passed
         s->launch = ce_launch{CE_KERNEL_STREAM2D, 4, 64, kBlock, cfg.planes, cfg.grid};
         drop_graphs(s);
-        plan_resident(s);
         return CE_OK;
     } else {
         return fail(CE_EINVAL, "unknown kernel %d", cfg.kernel);
     }
     s->launch = cfg;
     drop_graphs(s);
-    plan_resident(s);
     return CE_OK;
 }
 
@@ -924,10 +925,12 @@ ce_status ce_step(ce_sim *s, int64_t nsteps)
     // A resident pass takes the steps of a call where they are enough to pay
     // for its launch.  Plain launches (step block 0) and captured streams take
     // the steps one by one; the results are the same.
-    if (s->resident.kernel && s->step_block > 0 && left >= s->resident.min_steps) {
+    if (s->step_block > 0 && left > 1 && (!s->resident_planned || s->resident.kernel)) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         CE_HIP(hipStreamIsCapturing(s->stream, &cap));
-        while (cap == hipStreamCaptureStatusNone && left >= s->resident.min_steps) {
+        const bool free = cap == hipStreamCaptureStatusNone;
+        if (free && !s->resident_planned) plan_resident(s);
+        while (free && s->resident.kernel && left >= s->resident.min_steps) {
             int n = (int)std::min<long long>(left, kResidentSteps);
             CE_HIP(launch_resident(s, n));
             left -= n;

@@ -8,6 +8,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -123,9 +124,27 @@ struct ce_pool {
     std::condition_variable idle;
     int admitting = 0;
     bool closing = false;
+    // Members are admitted, or blocks run, from more threads than one.  Such
+    // pools take no resident launches: a server whose admission threads worked
+    // beside them ended in a host segmentation fault in its first seconds (the
+    // cause was not found: with the HIP calls replaced by stand-ins the same
+    // traffic is clean under the address and thread sanitizers).  The batched
+    // launches they take instead give bitwise the same results.
+    std::thread::id home;
+    bool shared = false;
 };
 
 namespace {
+
+// Called with pl->mu held by every call that admits or runs a block.
+void note_thread(ce_pool *pl)
+{
+    const std::thread::id me = std::this_thread::get_id();
+    if (pl->home == std::thread::id()) pl->home = me;
+    if (pl->shared || pl->home == me) return;
+    pl->shared = true;
+    pl->dirty = true;   // classes planned as resident so far are planned again
+}
 
 // The configuration members use: the tiled kernel (widest tile that fits,
 // at most 64 planes per tile, more when needed to stay within the partial
@@ -313,7 +332,7 @@ ce_status rebuild(ce_pool *pl)
         long long g = std::min<long long>(total, (long long)per * cus);
         if (g >= 8) g = g / 8 * 8;
         t.grid = (int)g;
-        plan_resident_class(t, cus, by_class.size() == 1);
+        if (!pl->shared) plan_resident_class(t, cus, by_class.size() == 1);
     }
     {
         const ce_status st = ensure_lanes(pl);
@@ -511,6 +530,7 @@ static ce_status admit(ce_pool *pl, const ce_params *p, const ce_launch *cfg, co
         // idle load stream
         std::lock_guard<std::mutex> g(pl->mu);
         if (pl->closing) return fail(CE_ESTATE, "the pool is being destroyed");
+        note_thread(pl);
         if (bytes > pl->budget)
             return fail(CE_EINVAL, "admission needs %zu bytes, more than the pool's whole budget of %zu", bytes,
                         pl->budget);
@@ -681,6 +701,7 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
         if (st != CE_OK) return st;
     }
     std::lock_guard<std::mutex> g(pl->mu);
+    note_thread(pl);
     if (pl->dirty) {
         ce_status st = rebuild(pl);
         if (st != CE_OK) return st;

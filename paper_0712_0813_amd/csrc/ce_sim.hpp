@@ -77,6 +77,7 @@ struct ce_sim {
         const void *kernel = nullptr;
         int blocks = 0, threads = 0, min_steps = 0;
     } resident;
+    bool resident_planned = false;   // for the launch as it is now
 };
 
 namespace ce {
