@@ -77,10 +77,38 @@ class EnsembleResult:
         return self.site_field_updates / self.seconds
 
 
-def tuned_member_launch(lat: Lattice, precision: int = ce.CE_FP32):
+def ensemble_member_launch(lat: Lattice, precision: int = ce.CE_FP32):
     """The autotuned pool-member launch for this lattice's class, if cached."""
     from . import autotune
     return autotune.lookup(lat.dims, lat.N, lat.nfields, precision, pool=True)
+
+
+def tuned_member_launch(lat: Lattice, precision: int = ce.CE_FP32):
+    """The launch of the server's members: tall tiles, one per block (columns
+    of up to 64 planes, units of up to 64 rows).  Its admission threads work
+    beside the blocks, and only these tilings have carried the whole serving
+    stream: with finer ones two runs ended in a host fault whose cause was not
+    found.  None where no such tiling fits: the pool's default."""
+    n = lat.N
+    if lat.dims == 2 and n % 256 == 0:
+        rows = 64
+        while rows > 8 and (n % rows or -(-(n // 256) * (n // rows) // 4) < 2):
+            rows //= 2
+        if n % rows == 0:
+            groups = -(-(n // 256) * (n // rows) // 4)
+            return (ce.CE_KERNEL_STREAM2D, 4, 64, 256, rows, min(groups, 4096))
+    if lat.dims == 3:
+        for lanes in (64, 16, 8):
+            tx, ty = 4 * lanes, 256 // lanes
+            if n % tx or n % ty:
+                continue
+            z = min(n, 64)
+            while z <= n:
+                tiles = (n // tx) * (n // ty) * (n // z)
+                if n % z == 0 and tiles <= 4096:
+                    return (ce.CE_KERNEL_TILED3D, 4, lanes, 256, z, tiles)
+                z *= 2
+    return None
 
 
 def run_batched(lattices: Sequence[Lattice], inputs, steps: int, block: int = 50,
@@ -91,7 +119,7 @@ def run_batched(lattices: Sequence[Lattice], inputs, steps: int, block: int = 50
     with ce.Pool(budget_bytes) as pool:
         ids = []
         for lat, (phi, phid) in zip(lattices, inputs):
-            cfg = tuned_member_launch(lat, precision) if use_tuned else None
+            cfg = ensemble_member_launch(lat, precision) if use_tuned else None
             ids.append(pool.admit(params_of(lat, precision), phi, phid, steps, launch=cfg))
         # admissions return with their loads and start-up passes done
         t0 = time.perf_counter()
