@@ -50,7 +50,7 @@ typedef enum {
     CE_OK = 0,
     CE_EINVAL = -1,      /* bad argument or parameter set */
     CE_ENOMEM = -2,      /* device or host allocation failed / arena too small */
-    CE_EDEVICE = -3,     /* a HIP call failed */
+    CE_EDEVICE = -3,     /* a HIP call failed, or a launch lost part of its blocks */
     CE_ESTATE = -4,      /* call not valid in the current state (e.g. step before load) */
     CE_ENONFINITE = -5,  /* a volume sum became NaN/Inf; state kept, step reported */
     CE_EBUSY = -6        /* pool admission refused: over the memory budget */
@@ -278,6 +278,14 @@ ce_status ce_set_launch(ce_sim *s, const ce_launch *cfg);
  * a graph, with bitwise the same results. */
 ce_status ce_set_step_block(ce_sim *s, int32_t k);
 
+/* Such a launch starts when all its blocks run.  Where other work holds the GPU
+ * (a long kernel of another stream, another process), it waits `ms` for that
+ * (default 200; 0: never starts), then leaves the state as it was; the next
+ * call that waits for the simulation takes the steps by plain launches, with
+ * the same results, and later steps are plain launches too until the launch
+ * configuration is set. */
+ce_status ce_set_wait_limit(ce_sim *s, double ms);
+
 /* Advance nsteps steps like ce_step and return, in *ms, the time between two
  * HIP events recorded on the simulation's stream around them (synchronises). */
 ce_status ce_time_steps(ce_sim *s, int64_t nsteps, float *ms);
@@ -455,6 +463,10 @@ ce_status ce_pool_poll(ce_pool *pl, int64_t job_id, int32_t *done, ce_energy *ou
  * (0: pause it; negative: no limit, the default).  Its results do not
  * change; only when its steps run. */
 ce_status ce_pool_set_quota(ce_pool *pl, int64_t job_id, int64_t steps_per_block);
+
+/* ce_set_wait_limit for the pool's blocks; a pool whose launches could not
+ * start takes batched launches from then on, with the same results. */
+ce_status ce_pool_set_wait_limit(ce_pool *pl, double ms);
 
 /* Steps of the member not yet enqueued by ce_pool_run_block (no waiting). */
 ce_status ce_pool_steps_left(const ce_pool *pl, int64_t job_id, int64_t *left);

@@ -153,6 +153,7 @@ SIGNATURES = {
                       ctypes.c_int),
     "ce_get_step": ([_P, ctypes.POINTER(ctypes.c_int64)], ctypes.c_int),
     "ce_set_step_block": ([_P, ctypes.c_int32], ctypes.c_int),
+    "ce_set_wait_limit": ([_P, ctypes.c_double], ctypes.c_int),
     "ce_get_launch": ([_P, ctypes.POINTER(ce_launch)], ctypes.c_int),
     "ce_set_launch": ([_P, ctypes.POINTER(ce_launch)], ctypes.c_int),
     "ce_sync": ([_P], ctypes.c_int),
@@ -179,6 +180,7 @@ SIGNATURES = {
                      ctypes.c_int),
     "ce_pool_steps_left": ([_P, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)], ctypes.c_int),
     "ce_pool_set_quota": ([_P, ctypes.c_int64, ctypes.c_int64], ctypes.c_int),
+    "ce_pool_set_wait_limit": ([_P, ctypes.c_double], ctypes.c_int),
     "ce_pool_retire": ([_P, ctypes.c_int64, _DP, _DP], ctypes.c_int),
     "ce_pool_get_info": ([_P, ctypes.POINTER(ce_pool_info)], ctypes.c_int),
     "ce_pool_member_image_bytes": ([_P, ctypes.c_int64, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
@@ -334,6 +336,10 @@ def ce_set_step_block(sim: int, k: int) -> None:
     _check(load_library().ce_set_step_block(sim, int(k)), "ce_set_step_block")
 
 
+def ce_set_wait_limit(sim: int, ms: float) -> None:
+    _check(load_library().ce_set_wait_limit(sim, float(ms)), "ce_set_wait_limit")
+
+
 def ce_get_launch(sim: int) -> ce_launch:
     out = ce_launch()
     _check(load_library().ce_get_launch(sim, ctypes.byref(out)), "ce_get_launch")
@@ -483,6 +489,10 @@ class Simulation:
     def set_step_block(self, k: int) -> None:
         ce_set_step_block(self.handle, k)
 
+    def set_wait_limit(self, ms: float) -> None:
+        """How long a launch that keeps the state on the chip waits for the GPU."""
+        ce_set_wait_limit(self.handle, ms)
+
     def get_launch(self) -> ce_launch:
         return ce_get_launch(self.handle)
 
@@ -612,6 +622,10 @@ def ce_pool_set_quota(pool: int, job_id: int, steps_per_block: int) -> None:
     _check(load_library().ce_pool_set_quota(pool, int(job_id), int(steps_per_block)), "ce_pool_set_quota")
 
 
+def ce_pool_set_wait_limit(pool: int, ms: float) -> None:
+    _check(load_library().ce_pool_set_wait_limit(pool, float(ms)), "ce_pool_set_wait_limit")
+
+
 def ce_pool_steps_left(pool: int, job_id: int) -> int:
     left = ctypes.c_int64()
     _check(load_library().ce_pool_steps_left(pool, int(job_id), ctypes.byref(left)), "ce_pool_steps_left")
@@ -705,6 +719,10 @@ class Pool:
     def set_quota(self, job_id: int, steps_per_block: int) -> None:
         """At most this many steps per block for the member (negative: no limit)."""
         ce_pool_set_quota(self.handle, job_id, steps_per_block)
+
+    def set_wait_limit(self, ms: float) -> None:
+        """How long launches that keep members on the chip wait for the GPU."""
+        ce_pool_set_wait_limit(self.handle, ms)
 
     def steps_left(self, job_id: int) -> int:
         """Steps of the member not yet enqueued (no waiting)."""

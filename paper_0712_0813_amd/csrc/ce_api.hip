@@ -30,6 +30,12 @@ Kept g_kept[kKeptBlocks];
 int g_kept_n = 0;
 size_t g_kept_bytes = 0;
 
+// Halt words: allocated together, the free ones in a list.
+std::mutex g_halt_mu;
+unsigned *g_halt = nullptr;
+unsigned *g_halt_free[kHaltWords];
+int g_halt_n = 0;
+
 Kept take_kept(int at)   // g_kept_mu held
 {
     const Kept k = g_kept[at];
@@ -93,6 +99,35 @@ void release_device_memory(void *mem, size_t bytes, int device)
     g_kept_bytes += bytes;
 }
 
+void ready_halt_words()
+{
+    std::lock_guard<std::mutex> g(g_halt_mu);
+    if (g_halt) return;
+    void *mem = nullptr;
+    if (hipHostMalloc(&mem, kHaltWords * sizeof(unsigned), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    g_halt = static_cast<unsigned *>(mem);
+    for (g_halt_n = 0; g_halt_n < kHaltWords; g_halt_n++) g_halt_free[g_halt_n] = g_halt + g_halt_n;
+}
+
+unsigned *take_halt_word()
+{
+    std::lock_guard<std::mutex> g(g_halt_mu);
+    if (g_halt_n == 0) return nullptr;
+    unsigned *w = g_halt_free[--g_halt_n];
+    __atomic_store_n(w, 0u, __ATOMIC_RELAXED);
+    return w;
+}
+
+void give_halt_word(unsigned *w)
+{
+    if (!w) return;
+    std::lock_guard<std::mutex> g(g_halt_mu);
+    g_halt_free[g_halt_n++] = w;
+}
+
 long long sites_of(const ce_params *p)
 {
     long long n = 1;
@@ -120,7 +155,7 @@ Layout layout_of(const ce_params *p)
     static_assert((1 + kTileCounters) * sizeof(unsigned int) <= kAlign, "ticket and tile counters share one line");
     off += kAlign;
     L.off_sync = off;
-    off += align_up(((size_t)2 * (2 * kMaxSums * kSyncRows + 8 * kTotalWords) + 1) * sizeof(unsigned long long));
+    off += align_up((size_t)kSyncWords * sizeof(unsigned long long));
     L.off_ring = off;
     off += align_up((size_t)kLogCap * sizeof(ce_energy));
     L.off_maxabs = off;
@@ -234,16 +269,55 @@ constexpr int kResidentSteps = 256;
 hipError_t launch_resident(ce_sim *s, int steps)
 {
     int src = s->cur;
-    void *args[] = {&s->lat, &src, &steps};
+    Start start{++s->launches, s->wait, s->halt};
+    void *args[] = {&s->lat, &src, &steps, &start};
     const dim3 grid(s->resident.blocks), block(s->resident.threads);
     // a single block waits for nobody
     const hipError_t e = s->resident.blocks > 1
                              ? hipLaunchCooperativeKernel(s->resident.kernel, grid, block, args, 0, s->stream)
                              : hipLaunchKernel(s->resident.kernel, grid, block, args, 0, s->stream);
     if (e != hipSuccess) return e;
+    s->unsettled = true;
     s->cur ^= steps & 1;
     s->step += steps;
     return hipSuccess;
+}
+
+ce_status take_missing_steps(ce_sim *s, const long long *left)
+{
+    Scalars sc;
+    CE_HIP(hipMemcpyAsync(&sc, s->lat.sc, sizeof(sc), hipMemcpyDeviceToHost, s->stream));
+    CE_HIP(hipStreamSynchronize(s->stream));
+    if (sc.halted == kRuns) return CE_OK;
+    if (sc.halted != kNotStarted)
+        return fail(CE_EDEVICE, "a resident launch lost its blocks' sums by step %lld: the state is lost", sc.step);
+    const long long missing = s->step - sc.step;
+    if (missing < 0) return fail(CE_EDEVICE, "halted at step %lld, ahead of step %lld", sc.step, s->step);
+    // the state is where it was, in the buffer of its own step; the tile
+    // counters may have been taken from
+    const int still = kRuns, from = s->cur ^ (int)(missing & 1);
+    CE_HIP(hipMemcpyAsync(&s->lat.sc->halted, &still, sizeof(still), hipMemcpyHostToDevice, s->stream));
+    CE_HIP(hipMemsetAsync(s->lat.ticket, 0, kAlign, s->stream));
+    for (long long k = 0; k < missing; k++)
+        CE_HIP(launch_pass(s->lat, s->p.precision, (from + (int)(k & 1)) & 1, kStep, s->stream));
+    if (left) {
+        CE_HIP(hipMemcpyAsync(&s->lat.sc->cur, &s->cur, sizeof(int), hipMemcpyHostToDevice, s->stream));
+        CE_HIP(hipMemcpyAsync(&s->lat.sc->remaining, left, sizeof(*left), hipMemcpyHostToDevice, s->stream));
+    }
+    CE_HIP(hipStreamSynchronize(s->stream));
+    return CE_OK;
+}
+
+ce_status settle(ce_sim *s)
+{
+    s->unsettled = false;
+    if (!halt_seen(s)) return CE_OK;
+    // plain launches from now on: other work holds the units
+    s->resident = ce_sim::Resident{};
+    s->resident_planned = true;
+    const ce_status st = take_missing_steps(s, nullptr);
+    if (st == CE_OK) __atomic_store_n(s->halt, 0u, __ATOMIC_RELAXED);
+    return st;
 }
 
 ce_status device_cus(int *cus)
@@ -300,6 +374,8 @@ void plan_resident(ce_sim *s)
         r.threads = kBlock + 64;
     }
     if (!r.kernel) return;
+    if (!s->halt) s->halt = take_halt_word();
+    if (!s->halt) return;
     // the fewest steps worth a launch: a cooperative one costs about 22 us
     // (32^3: 4 steps 36 us plain, 40 resident, 6 steps 54 and 48; 64^3: 2 steps
     // 27 and 32, 3 steps 40 and 37), a single block's 3 (1-D 1024: 2 steps 10.9
@@ -731,6 +807,7 @@ ce_status ce_create(const ce_params *p, ce_sim **out)
     lat.sync = reinterpret_cast<unsigned long long *>(s->base + L.off_sync);
     lat.ring = reinterpret_cast<ce_energy *>(s->base + L.off_ring);
     lat.columns = s->base + L.off_staging;
+    ready_halt_words();
     {
         int cus = 0;
         ce_status st2 = device_cus(&cus);
@@ -916,6 +993,14 @@ ce_status ce_set_step_block(ce_sim *s, int32_t k)
     return CE_OK;
 }
 
+ce_status ce_set_wait_limit(ce_sim *s, double ms)
+{
+    if (!s) return fail(CE_EINVAL, "sim is NULL");
+    if (!(ms >= 0.0) || ms > 1e6) return fail(CE_EINVAL, "wait limit must be 0..1e6 ms");
+    s->wait = (unsigned long long)(ms * (double)kTicksPerMs);
+    return CE_OK;
+}
+
 ce_status ce_step(ce_sim *s, int64_t nsteps)
 {
     if (!s) return fail(CE_EINVAL, "sim is NULL");
@@ -973,6 +1058,7 @@ ce_status ce_time_steps(ce_sim *s, int64_t nsteps, float *ms)
         if (st == CE_OK) err = hipEventRecord(e1, s->stream);
         if (st == CE_OK && err == hipSuccess) err = hipEventSynchronize(e1);
         if (st == CE_OK && err == hipSuccess) err = hipEventElapsedTime(ms, e0, e1);
+        if (st == CE_OK && err == hipSuccess) st = settle(s);
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -985,7 +1071,7 @@ ce_status ce_sync(ce_sim *s)
 {
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     CE_HIP(hipStreamSynchronize(s->stream));
-    return CE_OK;
+    return settle(s);
 }
 
 ce_status ce_get_step(const ce_sim *s, int64_t *step)
@@ -1000,9 +1086,15 @@ ce_status ce_energies(ce_sim *s, ce_energy *out)
     if (!s || !out) return fail(CE_EINVAL, "NULL argument");
     if (!s->started) return fail(CE_ESTATE, "no diagnostics before every field is loaded");
     CE_HIP(hipStreamSynchronize(s->stream));
+    {
+        const ce_status st = settle(s);
+        if (st != CE_OK) return st;
+    }
     CE_HIP(hipMemcpy(out, s->lat.ring + (s->step % kLogCap), sizeof(ce_energy), hipMemcpyDeviceToHost));
     Scalars sc;
     CE_HIP(hipMemcpy(&sc, s->lat.sc, sizeof(sc), hipMemcpyDeviceToHost));
+    if (sc.halted != kRuns)
+        return fail(CE_EDEVICE, "a resident launch lost its blocks' sums by step %lld: the state is lost", sc.step);
     if (out->step != s->step)
         return fail(CE_EDEVICE, "diagnostics record for step %lld holds step %lld", (long long)s->step,
                     (long long)out->step);
@@ -1018,6 +1110,10 @@ ce_status ce_energy_log(ce_sim *s, int32_t count, ce_energy *out)
     if (count < 1 || count > kLogCap || count > s->step + 1)
         return fail(CE_EINVAL, "count must be 1..min(%d, step+1)", kLogCap);
     CE_HIP(hipStreamSynchronize(s->stream));
+    {
+        const ce_status st = settle(s);
+        if (st != CE_OK) return st;
+    }
     const long long first = s->step - count + 1;
     for (int k = 0; k < count;) {
         const long long idx = (first + k) % kLogCap;
@@ -1029,10 +1125,8 @@ ce_status ce_energy_log(ce_sim *s, int32_t count, ce_energy *out)
     return CE_OK;
 }
 
-ce_status ce_read_fields(ce_sim *s, double *f, double *fdot)
+static ce_status read_fields(ce_sim *s, double *f, double *fdot)
 {
-    if (!s) return fail(CE_EINVAL, "sim is NULL");
-    if (s->loaded != (1u << s->p.nfields) - 1) return fail(CE_ESTATE, "fields not loaded");
     const long long ns = s->lat.nsites;
     const long long chunk = s->lay.staging_elems / 2;  // f and fdot share the staging block
     for (int i = 0; i < s->p.nfields; i++) {
@@ -1052,6 +1146,17 @@ ce_status ce_read_fields(ce_sim *s, double *f, double *fdot)
         }
     }
     return CE_OK;
+}
+
+ce_status ce_read_fields(ce_sim *s, double *f, double *fdot)
+{
+    if (!s) return fail(CE_EINVAL, "sim is NULL");
+    if (s->loaded != (1u << s->p.nfields) - 1) return fail(CE_ESTATE, "fields not loaded");
+    const ce_status st = read_fields(s, f, fdot);
+    if (st != CE_OK || !halt_seen(s)) return st;
+    // the steps before it had not all been taken
+    const ce_status st2 = settle(s);
+    return st2 != CE_OK ? st2 : read_fields(s, f, fdot);
 }
 
 ce_status ce_read_sites(ce_sim *s, int32_t field, int64_t count, const int64_t *sites, double *f,
@@ -1077,7 +1182,10 @@ ce_status ce_read_sites(ce_sim *s, int32_t field, int64_t count, const int64_t *
     if (f) CE_HIP(hipMemcpyAsync(f, df, (size_t)count * sizeof(double), hipMemcpyDeviceToHost, s->stream));
     if (fdot) CE_HIP(hipMemcpyAsync(fdot, dp, (size_t)count * sizeof(double), hipMemcpyDeviceToHost, s->stream));
     CE_HIP(hipStreamSynchronize(s->stream));
-    return CE_OK;
+    if (!halt_seen(s)) return CE_OK;
+    // the steps before it had not all been taken
+    const ce_status st = settle(s);
+    return st != CE_OK ? st : ce_read_sites(s, field, count, sites, f, fdot);
 }
 
 void ce_destroy(ce_sim *s)
@@ -1094,6 +1202,7 @@ void ce_destroy(ce_sim *s)
         else
             (void)hipFree(s->base);
     }
+    if (idle) give_halt_word(s->halt);   // else a launch may still write it
     delete s;
 }
 

@@ -111,6 +111,10 @@ ce_status ce_save_image(ce_sim *s, void *buf, size_t bytes)
     const size_t total = image_total(p);
     if (bytes < total) return fail(CE_EINVAL, "image buffer holds %zu bytes, %zu needed", bytes, total);
     CE_HIP(hipStreamSynchronize(s->stream));
+    {
+        const ce_status st = settle(s);
+        if (st != CE_OK) return st;
+    }
 
     ce_image_header h;
     memset(&h, 0, sizeof(h));
@@ -213,7 +217,9 @@ ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes)
         CE_HIP(hipMemcpyAsync(s->lat.p[0][i], in + off, h.field_bytes, hipMemcpyHostToDevice, s->stream));
         off += h.field_bytes;
     }
+    CE_HIP(hipMemsetAsync(s->lat.ticket, 0, kAlign, s->stream));   // launches of a halted state may have taken tiles
     CE_HIP(hipStreamSynchronize(s->stream));
+    if (s->halt) __atomic_store_n(s->halt, 0u, __ATOMIC_RELAXED);   // with the state it was about
     for (int i = 0; i < CE_MAX_FIELDS; i++) s->m_host[i] = sc.m[i];
     s->cur = 0;
     s->step = h.step;

@@ -45,7 +45,7 @@ struct Scalars {
     long long first_bad;            // first step with a non-finite sum, -1 if none
     long long remaining;            // pool members: steps still to take (0: the lattice is idle)
     int cur;                        // pool members: buffer holding the current state
-    int pad_cur;
+    int halted;                     // Halt: why the lattice stands still, 0 if it does not
     double m[kMaxFields];           // homogeneous reference of f_i at step n
     double fdot_mean[kMaxFields];   // volume mean of fdot_i^{n+1/2}
     double r[kMaxFields];           // fdot_mean rounded to the storage type
@@ -80,7 +80,7 @@ struct Lattice {
     unsigned int *ticket;  // last-block counter, then the tiled pass's tile counters; 0 between launches
     int slots;             // entries per sum in `partials` (at least kMaxBlocks)
     ce_energy *ring;       // [kLogCap]
-    unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords], the last step's tag
+    unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords], the last step's tag, blocks arrived, the launch's decision
     void *columns;         // resident passes: edge columns of the tiles or units (the staging chunk, idle during steps)
     int nblocks;           // blocks of the step launch (fixed per lattice)
     int kind;              // kDirect or kTiled3d
@@ -97,9 +97,25 @@ constexpr int kMaxBlocks = 4096;  // blocks per launch; partial-sum rows per lat
 constexpr int kRunRows = 3;      // blocks of the direct pass that one resident block takes at most
 constexpr int kSyncRows = 256;    // blocks of a resident pass at most
 constexpr int kTotalWords = 48;  // words kept for one copy of the totals (2 kMaxSums, whole lines)
+constexpr int kSyncWords = 2 * (2 * kMaxSums * kSyncRows + 8 * kTotalWords) + 3;  // words of Lattice::sync
 constexpr int kTileCounters = 8;  // the tiled pass's tile counters, one per XCD, after the ticket
 
 enum Mode { kStep = 0, kInit = 1 };
+
+// Scalars::halted.  Blocks of a resident launch wait for each other, so none
+// of them works before all of them run.  Where that does not come about in time
+// (other work holds the compute units), the launch ends with the state as it
+// was and kNotStarted; every later step leaves such a lattice alone until the
+// host, which sees the launch's halt word, has taken the missing steps by plain
+// launches.  kLost: a block that had started stopped; the sums are lost.
+enum Halt { kRuns = 0, kNotStarted = 1, kLost = 2 };
+
+// What a resident launch's blocks agree with on whether it starts.
+struct Start {
+    unsigned long long id;     // of the launch, higher than any before on these lattices
+    unsigned long long wait;   // ticks (100 MHz) to wait for the other blocks; 0: do not start
+    unsigned *halt;            // page-locked host memory: set to 1 when a lattice halts
+};
 
 // Launch one pass over `lat` reading buffer `src` and writing buffer 1-src
 // (kStep) or updating the derivative of buffer `src` in place (kInit).
@@ -133,12 +149,12 @@ template <int MODEL>
 int stream2d_batched_resident_model(const Lattice &proto, int precision);
 // Kernel of the resident direct pass (vb consecutive blocks of the direct
 // launch per block), nullptr where that is not built.  Arguments: Lattice,
-// int src, int steps; 256 vb + 64 threads.
+// int src, int steps, Start; 256 vb + 64 threads.
 template <int MODEL>
 const void *resident_direct_model(int precision, int dims, int nf, int vb);
 // The same of the tiled 3-D pass (tiles of `planes` whole planes, one per
 // block; bs + 64 threads), and of its batched form: arguments const Lattice
-// *lats, int lattices, int tiles of each, int steps.
+// *lats, int lattices, int tiles of each, int steps, Start.
 template <int MODEL>
 const void *resident_tiled_model(int precision, int nf, int vec, int lpr, int bs, int planes, bool ragged,
                                  bool batched);

@@ -132,6 +132,12 @@ struct ce_pool {
     // launches they take instead give bitwise the same results.
     std::thread::id home;
     bool shared = false;
+    // resident launches: their number, how long their blocks wait for each
+    // other, and the word they set if members halt (see Halt); a pool that has
+    // seen that takes batched launches from then on
+    unsigned long long launches = 0, wait = kStartWait;
+    unsigned *halt = nullptr;
+    bool no_resident = false;
 };
 
 namespace {
@@ -332,7 +338,7 @@ ce_status rebuild(ce_pool *pl)
         long long g = std::min<long long>(total, (long long)per * cus);
         if (g >= 8) g = g / 8 * 8;
         t.grid = (int)g;
-        if (!pl->shared) plan_resident_class(t, cus, by_class.size() == 1);
+        if (!pl->shared && !pl->no_resident && pl->halt) plan_resident_class(t, cus, by_class.size() == 1);
     }
     {
         const ce_status st = ensure_lanes(pl);
@@ -396,20 +402,19 @@ ce_status rebuild(ce_pool *pl)
     return CE_OK;
 }
 
-// k steps of a class: one resident launch, or k batched ones.
-hipError_t launch_class_steps(const ClassTable &t, hipStream_t st, int k);
-
 hipError_t launch_class(const ClassTable &t, hipStream_t st)
 {
     return launch_batched(t.d_lats, t.d_blk, (int)t.blk_lat.size(), t.grid, t.proto, t.precision, st);
 }
 
-hipError_t launch_class_steps(const ClassTable &t, hipStream_t st, int k)
+// k steps of a class: one resident launch, or k batched ones.
+hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, int k)
 {
     if (t.res_kernel && k > 1) {
         const Lattice *lats = t.d_lats;
         int n = (int)t.lats.size(), tiles = t.res_tiles;
-        void *args[] = {&lats, &n, &tiles, &k};
+        Start start{++pl->launches, pl->wait, pl->halt};
+        void *args[] = {&lats, &n, &tiles, &k, &start};
         return hipLaunchCooperativeKernel(t.res_kernel, dim3(t.res_grid), dim3(t.proto.bs + 64), args, 0, st);
     }
     for (int i = 0; i < k; i++) {
@@ -425,12 +430,12 @@ hipError_t launch_class_steps(const ClassTable &t, hipStream_t st, int k)
 hipError_t launch_block(ce_pool *pl, hipStream_t st, int k)
 {
     const int nc = (int)pl->classes.size();
-    if (nc == 1) return launch_class_steps(pl->classes[0], st, k);
+    if (nc == 1) return launch_class_steps(pl, pl->classes[0], st, k);
     const int nl = std::min(nc, ce_pool::kLanes);
     hipError_t e = hipEventRecord(pl->fork_ev, st);
     for (int l = 0; l < nl && e == hipSuccess; l++) e = hipStreamWaitEvent(pl->lanes[l], pl->fork_ev, 0);
     for (int c = 0; c < nc && e == hipSuccess; c++)
-        e = launch_class_steps(pl->classes[c], pl->lanes[pl->lane_of[c]], k);
+        e = launch_class_steps(pl, pl->classes[c], pl->lanes[pl->lane_of[c]], k);
     for (int l = 0; l < nl && e == hipSuccess; l++) {
         e = hipEventRecord(pl->join_ev[l], pl->lanes[l]);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, pl->join_ev[l], 0);
@@ -456,6 +461,33 @@ ce_status build_pool_graph(ce_pool *pl, int k, hipGraphExec_t *out)
     if (err != hipSuccess) return fail(CE_EDEVICE, "pool graph instantiate failed: %s", hipGetErrorString(err));
     *out = exec;
     return CE_OK;
+}
+
+// After a launch that left members halted: wait for what is queued and take
+// the steps those members are behind with by plain launches.  Called with
+// pl->mu held.
+ce_status settle_pool(ce_pool *pl)
+{
+    if (!pl->halt || __atomic_load_n(pl->halt, __ATOMIC_ACQUIRE) == 0) return CE_OK;
+    CE_HIP(hipStreamSynchronize(pl->stream));
+    __atomic_store_n(pl->halt, 0u, __ATOMIC_RELAXED);
+    pl->no_resident = true;
+    pl->dirty = true;
+    pl->budgets_set = true;   // the members' counts are written again before the next block
+    for (auto &kv : pl->members) {
+        // (one whose sums are lost reports it itself, see ce_pool_poll)
+        const ce_status st = take_missing_steps(kv.second.sim, &kv.second.remaining);
+        if (st != CE_OK && st != CE_EDEVICE) return st;
+    }
+    return CE_OK;
+}
+
+// The same for a caller that has waited for the blocks it asks about.
+ce_status settle_locked(ce_pool *pl)
+{
+    if (!pl->halt || __atomic_load_n(pl->halt, __ATOMIC_ACQUIRE) == 0) return CE_OK;
+    std::lock_guard<std::mutex> g(pl->mu);
+    return settle_pool(pl);
 }
 
 Member *find(ce_pool *pl, long long id)
@@ -484,11 +516,14 @@ ce_status ce_pool_create(size_t budget_bytes, void *stream, ce_pool **out)
     ce_pool *pl = new (std::nothrow) ce_pool();
     if (!pl) return fail(CE_ENOMEM, "host allocation failed");
     pl->budget = budget_bytes;
+    ready_halt_words();
+    pl->halt = take_halt_word();
     if (stream) {
         pl->stream = static_cast<hipStream_t>(stream);
     } else {
         hipError_t e = hipStreamCreateWithFlags(&pl->stream, hipStreamNonBlocking);
         if (e != hipSuccess) {
+            give_halt_word(pl->halt);
             delete pl;
             return fail(CE_EDEVICE, "stream creation failed: %s", hipGetErrorString(e));
         }
@@ -702,6 +737,10 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
     }
     std::lock_guard<std::mutex> g(pl->mu);
     note_thread(pl);
+    {
+        const ce_status st = settle_pool(pl);
+        if (st != CE_OK) return st;
+    }
     if (pl->dirty) {
         ce_status st = rebuild(pl);
         if (st != CE_OK) return st;
@@ -788,6 +827,15 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
     return CE_OK;
 }
 
+ce_status ce_pool_set_wait_limit(ce_pool *pl, double ms)
+{
+    if (!pl) return fail(CE_EINVAL, "pool is NULL");
+    if (!(ms >= 0.0) || ms > 1e6) return fail(CE_EINVAL, "wait limit must be 0..1e6 ms");
+    std::lock_guard<std::mutex> g(pl->mu);
+    pl->wait = (unsigned long long)(ms * (double)kTicksPerMs);
+    return CE_OK;
+}
+
 ce_status ce_pool_poll(ce_pool *pl, int64_t job_id, int32_t *done, ce_energy *out)
 {
     if (!pl || !done) return fail(CE_EINVAL, "NULL argument");
@@ -807,10 +855,12 @@ ce_status ce_pool_poll(ce_pool *pl, int64_t job_id, int32_t *done, ce_energy *ou
         *done = 0;
         if (!out) return CE_OK;
         CE_HIP(hipStreamSynchronize(pl->stream));
-        return ce_energies(sim, out);
+        const ce_status st = settle_locked(pl);
+        return st != CE_OK ? st : ce_energies(sim, out);
     }
     // only the block that holds its last step has to finish
     ce_status st = wait_block(pl, finish_seq);
+    if (st == CE_OK) st = settle_locked(pl);
     if (st != CE_OK) return st;
     *done = 1;
     return out ? ce_energies(sim, out) : CE_OK;
@@ -858,6 +908,10 @@ ce_status ce_pool_retire(ce_pool *pl, int64_t job_id, double *f, double *fdot)
         const ce_status st = wait_block(pl, finish_seq);
         if (st != CE_OK) return st;
     }
+    {
+        const ce_status st = settle_locked(pl);
+        if (st != CE_OK) return st;
+    }
     if (f || fdot) {
         ce_status st = ce_read_fields(sim, f, fdot);
         if (st != CE_OK) return st;
@@ -896,7 +950,8 @@ ce_status ce_pool_save_member(ce_pool *pl, int64_t job_id, void *buf, size_t byt
         const ce_status st = wait_block(pl, finish_seq);
         if (st != CE_OK) return st;
     }
-    return ce_save_image(sim, buf, bytes);
+    const ce_status st = settle_locked(pl);
+    return st != CE_OK ? st : ce_save_image(sim, buf, bytes);
 }
 
 ce_status ce_pool_member_image_bytes(const ce_pool *pl, int64_t job_id, size_t *out)
@@ -933,7 +988,7 @@ void ce_pool_destroy(ce_pool *pl)
         pl->closing = true;
         pl->idle.wait(g, [pl] { return pl->admitting == 0; });
     }
-    if (pl->stream) (void)hipStreamSynchronize(pl->stream);
+    if (!pl->stream || hipStreamSynchronize(pl->stream) == hipSuccess) give_halt_word(pl->halt);
     for (ce_pool::TableBuf &T : pl->tbuf) {
         drop_graphs(T);
         if (T.d) (void)hipFree(T.d);

@@ -32,10 +32,16 @@
 //
 // Waiting.  Blocks wait for each other, so every block of the launch must be
 // resident at once: the launch is cooperative, and the host offers it only
-// when the occupancy query says the grid fits.  Should a wait nevertheless
-// exceed kSpinLimit polls (seconds; a step takes microseconds), the block
-// takes the sums as NaN and stops waiting: the run ends and reports a
-// non-finite state instead of hanging.
+// when the occupancy query says the grid fits.  That query counts an empty GPU:
+// a long kernel of another stream or another process's grid may hold units.  So
+// the blocks check in before the first step, and only when all have (all run,
+// and none is taken off its unit before it ends) does the launch start.  When
+// they have not in Start::wait, they agree to leave, with nothing written but
+// Scalars::halted, and the host takes the steps by plain launches.  (One
+// exchange of a flag, while the state loads.)
+// A wait of a started launch is bounded as well: past kSpinLimit polls (seconds;
+// a step takes microseconds) the block takes the sums as NaN, waits no more and
+// leaves kLost in Scalars::halted, which the host reports as a device error.
 #pragma once
 
 #include "ce_device.hpp"
@@ -267,6 +273,64 @@ __device__ __forceinline__ unsigned long long *total_word(const Lattice &lat, in
     return lat.sync + (long long)2 * (2 * kMaxSums) * kSyncRows + ((tag & 1u) * kTotalCopies + c) * kTotalWords + j;
 }
 
+__device__ __forceinline__ int halted(const Lattice &lat)
+{
+    return __hip_atomic_load(&lat.sc->halted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Leave the lattice halted, for the host to see once the launch has ended.
+__device__ __forceinline__ void halt(const Lattice &lat, int why, const Start &start)
+{
+    __hip_atomic_store(&lat.sc->halted, why, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(start.halt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// What a launch's blocks made of their check-in.
+enum { kGo = 0, kLeave = 1, kLeaveAndHalt = 2 };   // the last: one block's, which halts the lattices
+
+// One thread of each of the nblk blocks that work together.  The last to arrive
+// clears the count and decides for going; a block that has waited long enough
+// decides against.  The decision word takes one value per launch, whichever
+// is first, so all blocks act alike, also those that come to run only when the
+// others have left.  `leave`: this block knows already that nothing is to run.
+__device__ __forceinline__ int check_in(const Lattice &lat, int nblk, const Start &start, bool leave)
+{
+    unsigned long long *arrived = last_tag(lat) + 1, *decision = last_tag(lat) + 2;
+    const unsigned long long go = 2 * start.id + 1, no = 2 * start.id;
+    const bool all = __hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                     (unsigned long long)(nblk - 1);
+    if (all) __hip_atomic_store(arrived, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (leave) return kLeave;
+    const unsigned long long t0 = wall_clock64();
+    unsigned long long w = __hip_atomic_load(decision, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (!all && w >> 1 != start.id && wall_clock64() - t0 < start.wait) {
+        __builtin_amdgcn_s_sleep(1);
+        w = __hip_atomic_load(decision, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const unsigned long long mine = all && start.wait > 0 ? go : no;
+    // (each failed exchange has seen another block's decision: at most two rounds)
+    while (w >> 1 != start.id)
+        if (__hip_atomic_compare_exchange_strong(decision, &w, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return mine == go ? kGo : kLeaveAndHalt;
+    return w == go ? kGo : kLeave;
+}
+
+// Whether the launch starts, the same in every thread of the block and every
+// block of the lattice; every thread calls it, once.
+__device__ __forceinline__ bool launch_starts(const Lattice &lat, int nblk, const Start &start)
+{
+    __shared__ int go;
+    if (threadIdx.x == blockDim.x - 64) {   // of the service wave, which has nothing else to do yet
+        const bool still = halted(lat) != kRuns;
+        const int r = nblk > 1 ? check_in(lat, nblk, start, still) : still ? kLeave : kGo;
+        if (r == kLeaveAndHalt) halt(lat, kNotStarted, start);
+        go = r == kGo;
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(go) != 0;
+}
+
 // One wavefront: sum q over the nblk <= kSyncRows = 256 published rows, in the
 // order of finish_pass (lane trees over 64 rows each, those in order).
 __device__ __forceinline__ double sum_rows(const Lattice &lat, int q, int nblk, unsigned tag, bool &alive)
@@ -353,7 +417,7 @@ __device__ __forceinline__ double collect_totals(const Lattice &lat, int rank, i
 // The block is the `rank`-th of the nblk that work the lattice.
 template <typename T, int NF, int GROUPS, int WAVES>
 __device__ __forceinline__ void service_wave(const Lattice &lat, int steps, int rank, int nblk, int row,
-                                             const double (*red)[kMaxSums], PassScalars<T> &next)
+                                             const double (*red)[kMaxSums], PassScalars<T> &next, const Start &start)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     __shared__ double scratch[2 * kMaxSums];
@@ -387,6 +451,7 @@ __device__ __forceinline__ void service_wave(const Lattice &lat, int steps, int 
         if (rank == 0) tail.record(lat);
         tail.advance();
     }
+    if (__ballot(!alive) != 0 && lane == 0) halt(lat, kLost, start);
     if (rank == 0) {
         tail.store(lat);
         if (lane == 0) {
@@ -399,16 +464,34 @@ __device__ __forceinline__ void service_wave(const Lattice &lat, int steps, int 
 
 // A pool's resident launch: up to k steps of each of n lattices that nblk
 // blocks work.  The grid's blocks form groups of nblk; group g takes lattices
-// g, g + groups, ... one after the other, each for all its steps.
+// g, g + groups, ... one after the other, each for all its steps.  A group
+// checks in once, by its first lattice's words; one that does not start leaves
+// those of its lattices halted that had steps to take.
 template <typename Body>
-__device__ __forceinline__ void run_members(const Lattice *lats, int n, int nblk, int k, Body body)
+__device__ __forceinline__ void run_members(const Lattice *lats, int n, int nblk, int k, const Start &start, Body body)
 {
-    const int rank = blockIdx.x % nblk, groups = gridDim.x / nblk;
-    for (int l = blockIdx.x / nblk; l < n; l += groups) {
-        const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
-        // the steps left and the buffer change only when every block of the
-        // group has published the last step, so all read the same
-        const int steps = (int)min((long long)k, lat.sc->remaining);
+    const int rank = blockIdx.x % nblk, groups = gridDim.x / nblk, first = blockIdx.x / nblk;
+    auto member = [&](int l) -> const Lattice & {
+        return *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
+    };
+    // the steps left and the buffer change only when every block of the group
+    // has published the last step, so all read the same
+    auto steps_of = [&](const Lattice &lat) {
+        return __builtin_amdgcn_readfirstlane(halted(lat) != kRuns ? 0 : (int)min((long long)k, lat.sc->remaining));
+    };
+    __shared__ int go;
+    if (threadIdx.x == blockDim.x - 64) {
+        const int r = nblk > 1 ? check_in(member(first), nblk, start, false) : kGo;
+        if (r == kLeaveAndHalt)
+            for (int l = first; l < n; l += groups)
+                if (steps_of(member(l)) > 0) halt(member(l), kNotStarted, start);
+        go = r == kGo;
+    }
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(go)) return;
+    for (int l = first; l < n; l += groups) {
+        const Lattice &lat = member(l);
+        const int steps = steps_of(lat);
         if (steps <= 0) continue;
         body(lat, lat.sc->cur, steps, rank, nblk);
         __syncthreads();   // the next lattice takes over the block's LDS

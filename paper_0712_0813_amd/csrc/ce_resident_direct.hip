@@ -26,7 +26,7 @@ namespace {
 using namespace dev;
 
 template <typename T, int D, int NF, int MODEL, int VB>
-__global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattice lat, int src, int steps)
+__global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattice lat, int src, int steps, Start start)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     constexpr int Q = kBlock * VB;
@@ -37,7 +37,8 @@ __global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattic
 
     const int t = threadIdx.x, wave = t >> 6;
     if (t >= Q) {
-        service_wave<T, NF, VB, 4>(lat, steps, blockIdx.x, gridDim.x, blockIdx.x, red, next);
+        if (launch_starts(lat, gridDim.x, start))
+            service_wave<T, NF, VB, 4>(lat, steps, blockIdx.x, gridDim.x, blockIdx.x, red, next, start);
         return;
     }
     const int N = lat.N;
@@ -125,6 +126,7 @@ __global__ __launch_bounds__(kBlock *VB + 64) void resident_direct_kernel(Lattic
         }
     };
     if (nblk > 1) load_far(src);
+    if (!launch_starts(lat, nblk, start)) return;
 
     for (int step = 0; step < steps; step++) {
         const int out = src ^ 1 ^ (step & 1);

@@ -32,8 +32,10 @@ using namespace dev;
 constexpr int kSeg = 256;   // x sites per unit
 
 // The block is the `rank`-th of the nblk that work the lattice.
-template <typename T, int NF, int MODEL, int R>
-__device__ __forceinline__ void resident_stream2d_body(const Lattice &lat, int src, int steps, int rank, int nblk)
+// CHECK: the block checks in here (a pool's has done so).
+template <typename T, int NF, int MODEL, int R, bool CHECK>
+__device__ __forceinline__ void resident_stream2d_body(const Lattice &lat, int src, int steps, int rank, int nblk,
+                                                       const Start &start)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     constexpr int WAVES = kBlock / 64;
@@ -46,7 +48,8 @@ __device__ __forceinline__ void resident_stream2d_body(const Lattice &lat, int s
     __shared__ PassScalars<T> next;
 
     if (threadIdx.x >= kBlock) {
-        service_wave<T, NF, 1, WAVES>(lat, steps, rank, nblk, rank, red, next);
+        if (!CHECK || launch_starts(lat, nblk, start))
+            service_wave<T, NF, 1, WAVES>(lat, steps, rank, nblk, rank, red, next, start);
         return;
     }
     const int N = lat.N;
@@ -123,6 +126,7 @@ __device__ __forceinline__ void resident_stream2d_body(const Lattice &lat, int s
         xd[i] = xp[i] = (T)0;
     }
     load_halo(src, false);   // no step has packed the columns yet
+    if (CHECK && !launch_starts(lat, nblk, start)) return;
 
     for (int step = 0; step < steps; step++) {
         const int out = src ^ 1 ^ (step & 1);
@@ -261,17 +265,18 @@ __device__ __forceinline__ void resident_stream2d_body(const Lattice &lat, int s
 }
 
 template <typename T, int NF, int MODEL, int R>
-__global__ __launch_bounds__(kBlock + 64) void resident_stream2d_kernel(Lattice lat, int src, int steps)
+__global__ __launch_bounds__(kBlock + 64) void resident_stream2d_kernel(Lattice lat, int src, int steps, Start start)
 {
-    resident_stream2d_body<T, NF, MODEL, R>(lat, src, steps, blockIdx.x, gridDim.x);
+    resident_stream2d_body<T, NF, MODEL, R, true>(lat, src, steps, blockIdx.x, gridDim.x, start);
 }
 
 // Up to k steps of each of n lattices; see run_members.
 template <typename T, int NF, int MODEL, int R>
-__global__ __launch_bounds__(kBlock + 64) void resident_stream2d_batched(const Lattice *lats, int n, int nblk, int k)
+__global__ __launch_bounds__(kBlock + 64) void resident_stream2d_batched(const Lattice *lats, int n, int nblk, int k,
+                                                                         Start start)
 {
-    run_members(lats, n, nblk, k, [](const Lattice &lat, int src, int steps, int rank, int blocks) {
-        resident_stream2d_body<T, NF, MODEL, R>(lat, src, steps, rank, blocks);
+    run_members(lats, n, nblk, k, start, [&](const Lattice &lat, int src, int steps, int rank, int blocks) {
+        resident_stream2d_body<T, NF, MODEL, R, false>(lat, src, steps, rank, blocks, start);
     });
 }
 

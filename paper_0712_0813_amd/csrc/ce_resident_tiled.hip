@@ -33,8 +33,10 @@ using namespace dev;
 // The block is the `rank`-th of the nblk that work the lattice.  RAGGED: a tile
 // at the end of a row or column holds vx x vy sites, and every tile zlen <= ZP
 // planes (see the tiled pass).
-template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP, bool RAGGED>
-__device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src, int steps, int rank, int nblk)
+// CHECK: the block checks in here (a pool's has done so).
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP, bool RAGGED, bool CHECK>
+__device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src, int steps, int rank, int nblk,
+                                                    const Start &start)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
     constexpr int TX = VEC * LPR, TY = BS / LPR;
@@ -55,7 +57,8 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
     const int tile = (int)xcd_item(rank, 0, nblk, nblk);
     const int t = threadIdx.x;
     if (t >= BS) {
-        service_wave<T, NF, 1, BS / 64>(lat, steps, rank, nblk, tile, red, next);
+        if (!CHECK || launch_starts(lat, nblk, start))
+            service_wave<T, NF, 1, BS / 64>(lat, steps, rank, nblk, tile, red, next, start);
         return;
     }
     const int wave = t >> 6;
@@ -150,6 +153,7 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
         }
     };
     load_halo(src, false);   // no step has packed the columns yet
+    if (CHECK && !launch_starts(lat, nblk, start)) return;
 
     for (int step = 0; step < steps; step++) {
         const int out = src ^ 1 ^ (step & 1);
@@ -302,19 +306,19 @@ constexpr int waves_wanted()
 }
 
 template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP, bool RAGGED>
-__global__ __launch_bounds__(BS + 64, (waves_wanted<T, NF, BS, ZP>())) void resident_tiled_kernel(Lattice lat, int src,
-                                                                                                int steps)
+__global__ __launch_bounds__(BS + 64, (waves_wanted<T, NF, BS, ZP>())) void
+resident_tiled_kernel(Lattice lat, int src, int steps, Start start)
 {
-    resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP, RAGGED>(lat, src, steps, blockIdx.x, gridDim.x);
+    resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP, RAGGED, true>(lat, src, steps, blockIdx.x, gridDim.x, start);
 }
 
 // Up to k steps of each of n lattices; see run_members.
 template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, int ZP>
 __global__ __launch_bounds__(BS + 64, (waves_wanted<T, NF, BS, ZP>())) void
-resident_tiled_batched(const Lattice *lats, int n, int nblk, int k)
+resident_tiled_batched(const Lattice *lats, int n, int nblk, int k, Start start)
 {
-    run_members(lats, n, nblk, k, [](const Lattice &lat, int src, int steps, int rank, int blocks) {
-        resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP, false>(lat, src, steps, rank, blocks);
+    run_members(lats, n, nblk, k, start, [&](const Lattice &lat, int src, int steps, int rank, int blocks) {
+        resident_tiled_body<T, NF, MODEL, VEC, LPR, BS, ZP, false, false>(lat, src, steps, rank, blocks, start);
     });
 }
 

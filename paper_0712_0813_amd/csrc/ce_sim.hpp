@@ -47,6 +47,22 @@ hipError_t device_memory(size_t bytes, void **out);
 void release_device_memory(void *mem, size_t bytes, int device);
 void give_back_kept_memory();
 
+// A word of page-locked memory, zero, that a resident launch writes if its
+// lattice halts (see Halt), so that the host learns of it with no copy; nullptr
+// if none is left (of kHaltWords, allocated by the process's first simulation
+// and held until it ends), and no resident pass is planned then.
+constexpr int kHaltWords = 1024;
+void ready_halt_words();
+unsigned *take_halt_word();
+void give_halt_word(unsigned *w);
+
+// Ticks of the GPU's clock (100 MHz) a resident launch waits for its blocks.
+// A launch queued behind another's blocks gets its units within that one's
+// time (at most some milliseconds of a resident launch, 7 ms of a 1024^3 pass,
+// of which a few may come first).
+constexpr unsigned long long kTicksPerMs = 100000;
+constexpr unsigned long long kStartWait = 200 * kTicksPerMs;
+
 }  // namespace host
 }  // namespace ce
 
@@ -78,6 +94,10 @@ struct ce_sim {
         int blocks = 0, threads = 0, min_steps = 0;
     } resident;
     bool resident_planned = false;   // for the launch as it is now
+    unsigned *halt = nullptr;        // set by a resident launch that left the lattice halted
+    unsigned long long launches = 0; // resident ones so far
+    bool unsettled = false;          // one has been queued since settle()
+    unsigned long long wait = ce::host::kStartWait;
 };
 
 namespace ce {
@@ -89,6 +109,15 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg);
 // the recorded field maxima and queue the start-up half step.
 ce_status start_run(ce_sim *s);
 void drop_graphs(ce_sim *s);
+// The steps that queued launches left out of a halted lattice, by plain launches
+// on its stream, which has nothing else queued; it has run when this returns.
+// left: of a pool's member, the steps it still has to be given (its scalar
+// state then says so, and in which buffer it is).
+ce_status take_missing_steps(ce_sim *s, const long long *left);
+// The same for a simulation whose stream has been waited for: nothing to do
+// unless a launch set its halt word.
+ce_status settle(ce_sim *s);
+inline bool halt_seen(const ce_sim *s) { return s->halt && __atomic_load_n(s->halt, __ATOMIC_ACQUIRE) != 0; }
 // Kernel of the resident pass of a tiled (ragged: on ragged tiles) or 2-D
 // streaming launch with one tile or group of units per block (batched: of its
 // pool form), nullptr if none.

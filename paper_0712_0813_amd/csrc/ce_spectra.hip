@@ -412,6 +412,12 @@ ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_f
     const int N = s->p.N, dims = s->p.dims;
     if (N > kMaxSpecN || (N & (N - 1)) != 0)
         return fail(CE_EINVAL, "spectra need N a power of two <= %d (got %d)", kMaxSpecN, N);
+    if (s->unsettled) {
+        // a halted state may lie in the buffers that are scratch here
+        CE_HIP(hipStreamSynchronize(s->stream));
+        const ce_status st = settle(s);
+        if (st != CE_OK) return st;
+    }
     int logN = 0;
     while ((1 << logN) < N) logN++;
     const int nb = nbins_of(dims, N);

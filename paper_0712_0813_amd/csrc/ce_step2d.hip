@@ -36,7 +36,8 @@ __device__ __forceinline__ void store_row(gptr<T> row, unsigned x, const Quad<T>
         store_quad(row, x, q);
 }
 
-template <typename T, int NF, int MODEL, int MODE>
+// LONE: of a launch of its own (batched launches leave halted lattices out).
+template <typename T, int NF, int MODEL, int MODE, bool LONE>
 __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b, int grid)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
@@ -116,6 +117,7 @@ __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b
                 rep[i] = edge ? (pin[i] + base)[edge_x] : (T)0;
             }
         }
+        if (LONE && MODE == kStep && stands_still(lat)) return;
         for (int k = 0; k < rows; k++) {
             const int y = y0 + k;
             // issue the loads of row y+2 before working on row y
@@ -207,6 +209,7 @@ __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b
         }
     }
 
+    if (LONE && MODE == kStep && stands_still(lat)) return;   // waves without a unit too
     block_sum<NQ>(acc, red);
     put_partials<NQ>(lat, red, b);
     finish_pass<T, NF, MODE>(lat, grid, grid, red);
@@ -215,7 +218,7 @@ __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b
 template <typename T, int NF, int MODEL, int MODE>
 __global__ __launch_bounds__(kBlock) void stream2d_kernel(Lattice lat, int src)
 {
-    stream2d_body<T, NF, MODEL, MODE>(lat, src, blockIdx.x, gridDim.x);
+    stream2d_body<T, NF, MODEL, MODE, true>(lat, src, blockIdx.x, gridDim.x);
 }
 
 template <typename T, int NF, int MODEL>
@@ -224,9 +227,9 @@ __global__ __launch_bounds__(kBlock) void stream2d_batched(const Lattice *lats, 
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         const int l = __builtin_amdgcn_readfirstlane(blk_lat[v]);
         const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
-        if (lat.sc->remaining <= 0) continue;
+        if (lat.sc->remaining <= 0 || lat.sc->halted) continue;
         const int src = lat.sc->cur;
-        stream2d_body<T, NF, MODEL, kStep>(lat, src, v - lat.first_block, lat.nblocks);
+        stream2d_body<T, NF, MODEL, kStep, false>(lat, src, v - lat.first_block, lat.nblocks);
     }
 }
 

@@ -289,6 +289,7 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
                 }
             }
         }
+        if (DYN && MODE == kStep && stands_still(lat)) return;   // (batched launches leave halted lattices out)
         __syncthreads();
 
         for (int k = 0; k < zlen; k++) {
@@ -391,6 +392,7 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
         }
     }
 
+    if (DYN && MODE == kStep && stands_still(lat)) return;   // blocks without a tile too
     if (!per_tile) {
         block_sum<NQ>(acc, red);
         put_partials<NQ>(lat, red, b);
@@ -414,7 +416,7 @@ tiled3d_batched(const Lattice *lats, const int *blk_lat, int total)
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         const int l = __builtin_amdgcn_readfirstlane(blk_lat[v]);
         const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
-        if (lat.sc->remaining <= 0) continue;
+        if (lat.sc->remaining <= 0 || lat.sc->halted) continue;
         const int src = lat.sc->cur;
         tiled3d_body<T, NF, MODEL, kStep, VEC, LPR, BS, false, RAGGED>(lat, src, v - lat.first_block, lat.nblocks);
     }
