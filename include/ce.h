@@ -273,9 +273,10 @@ ce_status ce_get_launch(const ce_sim *s, ce_launch *out);
 ce_status ce_set_launch(ce_sim *s, const ce_launch *cfg);
 
 /* Steps per captured hipGraph inside ce_step (0 = plain launches, one a step).
- * Default 32.  Unless it is 0 or the stream is being captured, a lattice whose
- * state fits the chip takes up to 256 steps of a call in one launch instead of
- * a graph, with bitwise the same results. */
+ * Default 32.  Unless it is 0, the stream is being captured or another thread
+ * is inside a call of this library, a lattice whose state fits the chip takes
+ * up to 256 steps of a call in one launch instead of a graph, with bitwise the
+ * same results. */
 ce_status ce_set_step_block(ce_sim *s, int32_t k);
 
 /* Such a launch starts when all its blocks run.  Where other work holds the GPU
@@ -382,8 +383,9 @@ ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes);
  * that still has steps left with one kernel launch per class of members
  * (same precision, dimension, field count and kernel shape; a class whose
  * members each fit the chip takes a whole block of steps in one launch, as
- * long as one thread makes the pool's admissions and runs its blocks), so
- * many small lattices fill the GPU that one alone cannot.  Each member is computed by
+ * long as one thread makes the pool's admissions and runs its blocks and no
+ * other thread is inside a call of this library), so many small lattices fill
+ * the GPU that one alone cannot.  Each member is computed by
  * the same blocks and in the same reduction order as a lone simulation
  * launched with ce_pool_launch_for's configuration, so its results do not
  * depend on what else is in the pool (bitwise).  Member state counts against

@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <new>
 
@@ -30,6 +31,13 @@ Kept g_kept[kKeptBlocks];
 int g_kept_n = 0;
 size_t g_kept_bytes = 0;
 
+// Threads inside the library, and the lock of a thread that has to be alone:
+// one that enters counts itself first and then waits for the lock, so a
+// holder of it that finds itself alone stays so.
+std::atomic<int> g_inside{0};
+std::mutex g_alone_mu;
+thread_local int t_depth = 0;   // calls of this thread, one within the other
+
 // Halt words: allocated together, the free ones in a list.
 std::mutex g_halt_mu;
 unsigned *g_halt = nullptr;
@@ -48,6 +56,20 @@ Kept take_kept(int at)   // g_kept_mu held
 
 namespace ce {
 namespace host {
+
+Use::Use()
+{
+    if (t_depth++ > 0) return;
+    g_inside.fetch_add(1);
+    std::lock_guard<std::mutex> wait(g_alone_mu);
+}
+
+Use::~Use()
+{
+    if (--t_depth == 0) g_inside.fetch_sub(1);
+}
+
+Alone::Alone() : lock(g_alone_mu), alone(g_inside.load() == 1) {}
 
 ce_status fail(ce_status st, const char *fmt, ...)
 {
@@ -683,6 +705,7 @@ ce_status ce_get_launch(const ce_sim *s, ce_launch *out)
 
 ce_status ce_set_launch(ce_sim *s, const ce_launch *cfg)
 {
+    const Use use;
     if (!s || !cfg) return fail(CE_EINVAL, "NULL argument");
     const ce_launch old = s->launch;
     const Lattice saved = s->lat;
@@ -709,6 +732,7 @@ ce_status ce_required_bytes(const ce_params *p, size_t *out)
 
 ce_status ce_create(const ce_params *p, ce_sim **out)
 {
+    const Use use;
     ce_status st = validate(p);
     if (st != CE_OK) return st;
     if (!out) return fail(CE_EINVAL, "out is NULL");
@@ -843,6 +867,7 @@ ce_status ce_create(const ce_params *p, ce_sim **out)
 ce_status ce_load_fields(ce_sim *s, int32_t first, int32_t count, const double *phi,
                          const double *phidot)
 {
+    const Use use;
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     if (s->started) return fail(CE_ESTATE, "fields already loaded and evolved");
     // compared without forming first + count, which could overflow
@@ -1003,6 +1028,7 @@ ce_status ce_set_wait_limit(ce_sim *s, double ms)
 
 ce_status ce_step(ce_sim *s, int64_t nsteps)
 {
+    const Use use;
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     if (nsteps < 0) return fail(CE_EINVAL, "nsteps must be >= 0");
     if (!s->started) return fail(CE_ESTATE, "load every field before stepping");
@@ -1016,6 +1042,8 @@ ce_status ce_step(ce_sim *s, int64_t nsteps)
         const bool free = cap == hipStreamCaptureStatusNone;
         if (free && !s->resident_planned) plan_resident(s);
         while (free && s->resident.kernel && left >= s->resident.min_steps) {
+            const Alone alone;
+            if (!alone && s->resident.blocks > 1) break;
             int n = (int)std::min<long long>(left, kResidentSteps);
             CE_HIP(launch_resident(s, n));
             left -= n;
@@ -1043,6 +1071,7 @@ ce_status ce_step(ce_sim *s, int64_t nsteps)
 
 ce_status ce_time_steps(ce_sim *s, int64_t nsteps, float *ms)
 {
+    const Use use;
     if (!s || !ms) return fail(CE_EINVAL, "NULL argument");
     hipEvent_t e0 = nullptr, e1 = nullptr;
     CE_HIP(hipEventCreate(&e0));
@@ -1069,6 +1098,7 @@ ce_status ce_time_steps(ce_sim *s, int64_t nsteps, float *ms)
 
 ce_status ce_sync(ce_sim *s)
 {
+    const Use use;
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     CE_HIP(hipStreamSynchronize(s->stream));
     return settle(s);
@@ -1083,6 +1113,7 @@ ce_status ce_get_step(const ce_sim *s, int64_t *step)
 
 ce_status ce_energies(ce_sim *s, ce_energy *out)
 {
+    const Use use;
     if (!s || !out) return fail(CE_EINVAL, "NULL argument");
     if (!s->started) return fail(CE_ESTATE, "no diagnostics before every field is loaded");
     CE_HIP(hipStreamSynchronize(s->stream));
@@ -1105,6 +1136,7 @@ ce_status ce_energies(ce_sim *s, ce_energy *out)
 
 ce_status ce_energy_log(ce_sim *s, int32_t count, ce_energy *out)
 {
+    const Use use;
     if (!s || !out) return fail(CE_EINVAL, "NULL argument");
     if (!s->started) return fail(CE_ESTATE, "no diagnostics before every field is loaded");
     if (count < 1 || count > kLogCap || count > s->step + 1)
@@ -1150,6 +1182,7 @@ static ce_status read_fields(ce_sim *s, double *f, double *fdot)
 
 ce_status ce_read_fields(ce_sim *s, double *f, double *fdot)
 {
+    const Use use;
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     if (s->loaded != (1u << s->p.nfields) - 1) return fail(CE_ESTATE, "fields not loaded");
     const ce_status st = read_fields(s, f, fdot);
@@ -1162,6 +1195,7 @@ ce_status ce_read_fields(ce_sim *s, double *f, double *fdot)
 ce_status ce_read_sites(ce_sim *s, int32_t field, int64_t count, const int64_t *sites, double *f,
                         double *fdot)
 {
+    const Use use;
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     if (s->loaded != (1u << s->p.nfields) - 1) return fail(CE_ESTATE, "fields not loaded");
     if (field < 0 || field >= s->p.nfields) return fail(CE_EINVAL, "field %d out of range", field);
@@ -1190,6 +1224,7 @@ ce_status ce_read_sites(ce_sim *s, int32_t field, int64_t count, const int64_t *
 
 void ce_destroy(ce_sim *s)
 {
+    const Use use;
     if (!s) return;
     // memory is kept only if everything that used it is known to have ended
     const bool idle = s->stream && hipStreamSynchronize(s->stream) == hipSuccess;

@@ -105,6 +105,7 @@ ce_status ce_image_bytes(const ce_sim *s, size_t *out)
 
 ce_status ce_save_image(ce_sim *s, void *buf, size_t bytes)
 {
+    const Use use;
     if (!s || !buf) return fail(CE_EINVAL, "NULL argument");
     if (!s->started) return fail(CE_ESTATE, "no grid image before every field is loaded");
     const ce_params &p = s->p;
@@ -176,6 +177,7 @@ ce_status ce_image_params(const void *buf, size_t bytes, ce_params *out)
 
 ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes)
 {
+    const Use use;
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     ce_image_header h;
     ce_params p;

@@ -502,11 +502,13 @@ extern "C" {
 
 ce_status ce_generate_fields(ce_sim *s, const ce_init_spec *spec)
 {
+    const Use use;
     return generate(s, spec, false);
 }
 
 ce_status ce_generate_fields_noalloc(ce_sim *s, const ce_init_spec *spec)
 {
+    const Use use;
     return generate(s, spec, true);
 }
 

@@ -89,6 +89,7 @@ struct Lattice {
     int bs;                // tiled: threads per block
     int ragged;            // tiled: tiles at the ends of rows and columns are cut short
     int zc;                // tiled: planes streamed per tile; 2-D streaming: rows per unit
+    int per_group;         // 2-D streaming, batched: sums per group of units, as when each has its block
     int first_block;       // batched launches: this lattice's first block
 };
 

@@ -129,9 +129,13 @@ struct ce_pool {
     // beside them ended in a host segmentation fault in its first seconds (the
     // cause was not found: with the HIP calls replaced by stand-ins the same
     // traffic is clean under the address and thread sanitizers).  The batched
-    // launches they take instead give bitwise the same results.
+    // launches they take instead give bitwise the same results.  Another such
+    // fault came with batched launches alone, of finely tiled members; so the
+    // members of these pools get tall blocks (see tall_blocks), as the server's
+    // that never faulted have.
     std::thread::id home;
     bool shared = false;
+    long long resident_seq = -1;   // last block with a resident launch
     // resident launches: their number, how long their blocks wait for each
     // other, and the word they set if members halt (see Halt); a pool that has
     // seen that takes batched launches from then on
@@ -142,14 +146,38 @@ struct ce_pool {
 
 namespace {
 
-// Called with pl->mu held by every call that admits or runs a block.
-void note_thread(ce_pool *pl)
+ce_status wait_block(ce_pool *pl, long long s);
+
+// Called with pl->mu held by every call that admits or runs a block.  The first
+// call of a second thread waits until no resident launch is in flight.
+ce_status note_thread(ce_pool *pl)
 {
     const std::thread::id me = std::this_thread::get_id();
     if (pl->home == std::thread::id()) pl->home = me;
-    if (pl->shared || pl->home == me) return;
+    if (pl->shared || pl->home == me) return CE_OK;
     pl->shared = true;
-    pl->dirty = true;   // classes planned as resident so far are planned again
+    pl->dirty = true;   // classes are planned again, see the rebuild
+    return wait_block(pl, pl->resident_seq);
+}
+
+// Blocks of a member in a pool that several threads use: those of the tallest
+// tiling of its tile shape, columns of up to 64 planes or units of up to 64
+// rows (two blocks at least).  Each works the tiles or groups of such a column
+// one after the other; sums are kept per tile or group, so the results are those of one
+// block each.  (us a pool step, tall blocks and one a tile: 16 x 64^3 x 2: 138
+// and 42, 256 x 64^3 x 2: 524 and 467, 16 x 1024^2 x 2: 139 and 121.)
+int tall_blocks(const Lattice &L)
+{
+    if (L.kind == kTiled3d && !L.ragged && tiled_tiles(L.N, L.vec, L.lpr, L.bs, L.zc) <= L.slots) {
+        const long long tall = tiled_tiles(L.N, L.vec, L.lpr, L.bs, std::min(L.N, 64));
+        return (int)std::min<long long>(L.nblocks, tall);
+    }
+    if (L.kind == kStream2d && stream2d_groups(L.N, L.zc) == L.nblocks) {
+        int rows = 64;
+        while (rows > 8 && stream2d_groups(L.N, rows) < 2) rows /= 2;
+        return (int)std::min<long long>(L.nblocks, stream2d_groups(L.N, rows));
+    }
+    return L.nblocks;
 }
 
 // The configuration members use: the tiled kernel (widest tile that fits,
@@ -311,6 +339,11 @@ ce_status rebuild(ce_pool *pl)
         if (m.remaining <= 0) continue;
         ClassTable &t = by_class[class_of(m.sim)];
         Lattice L = m.sim->lat;
+        if (pl->shared) {
+            const int all = L.nblocks;
+            L.nblocks = tall_blocks(L);
+            L.per_group = L.kind == kStream2d && L.nblocks < all;
+        }
         L.first_block = (int)t.blk_lat.size();
         if (t.lats.empty()) {
             t.proto = L;
@@ -407,10 +440,12 @@ hipError_t launch_class(const ClassTable &t, hipStream_t st)
     return launch_batched(t.d_lats, t.d_blk, (int)t.blk_lat.size(), t.grid, t.proto, t.precision, st);
 }
 
-// k steps of a class: one resident launch, or k batched ones.
-hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, int k)
+// k steps of a class: one resident launch (if such are free to take), or k
+// batched ones.
+hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, int k, bool resident)
 {
-    if (t.res_kernel && k > 1) {
+    if (resident && t.res_kernel && k > 1) {
+        pl->resident_seq = pl->seq;
         const Lattice *lats = t.d_lats;
         int n = (int)t.lats.size(), tiles = t.res_tiles;
         Start start{++pl->launches, pl->wait, pl->halt};
@@ -427,15 +462,15 @@ hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, 
 // k steps of every class, ordered after the work already on `st` and ahead of
 // what follows it.  One class runs its chain on `st`; several fork onto the
 // lanes, each lane running the chains of its classes, and join again.
-hipError_t launch_block(ce_pool *pl, hipStream_t st, int k)
+hipError_t launch_block(ce_pool *pl, hipStream_t st, int k, bool resident)
 {
     const int nc = (int)pl->classes.size();
-    if (nc == 1) return launch_class_steps(pl, pl->classes[0], st, k);
+    if (nc == 1) return launch_class_steps(pl, pl->classes[0], st, k, resident);
     const int nl = std::min(nc, ce_pool::kLanes);
     hipError_t e = hipEventRecord(pl->fork_ev, st);
     for (int l = 0; l < nl && e == hipSuccess; l++) e = hipStreamWaitEvent(pl->lanes[l], pl->fork_ev, 0);
     for (int c = 0; c < nc && e == hipSuccess; c++)
-        e = launch_class_steps(pl, pl->classes[c], pl->lanes[pl->lane_of[c]], k);
+        e = launch_class_steps(pl, pl->classes[c], pl->lanes[pl->lane_of[c]], k, resident);
     for (int l = 0; l < nl && e == hipSuccess; l++) {
         e = hipEventRecord(pl->join_ev[l], pl->lanes[l]);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, pl->join_ev[l], 0);
@@ -449,7 +484,7 @@ ce_status build_pool_graph(ce_pool *pl, int k, hipGraphExec_t *out)
     if (!pl->cap_stream) CE_HIP(hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking));
     hipGraph_t g = nullptr;
     CE_HIP(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeRelaxed));
-    hipError_t err = launch_block(pl, pl->cap_stream, k);
+    hipError_t err = launch_block(pl, pl->cap_stream, k, false);
     const hipError_t e2 = hipStreamEndCapture(pl->cap_stream, &g);
     if (err != hipSuccess || e2 != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -511,6 +546,7 @@ ce_status ce_pool_launch_for(const ce_params *p, ce_launch *out)
 
 ce_status ce_pool_create(size_t budget_bytes, void *stream, ce_pool **out)
 {
+    const Use use;
     if (!out) return fail(CE_EINVAL, "out is NULL");
     *out = nullptr;
     ce_pool *pl = new (std::nothrow) ce_pool();
@@ -549,6 +585,7 @@ struct Source {
 static ce_status admit(ce_pool *pl, const ce_params *p, const ce_launch *cfg, const Source &src, int64_t nsteps,
                 int64_t *job_id)
 {
+    const Use use;
     if (!pl || !p || !job_id) return fail(CE_EINVAL, "NULL argument");
     if (nsteps < 0) return fail(CE_EINVAL, "nsteps must be >= 0");
     if (cfg && cfg->grid == 0) return fail(CE_EINVAL, "pool members need an explicit grid");
@@ -565,7 +602,8 @@ static ce_status admit(ce_pool *pl, const ce_params *p, const ce_launch *cfg, co
         // idle load stream
         std::lock_guard<std::mutex> g(pl->mu);
         if (pl->closing) return fail(CE_ESTATE, "the pool is being destroyed");
-        note_thread(pl);
+        st = note_thread(pl);
+        if (st != CE_OK) return st;
         if (bytes > pl->budget)
             return fail(CE_EINVAL, "admission needs %zu bytes, more than the pool's whole budget of %zu", bytes,
                         pl->budget);
@@ -709,6 +747,7 @@ ce_status ce_pool_admit_image(ce_pool *pl, const void *image, size_t bytes, int6
 
 ce_status ce_pool_set_member_launch(ce_pool *pl, int64_t job_id, const ce_launch *cfg)
 {
+    const Use use;
     if (!pl || !cfg) return fail(CE_EINVAL, "NULL argument");
     std::lock_guard<std::mutex> g(pl->mu);
     Member *m = find(pl, job_id);
@@ -723,6 +762,7 @@ ce_status ce_pool_set_member_launch(ce_pool *pl, int64_t job_id, const ce_launch
 
 ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
 {
+    const Use use;
     if (!pl) return fail(CE_EINVAL, "pool is NULL");
     if (k < 0 || k > 4096) return fail(CE_EINVAL, "k must be 0..4096");
     if (k == 0) return CE_OK;
@@ -736,9 +776,9 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
         if (st != CE_OK) return st;
     }
     std::lock_guard<std::mutex> g(pl->mu);
-    note_thread(pl);
     {
-        const ce_status st = settle_pool(pl);
+        ce_status st = note_thread(pl);
+        if (st == CE_OK) st = settle_pool(pl);
         if (st != CE_OK) return st;
     }
     if (pl->dirty) {
@@ -800,10 +840,14 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
             if (build_pool_graph(pl, k, &g) == CE_OK) graph = T.graphs.emplace(k, g).first->second;
         }
     }
-    if (graph)
+    if (graph) {
         CE_HIP(hipGraphLaunch(graph, pl->stream));
-    else
-        CE_HIP(launch_block(pl, pl->stream, k));
+    } else if (resident) {
+        const Alone alone;
+        CE_HIP(launch_block(pl, pl->stream, k, (bool)alone));
+    } else {
+        CE_HIP(launch_block(pl, pl->stream, k, false));
+    }
     const long long s = pl->seq++;
     CE_HIP(hipEventRecord(pl->block_ev[s % ce_pool::kEvRing], pl->stream));
     T.last_seq = s;
@@ -838,6 +882,7 @@ ce_status ce_pool_set_wait_limit(ce_pool *pl, double ms)
 
 ce_status ce_pool_poll(ce_pool *pl, int64_t job_id, int32_t *done, ce_energy *out)
 {
+    const Use use;
     if (!pl || !done) return fail(CE_EINVAL, "NULL argument");
     ce_sim *sim = nullptr;
     long long remaining = 0, finish_seq = -1;
@@ -888,6 +933,7 @@ ce_status ce_pool_steps_left(const ce_pool *pl, int64_t job_id, int64_t *left)
 
 ce_status ce_pool_retire(ce_pool *pl, int64_t job_id, double *f, double *fdot)
 {
+    const Use use;
     if (!pl) return fail(CE_EINVAL, "pool is NULL");
     ce_sim *sim = nullptr;
     long long remaining = 0, finish_seq = -1;
@@ -931,6 +977,7 @@ ce_status ce_pool_retire(ce_pool *pl, int64_t job_id, double *f, double *fdot)
 
 ce_status ce_pool_save_member(ce_pool *pl, int64_t job_id, void *buf, size_t bytes)
 {
+    const Use use;
     if (!pl) return fail(CE_EINVAL, "pool is NULL");
     ce_sim *sim = nullptr;
     long long remaining = 0, finish_seq = -1;
@@ -980,6 +1027,7 @@ ce_status ce_pool_get_info(const ce_pool *pl, ce_pool_info *out)
 
 void ce_pool_destroy(ce_pool *pl)
 {
+    const Use use;
     if (!pl) return;
     {
         // admissions in progress on other threads hold the pool's streams

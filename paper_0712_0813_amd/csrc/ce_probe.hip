@@ -190,6 +190,7 @@ ce_status default_grid(int32_t *grid)
 extern "C" ce_status ce_stream_copy(const void *src, void *dst, size_t bytes, int32_t streams, int32_t grid,
                                     int32_t reps, void *stream, float *ms)
 {
+    const Use use;
     if (!src || !dst || !ms) return fail(CE_EINVAL, "NULL argument");
     if (streams != 1 && streams != 2 && streams != 4) return fail(CE_EINVAL, "streams must be 1, 2 or 4");
     if (bytes == 0 || bytes % (16u * (size_t)streams)) return fail(CE_EINVAL, "bytes must be a multiple of 16 * streams");
@@ -208,6 +209,7 @@ extern "C" ce_status ce_stream_probe(int32_t kind, const void *src, void *dst, s
                                      int32_t unroll, int32_t nt, int32_t grid, int32_t reps, void *stream,
                                      float *ms)
 {
+    const Use use;
     if (!ms) return fail(CE_EINVAL, "NULL argument");
     if (kind != CE_PROBE_COPY && kind != CE_PROBE_READ && kind != CE_PROBE_WRITE)
         return fail(CE_EINVAL, "kind must be CE_PROBE_COPY, CE_PROBE_READ or CE_PROBE_WRITE");

@@ -2,6 +2,8 @@
 // single-lattice API and the batched pool.
 #pragma once
 
+#include <mutex>
+
 #include "ce_internal.hpp"
 
 namespace ce {
@@ -21,6 +23,28 @@ struct Layout {
     int nblocks;
 };
 
+
+// Every call that uses the GPU holds a Use while it runs.  Cooperative launches
+// are taken only by a thread that is alone in the library, and other threads'
+// calls wait (some 20 us) while one is: a server whose admission threads worked
+// beside such launches ended in a host fault, and what the runtime does with
+// them on several threads at once is not known.  Where other threads are in the
+// library, the steps are plain or batched launches, with the same results.
+class Use {
+public:
+    Use();
+    ~Use();
+    Use(const Use &) = delete;
+};
+class Alone {
+public:
+    Alone();   // by a thread with a Use
+    explicit operator bool() const { return alone; }
+
+private:
+    std::lock_guard<std::mutex> lock;
+    bool alone;
+};
 
 // Record a failure for ce_last_error() and return `st`.
 ce_status fail(ce_status st, const char *fmt, ...);

@@ -406,6 +406,7 @@ ce_status ce_spectrum_bins(const ce_sim *s, int32_t *nbins)
 
 ce_status ce_spectrum(ce_sim *s, int32_t field, double *power_f, double *power_fdot, double *count)
 {
+    const Use use;
     if (!s) return fail(CE_EINVAL, "sim is NULL");
     if (s->loaded != (1u << s->p.nfields) - 1) return fail(CE_ESTATE, "fields not loaded");
     if (field < 0 || field >= s->p.nfields) return fail(CE_EINVAL, "field %d out of range", field);

@@ -73,146 +73,159 @@ __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b
         const long long g = xcd_item(b, j, grid, ngroups);
         if (g < 0) break;
         const long long u = g * kWaves + wave;
-        if (u >= units) continue;
-        const int seg = (int)(u % nseg);
-        const int y0 = (int)(u / nseg) * rows;
-        const int x0 = seg * kSeg;
-        const unsigned own_x = (unsigned)(x0 + kVec * lane);
-        // the site beyond the segment edge that this lane needs, if any
-        const unsigned edge_x = left_edge ? (unsigned)((x0 + N - 1) % N) : (unsigned)((x0 + kSeg) % N);
-        const bool edge = left_edge || right_edge;
+        if (u < units) {
+            const int seg = (int)(u % nseg);
+            const int y0 = (int)(u / nseg) * rows;
+            const int x0 = seg * kSeg;
+            const unsigned own_x = (unsigned)(x0 + kVec * lane);
+            // the site beyond the segment edge that this lane needs, if any
+            const unsigned edge_x = left_edge ? (unsigned)((x0 + N - 1) % N) : (unsigned)((x0 + kSeg) % N);
+            const bool edge = left_edge || right_edge;
 
-        T dm[NF][kVec], dcur[NF][kVec], fcur[NF][kVec], ecur[NF];
-        {
-            const long long base = (long long)((y0 + N - 1) % N) * N;
-#pragma unroll
-            for (int i = 0; i < NF; i++) {
-                const Quad<T> dq = load_quad(din[i] + base, own_x);
-                const Quad<T> pq = load_quad(pin[i] + base, own_x);
-#pragma unroll
-                for (int e = 0; e < kVec; e++) dm[i][e] = nbr_drift<T, NF, MODE>(c, i, dq.v[e], pq.v[e]);
-            }
-        }
-        {
-            const long long base = (long long)y0 * N;
-#pragma unroll
-            for (int i = 0; i < NF; i++) {
-                const Quad<T> dq = load_quad(din[i] + base, own_x);
-                const Quad<T> pq = load_quad(pin[i] + base, own_x);
-#pragma unroll
-                for (int e = 0; e < kVec; e++) own_drift<T, NF, MODE>(c, i, dq.v[e], pq.v[e], fcur[i][e], dcur[i][e]);
-                ecur[i] = edge ? nbr_drift<T, NF, MODE>(c, i, (din[i] + base)[edge_x], (pin[i] + base)[edge_x]) : (T)0;
-            }
-        }
-        // stored values of row y+1, loaded one iteration ahead of their use
-        Quad<T> rd[NF], rp[NF];
-        T red[NF], rep[NF];
-        {
-            const long long base = (long long)((y0 + 1) % N) * N;
-#pragma unroll
-            for (int i = 0; i < NF; i++) {
-                rd[i] = load_quad(din[i] + base, own_x);
-                rp[i] = load_quad(pin[i] + base, own_x);
-                red[i] = edge ? (din[i] + base)[edge_x] : (T)0;
-                rep[i] = edge ? (pin[i] + base)[edge_x] : (T)0;
-            }
-        }
-        if (LONE && MODE == kStep && stands_still(lat)) return;
-        for (int k = 0; k < rows; k++) {
-            const int y = y0 + k;
-            // issue the loads of row y+2 before working on row y
-            Quad<T> qd[NF], qp[NF];
-            T qed[NF], qep[NF];
-            if (k + 1 < rows) {
-                const long long qbase = (long long)((y + 2) % N) * N;
+            T dm[NF][kVec], dcur[NF][kVec], fcur[NF][kVec], ecur[NF];
+            {
+                const long long base = (long long)((y0 + N - 1) % N) * N;
 #pragma unroll
                 for (int i = 0; i < NF; i++) {
-                    qd[i] = load_quad(din[i] + qbase, own_x);
-                    qp[i] = load_quad(pin[i] + qbase, own_x);
-                    qed[i] = edge ? (din[i] + qbase)[edge_x] : (T)0;
-                    qep[i] = edge ? (pin[i] + qbase)[edge_x] : (T)0;
+                    const Quad<T> dq = load_quad(din[i] + base, own_x);
+                    const Quad<T> pq = load_quad(pin[i] + base, own_x);
+#pragma unroll
+                    for (int e = 0; e < kVec; e++) dm[i][e] = nbr_drift<T, NF, MODE>(c, i, dq.v[e], pq.v[e]);
                 }
-            } else {
+            }
+            {
+                const long long base = (long long)y0 * N;
 #pragma unroll
                 for (int i = 0; i < NF; i++) {
-                    qd[i] = rd[i];
-                    qp[i] = rp[i];
-                    qed[i] = red[i];
-                    qep[i] = rep[i];
+                    const Quad<T> dq = load_quad(din[i] + base, own_x);
+                    const Quad<T> pq = load_quad(pin[i] + base, own_x);
+#pragma unroll
+                    for (int e = 0; e < kVec; e++) own_drift<T, NF, MODE>(c, i, dq.v[e], pq.v[e], fcur[i][e], dcur[i][e]);
+                    ecur[i] = edge ? nbr_drift<T, NF, MODE>(c, i, (din[i] + base)[edge_x], (pin[i] + base)[edge_x]) : (T)0;
                 }
             }
-            T pair[NF][kVec];
-#pragma unroll
-            for (int i = 0; i < NF; i++) {
-                T xl = lane_from_left(dcur[i][kVec - 1]);
-                T xr = lane_from_right(dcur[i][0]);
-                if (left_edge) xl = ecur[i];
-                if (right_edge) xr = ecur[i];
-#pragma unroll
-                for (int e = 0; e < kVec; e++) {
-                    const T l = e == 0 ? xl : dcur[i][e - 1];
-                    const T r = e == kVec - 1 ? xr : dcur[i][e + 1];
-                    pair[i][e] = l + r;
-                }
-            }
-            T dn1[NF][kVec], fn1[NF][kVec], en1[NF];
-#pragma unroll
-            for (int i = 0; i < NF; i++) {
-#pragma unroll
-                for (int e = 0; e < kVec; e++) own_drift<T, NF, MODE>(c, i, rd[i].v[e], rp[i].v[e], fn1[i][e], dn1[i][e]);
-                en1[i] = edge ? nbr_drift<T, NF, MODE>(c, i, red[i], rep[i]) : (T)0;
-            }
-            const long long obase = (long long)y * N;
-            T part[NQ];
-            clear_part(part);
-#pragma unroll
-            for (int e = 0; e < kVec; e++) {
-                T d1s[NF], fds[NF], lap[NF], pn[NF];
+            // stored values of row y+1, loaded one iteration ahead of their use
+            Quad<T> rd[NF], rp[NF];
+            T red[NF], rep[NF];
+            {
+                const long long base = (long long)((y0 + 1) % N) * N;
 #pragma unroll
                 for (int i = 0; i < NF; i++) {
-                    const T pr = pair[i][e] + (dn1[i][e] + dm[i][e]);
-                    lap[i] = fma_t((T)-4, dcur[i][e], pr) * c.inv_dx2;
-                    d1s[i] = dcur[i][e];
-                    fds[i] = fcur[i][e];
+                    rd[i] = load_quad(din[i] + base, own_x);
+                    rp[i] = load_quad(pin[i] + base, own_x);
+                    red[i] = edge ? (din[i] + base)[edge_x] : (T)0;
+                    rep[i] = edge ? (pin[i] + base)[edge_x] : (T)0;
                 }
-                site_update<T, NF, MODEL, MODE, NQ>(c, d1s, fds, lap, pn, part);
-#pragma unroll
-                for (int i = 0; i < NF; i++) fcur[i][e] = pn[i];
             }
-            flush_sums(part, acc);
+            if (LONE && MODE == kStep && stands_still(lat)) return;
+            for (int k = 0; k < rows; k++) {
+                const int y = y0 + k;
+                // issue the loads of row y+2 before working on row y
+                Quad<T> qd[NF], qp[NF];
+                T qed[NF], qep[NF];
+                if (k + 1 < rows) {
+                    const long long qbase = (long long)((y + 2) % N) * N;
 #pragma unroll
-            for (int i = 0; i < NF; i++) {
-                Quad<T> dq, pq;
-#pragma unroll
-                for (int e = 0; e < kVec; e++) {
-                    dq.v[e] = dcur[i][e];
-                    pq.v[e] = fcur[i][e];
-                }
-                if (MODE == kStep) {
-                    store_row(dout[i] + obase, own_x, dq);
-                    store_row(pout[i] + obase, own_x, pq);
+                    for (int i = 0; i < NF; i++) {
+                        qd[i] = load_quad(din[i] + qbase, own_x);
+                        qp[i] = load_quad(pin[i] + qbase, own_x);
+                        qed[i] = edge ? (din[i] + qbase)[edge_x] : (T)0;
+                        qep[i] = edge ? (pin[i] + qbase)[edge_x] : (T)0;
+                    }
                 } else {
-                    store_row(as_global<T>(lat.p[src][i]) + obase, own_x, pq);
+#pragma unroll
+                    for (int i = 0; i < NF; i++) {
+                        qd[i] = rd[i];
+                        qp[i] = rp[i];
+                        qed[i] = red[i];
+                        qep[i] = rep[i];
+                    }
                 }
+                T pair[NF][kVec];
+#pragma unroll
+                for (int i = 0; i < NF; i++) {
+                    T xl = lane_from_left(dcur[i][kVec - 1]);
+                    T xr = lane_from_right(dcur[i][0]);
+                    if (left_edge) xl = ecur[i];
+                    if (right_edge) xr = ecur[i];
+#pragma unroll
+                    for (int e = 0; e < kVec; e++) {
+                        const T l = e == 0 ? xl : dcur[i][e - 1];
+                        const T r = e == kVec - 1 ? xr : dcur[i][e + 1];
+                        pair[i][e] = l + r;
+                    }
+                }
+                T dn1[NF][kVec], fn1[NF][kVec], en1[NF];
+#pragma unroll
+                for (int i = 0; i < NF; i++) {
+#pragma unroll
+                    for (int e = 0; e < kVec; e++) own_drift<T, NF, MODE>(c, i, rd[i].v[e], rp[i].v[e], fn1[i][e], dn1[i][e]);
+                    en1[i] = edge ? nbr_drift<T, NF, MODE>(c, i, red[i], rep[i]) : (T)0;
+                }
+                const long long obase = (long long)y * N;
+                T part[NQ];
+                clear_part(part);
 #pragma unroll
                 for (int e = 0; e < kVec; e++) {
-                    dm[i][e] = dcur[i][e];
-                    dcur[i][e] = dn1[i][e];
-                    fcur[i][e] = fn1[i][e];
+                    T d1s[NF], fds[NF], lap[NF], pn[NF];
+#pragma unroll
+                    for (int i = 0; i < NF; i++) {
+                        const T pr = pair[i][e] + (dn1[i][e] + dm[i][e]);
+                        lap[i] = fma_t((T)-4, dcur[i][e], pr) * c.inv_dx2;
+                        d1s[i] = dcur[i][e];
+                        fds[i] = fcur[i][e];
+                    }
+                    site_update<T, NF, MODEL, MODE, NQ>(c, d1s, fds, lap, pn, part);
+#pragma unroll
+                    for (int i = 0; i < NF; i++) fcur[i][e] = pn[i];
                 }
-                ecur[i] = en1[i];
-                rd[i] = qd[i];
-                rp[i] = qp[i];
-                red[i] = qed[i];
-                rep[i] = qep[i];
+                flush_sums(part, acc);
+#pragma unroll
+                for (int i = 0; i < NF; i++) {
+                    Quad<T> dq, pq;
+#pragma unroll
+                    for (int e = 0; e < kVec; e++) {
+                        dq.v[e] = dcur[i][e];
+                        pq.v[e] = fcur[i][e];
+                    }
+                    if (MODE == kStep) {
+                        store_row(dout[i] + obase, own_x, dq);
+                        store_row(pout[i] + obase, own_x, pq);
+                    } else {
+                        store_row(as_global<T>(lat.p[src][i]) + obase, own_x, pq);
+                    }
+#pragma unroll
+                    for (int e = 0; e < kVec; e++) {
+                        dm[i][e] = dcur[i][e];
+                        dcur[i][e] = dn1[i][e];
+                        fcur[i][e] = fn1[i][e];
+                    }
+                    ecur[i] = en1[i];
+                    rd[i] = qd[i];
+                    rp[i] = qp[i];
+                    red[i] = qed[i];
+                    rep[i] = qep[i];
+                }
             }
+        }
+        if (!LONE && lat.per_group) {
+            // the group's row is that of the block that takes it when each
+            // group has one; the next group starts its sums from zero
+            block_sum<NQ>(acc, red);
+            const long long per = ngroups >> 3;
+            put_partials<NQ>(lat, red, (ngroups & 7) == 0 ? (g % per) * 8 + g / per : g);
+#pragma unroll
+            for (int k = 0; k < NQ; k++) acc[k] = 0.0;
         }
     }
 
     if (LONE && MODE == kStep && stands_still(lat)) return;   // waves without a unit too
-    block_sum<NQ>(acc, red);
-    put_partials<NQ>(lat, red, b);
-    finish_pass<T, NF, MODE>(lat, grid, grid, red);
+    const bool per_group = !LONE && lat.per_group;
+    if (!per_group) {
+        block_sum<NQ>(acc, red);
+        put_partials<NQ>(lat, red, b);
+    }
+    finish_pass<T, NF, MODE>(lat, grid, per_group ? (int)ngroups : grid, red);
 }
 
 template <typename T, int NF, int MODEL, int MODE>
