@@ -268,7 +268,8 @@ ce_status build_graph(ce_sim *s, int parity)
     CE_HIP(hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
     hipError_t err = hipSuccess;
     for (int k = 0; k < s->step_block && err == hipSuccess; k++)
-        err = launch_pass(s->lat, s->p.precision, (parity + k) & 1, kStep, s->cap_stream);
+        err = launch_pass(s->lat, s->p.precision, (parity + k) & 1, s->resident.kernel ? kGuardedStep : kStep,
+                          s->cap_stream);
     hipError_t e2 = hipStreamEndCapture(s->cap_stream, &g);
     if (err != hipSuccess || e2 != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -291,7 +292,7 @@ constexpr int kResidentSteps = 256;
 hipError_t launch_resident(ce_sim *s, int steps)
 {
     int src = s->cur;
-    Start start{++s->launches, s->wait, s->halt};
+    Start start{s->wait, s->halt};
     void *args[] = {&s->lat, &src, &steps, &start};
     const dim3 grid(s->resident.blocks), block(s->resident.threads);
     // a single block waits for nobody
@@ -305,6 +306,12 @@ hipError_t launch_resident(ce_sim *s, int steps)
     return hipSuccess;
 }
 
+hipError_t clear_arrivals(ce_sim *s)
+{
+    static const unsigned long long none = 0;
+    return hipMemcpyAsync(s->lat.sync + kArrivals, &none, sizeof(none), hipMemcpyHostToDevice, s->stream);
+}
+
 ce_status take_missing_steps(ce_sim *s, const long long *left)
 {
     Scalars sc;
@@ -315,11 +322,10 @@ ce_status take_missing_steps(ce_sim *s, const long long *left)
         return fail(CE_EDEVICE, "a resident launch lost its blocks' sums by step %lld: the state is lost", sc.step);
     const long long missing = s->step - sc.step;
     if (missing < 0) return fail(CE_EDEVICE, "halted at step %lld, ahead of step %lld", sc.step, s->step);
-    // the state is where it was, in the buffer of its own step; the tile
-    // counters may have been taken from
-    const int still = kRuns, from = s->cur ^ (int)(missing & 1);
-    CE_HIP(hipMemcpyAsync(&s->lat.sc->halted, &still, sizeof(still), hipMemcpyHostToDevice, s->stream));
-    CE_HIP(hipMemsetAsync(s->lat.ticket, 0, kAlign, s->stream));
+    CE_HIP(clear_arrivals(s));
+    // the state is where it was, in the buffer of its own step
+    const int runs = kRuns, from = s->cur ^ (int)(missing & 1);
+    CE_HIP(hipMemcpyAsync(&s->lat.sc->halted, &runs, sizeof(runs), hipMemcpyHostToDevice, s->stream));
     for (long long k = 0; k < missing; k++)
         CE_HIP(launch_pass(s->lat, s->p.precision, (from + (int)(k & 1)) & 1, kStep, s->stream));
     if (left) {
@@ -707,6 +713,16 @@ ce_status ce_set_launch(ce_sim *s, const ce_launch *cfg)
 {
     const Use use;
     if (!s || !cfg) return fail(CE_EINVAL, "NULL argument");
+    if (s->unsettled) {
+        // steps left out of a halted state are those of the launch as it is
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        CE_HIP(hipStreamIsCapturing(s->stream, &cap));
+        if (cap == hipStreamCaptureStatusNone) {
+            CE_HIP(hipStreamSynchronize(s->stream));
+            const ce_status st = settle(s);
+            if (st != CE_OK) return st;
+        }
+    }
     const ce_launch old = s->launch;
     const Lattice saved = s->lat;
     const ce_sim::Resident resident = s->resident;
@@ -1061,8 +1077,12 @@ ce_status ce_step(ce_sim *s, int64_t nsteps)
             left -= s->step_block;
         }
     }
+    // behind a resident launch that may have left the state halted
+    const Mode mode = s->unsettled ? kGuardedStep : kStep;
+    if (left > 0 && mode == kGuardedStep && !guarded_built(s->lat, s->p.precision))
+        return fail(CE_ESTATE, "launch set under capture behind steps not waited for: wait for the simulation first");
     for (; left > 0; left--) {
-        CE_HIP(launch_pass(s->lat, s->p.precision, s->cur, kStep, s->stream));
+        CE_HIP(launch_pass(s->lat, s->p.precision, s->cur, mode, s->stream));
         s->cur ^= 1;
         s->step += 1;
     }

@@ -290,16 +290,6 @@ __device__ __forceinline__ int tree_index()
     return ok ? q : -1;
 }
 
-// Whether the lattice stands still (see Halt): a step leaves it as it is.
-// Asked once the first loads are under way, and hidden from the compiler so
-// that it stays there; the answer arrives with the pass's coefficients.
-__device__ __forceinline__ bool stands_still(const Lattice &lat)
-{
-    int h = __builtin_amdgcn_readfirstlane(((const __attribute__((address_space(4))) Scalars *)lat.sc)->halted);
-    asm volatile("" : "+s"(h));
-    return h != kRuns;
-}
-
 // Sum acc[0..NQ) over the block (blockDim.x a multiple of 64, red holding
 // one row per wave); the totals land in red[0][q].  Fixed order: the lane
 // tree within a wave, then the waves in order.

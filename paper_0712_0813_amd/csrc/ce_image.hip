@@ -219,9 +219,13 @@ ce_status ce_restore_image(ce_sim *s, const void *buf, size_t bytes)
         CE_HIP(hipMemcpyAsync(s->lat.p[0][i], in + off, h.field_bytes, hipMemcpyHostToDevice, s->stream));
         off += h.field_bytes;
     }
-    CE_HIP(hipMemsetAsync(s->lat.ticket, 0, kAlign, s->stream));   // launches of a halted state may have taken tiles
     CE_HIP(hipStreamSynchronize(s->stream));
-    if (s->halt) __atomic_store_n(s->halt, 0u, __ATOMIC_RELAXED);   // with the state it was about
+    s->unsettled = false;
+    if (halt_seen(s)) {   // it was about the state that is gone
+        __atomic_store_n(s->halt, 0u, __ATOMIC_RELAXED);
+        CE_HIP(clear_arrivals(s));
+        CE_HIP(hipStreamSynchronize(s->stream));
+    }
     for (int i = 0; i < CE_MAX_FIELDS; i++) s->m_host[i] = sc.m[i];
     s->cur = 0;
     s->step = h.step;

@@ -80,7 +80,7 @@ struct Lattice {
     unsigned int *ticket;  // last-block counter, then the tiled pass's tile counters; 0 between launches
     int slots;             // entries per sum in `partials` (at least kMaxBlocks)
     ce_energy *ring;       // [kLogCap]
-    unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords], the last step's tag, blocks arrived, the launch's decision
+    unsigned long long *sync;  // resident passes: published sums [2][2 kMaxSums][kSyncRows], then totals [2][8][kTotalWords], the last step's tag, the blocks checked in
     void *columns;         // resident passes: edge columns of the tiles or units (the staging chunk, idle during steps)
     int nblocks;           // blocks of the step launch (fixed per lattice)
     int kind;              // kDirect or kTiled3d
@@ -98,10 +98,13 @@ constexpr int kMaxBlocks = 4096;  // blocks per launch; partial-sum rows per lat
 constexpr int kRunRows = 3;      // blocks of the direct pass that one resident block takes at most
 constexpr int kSyncRows = 256;    // blocks of a resident pass at most
 constexpr int kTotalWords = 48;  // words kept for one copy of the totals (2 kMaxSums, whole lines)
-constexpr int kSyncWords = 2 * (2 * kMaxSums * kSyncRows + 8 * kTotalWords) + 3;  // words of Lattice::sync
+constexpr int kTotalCopies = 8;  // of the totals
+constexpr int kLastTag = 2 * (2 * kMaxSums * kSyncRows + kTotalCopies * kTotalWords);  // Lattice::sync: the last step's tag
+constexpr int kArrivals = kLastTag + 1;   // and the blocks checked in
+constexpr int kSyncWords = kLastTag + 2;
 constexpr int kTileCounters = 8;  // the tiled pass's tile counters, one per XCD, after the ticket
 
-enum Mode { kStep = 0, kInit = 1 };
+enum Mode { kStep = 0, kInit = 1, kGuardedStep = 2 };   // the last: kStep that leaves a halted lattice alone
 
 // Scalars::halted.  Blocks of a resident launch wait for each other, so none
 // of them works before all of them run.  Where that does not come about in time
@@ -113,13 +116,13 @@ enum Halt { kRuns = 0, kNotStarted = 1, kLost = 2 };
 
 // What a resident launch's blocks agree with on whether it starts.
 struct Start {
-    unsigned long long id;     // of the launch, higher than any before on these lattices
-    unsigned long long wait;   // ticks (100 MHz) to wait for the other blocks; 0: do not start
+    unsigned long long wait;   // ticks (100 MHz) to wait for the other blocks
     unsigned *halt;            // page-locked host memory: set to 1 when a lattice halts
 };
 
 // Launch one pass over `lat` reading buffer `src` and writing buffer 1-src
-// (kStep) or updating the derivative of buffer `src` in place (kInit).
+// (kStep, kGuardedStep) or updating the derivative of buffer `src` in place
+// (kInit).
 hipError_t launch_pass(const Lattice &lat, int precision, int src, Mode mode, hipStream_t st);
 
 // Each kernel family is compiled once per model (the source built with
@@ -188,6 +191,9 @@ CE_DECLARE_MODEL_ENTRIES(kPoly)
 int pass_blocks(int dims, int N);
 // Tiled 3-D pass: whether (N, lpr, zc) fits, its tile count, and the largest
 // grid that keeps every block resident.
+// Whether launch_pass has kGuardedStep for this launch (every direct and 2-D
+// streaming one, tiled ones of the shapes a resident pass takes).
+bool guarded_built(const Lattice &lat, int precision);
 bool tiled_shape_built(int vec, int lpr, int bs);
 bool tiled_fits(int dims, int N, int vec, int lpr, int bs, int zc);
 long long tiled_tiles(int N, int vec, int lpr, int bs, int zc);

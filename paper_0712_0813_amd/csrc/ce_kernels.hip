@@ -33,8 +33,7 @@ namespace {
 using namespace dev;
 
 // Body of the direct pass: block b of the `grid` blocks this lattice gets.
-// LONE: of a launch of its own (batched launches leave halted lattices out).
-template <typename T, int D, int NF, int MODEL, int MODE, bool LONE>
+template <typename T, int D, int NF, int MODEL, int MODE>
 __device__ __forceinline__ void pass_body(const Lattice &lat, int src, int b, int grid)
 {
     constexpr int NQ = kSumsPerField * NF + 1;
@@ -121,7 +120,6 @@ __device__ __forceinline__ void pass_body(const Lattice &lat, int src, int b, in
 #pragma unroll
         for (int e = 0; e < 4; e++) site_update<T, NF, MODEL, MODE, NQ>(c, d1[e], fdot[e], lap[e], pn[e], part);
         flush_sums(part, acc);
-        if (LONE && MODE == kStep && stands_still(lat)) break;
 #pragma unroll
         for (int i = 0; i < NF; i++) {
             Quad<T> po;
@@ -140,7 +138,6 @@ __device__ __forceinline__ void pass_body(const Lattice &lat, int src, int b, in
         }
     }
 
-    if (LONE && MODE == kStep && stands_still(lat)) return;
     block_sum<NQ>(acc, red);
     put_partials<NQ>(lat, red, b);
     finish_pass<T, NF, MODE, 1, true>(lat, grid, grid, red);
@@ -149,7 +146,15 @@ __device__ __forceinline__ void pass_body(const Lattice &lat, int src, int b, in
 template <typename T, int D, int NF, int MODEL, int MODE>
 __global__ __launch_bounds__(kBlock) void pass_kernel(Lattice lat, int src)
 {
-    pass_body<T, D, NF, MODEL, MODE, true>(lat, src, blockIdx.x, gridDim.x);
+    pass_body<T, D, NF, MODEL, MODE>(lat, src, blockIdx.x, gridDim.x);
+}
+
+// A step that leaves a halted lattice as it is (see Halt).
+template <typename T, int D, int NF, int MODEL>
+__global__ __launch_bounds__(kBlock) void pass_guarded(Lattice lat, int src)
+{
+    if (lat.sc->halted) return;
+    pass_body<T, D, NF, MODEL, kStep>(lat, src, blockIdx.x, gridDim.x);
 }
 
 // Step pass over many lattices: block -> (lattice, its own block index), so
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void pass_batched(const Lattice *lats, cons
         const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
         if (lat.sc->remaining <= 0 || lat.sc->halted) continue;
         const int src = lat.sc->cur;
-        pass_body<T, D, NF, MODEL, kStep, false>(lat, src, v - lat.first_block, lat.nblocks);
+        pass_body<T, D, NF, MODEL, kStep>(lat, src, v - lat.first_block, lat.nblocks);
     }
 }
 
@@ -172,6 +177,8 @@ hipError_t launch_typed(const Lattice &lat, int src, Mode mode, hipStream_t st)
     dim3 grid(lat.nblocks), block(kBlock);
     if (mode == kStep)
         hipLaunchKernelGGL((pass_kernel<T, D, NF, MODEL, kStep>), grid, block, 0, st, lat, src);
+    else if (mode == kGuardedStep)
+        hipLaunchKernelGGL((pass_guarded<T, D, NF, MODEL>), grid, block, 0, st, lat, src);
     else
         hipLaunchKernelGGL((pass_kernel<T, D, NF, MODEL, kInit>), grid, block, 0, st, lat, src);
     return hipGetLastError();

@@ -136,10 +136,10 @@ struct ce_pool {
     std::thread::id home;
     bool shared = false;
     long long resident_seq = -1;   // last block with a resident launch
-    // resident launches: their number, how long their blocks wait for each
-    // other, and the word they set if members halt (see Halt); a pool that has
-    // seen that takes batched launches from then on
-    unsigned long long launches = 0, wait = kStartWait;
+    // resident launches: how long their blocks wait for each other, and the
+    // word they set if members halt (see Halt); a pool that has seen that takes
+    // batched launches from then on
+    unsigned long long wait = kStartWait;
     unsigned *halt = nullptr;
     bool no_resident = false;
 };
@@ -448,7 +448,7 @@ hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, 
         pl->resident_seq = pl->seq;
         const Lattice *lats = t.d_lats;
         int n = (int)t.lats.size(), tiles = t.res_tiles;
-        Start start{++pl->launches, pl->wait, pl->halt};
+        Start start{pl->wait, pl->halt};
         void *args[] = {&lats, &n, &tiles, &k, &start};
         return hipLaunchCooperativeKernel(t.res_kernel, dim3(t.res_grid), dim3(t.proto.bs + 64), args, 0, st);
     }

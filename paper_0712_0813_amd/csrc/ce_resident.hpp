@@ -37,8 +37,7 @@
 // the blocks check in before the first step, and only when all have (all run,
 // and none is taken off its unit before it ends) does the launch start.  When
 // they have not in Start::wait, they agree to leave, with nothing written but
-// Scalars::halted, and the host takes the steps by plain launches.  (One
-// exchange of a flag, while the state loads.)
+// Scalars::halted, and the host takes the steps by plain launches.
 // A wait of a started launch is bounded as well: past kSpinLimit polls (seconds;
 // a step takes microseconds) the block takes the sums as NaN, waits no more and
 // leaves kLost in Scalars::halted, which the host reports as a device error.
@@ -50,7 +49,6 @@ namespace ce {
 namespace dev {
 
 constexpr int kSpinLimit = 1 << 22;
-constexpr int kTotalCopies = 8;
 
 // Cache-policy bits of an agent-scope buffer access on gfx950: sc1.
 constexpr int kAgentPolicy = 16;
@@ -264,7 +262,7 @@ __device__ __forceinline__ void next_coef(PassCoef<T, NF> &c, const PassScalars<
 // writes it when it has every block's last step, so every block has read it.
 __device__ __forceinline__ unsigned long long *last_tag(const Lattice &lat)
 {
-    return lat.sync + (long long)2 * (2 * kMaxSums * kSyncRows + kTotalCopies * kTotalWords);
+    return lat.sync + kLastTag;
 }
 
 // Word j of copy c of the totals of step `tag`, after the rows.
@@ -285,35 +283,36 @@ __device__ __forceinline__ void halt(const Lattice &lat, int why, const Start &s
     __hip_atomic_store(start.halt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// The blocks of a launch that have checked in, and whether they were told to leave.
+__device__ __forceinline__ unsigned long long *arrivals(const Lattice &lat) { return lat.sync + kArrivals; }
+constexpr unsigned long long kNoStart = 1ull << 32;   // in the word of arrivals
+
 // What a launch's blocks made of their check-in.
 enum { kGo = 0, kLeave = 1, kLeaveAndHalt = 2 };   // the last: one block's, which halts the lattices
 
-// One thread of each of the nblk blocks that work together.  The last to arrive
-// clears the count and decides for going; a block that has waited long enough
-// decides against.  The decision word takes one value per launch, whichever
-// is first, so all blocks act alike, also those that come to run only when the
-// others have left.  `leave`: this block knows already that nothing is to run.
-__device__ __forceinline__ int check_in(const Lattice &lat, int nblk, const Start &start, bool leave)
+// One thread of each of the nblk blocks that work together.  They go when all
+// have arrived.  A block that has waited long enough marks the word, but only
+// while some are missing: so it says either that all came or that none goes,
+// also to blocks that come to run only when the others have left, and to later
+// launches, until the host clears it.  After a start the launch clears it.
+// (One round trip to memory, while the state loads: 2 us a launch; with
+// arrivals and decision in words of their own 4.)
+__device__ __forceinline__ int check_in(const Lattice &lat, int nblk, const Start &start)
 {
-    unsigned long long *arrived = last_tag(lat) + 1, *decision = last_tag(lat) + 2;
-    const unsigned long long go = 2 * start.id + 1, no = 2 * start.id;
-    const bool all = __hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                     (unsigned long long)(nblk - 1);
-    if (all) __hip_atomic_store(arrived, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (leave) return kLeave;
+    unsigned long long *word = arrivals(lat);
+    const unsigned long long all = (unsigned long long)nblk;
+    unsigned long long w = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
     const unsigned long long t0 = wall_clock64();
-    unsigned long long w = __hip_atomic_load(decision, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (!all && w >> 1 != start.id && wall_clock64() - t0 < start.wait) {
+    while (w < all && wall_clock64() - t0 < start.wait) {
         __builtin_amdgcn_s_sleep(1);
-        w = __hip_atomic_load(decision, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    const unsigned long long mine = all && start.wait > 0 ? go : no;
-    // (each failed exchange has seen another block's decision: at most two rounds)
-    while (w >> 1 != start.id)
-        if (__hip_atomic_compare_exchange_strong(decision, &w, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+    // (each failed exchange has seen another arrival or the mark)
+    while (w < all)
+        if (__hip_atomic_compare_exchange_strong(word, &w, w | kNoStart, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
-            return mine == go ? kGo : kLeaveAndHalt;
-    return w == go ? kGo : kLeave;
+            return kLeaveAndHalt;
+    return w == all ? kGo : kLeave;
 }
 
 // Whether the launch starts, the same in every thread of the block and every
@@ -322,8 +321,7 @@ __device__ __forceinline__ bool launch_starts(const Lattice &lat, int nblk, cons
 {
     __shared__ int go;
     if (threadIdx.x == blockDim.x - 64) {   // of the service wave, which has nothing else to do yet
-        const bool still = halted(lat) != kRuns;
-        const int r = nblk > 1 ? check_in(lat, nblk, start, still) : still ? kLeave : kGo;
+        const int r = nblk > 1 ? check_in(lat, nblk, start) : halted(lat) == kRuns ? kGo : kLeave;
         if (r == kLeaveAndHalt) halt(lat, kNotStarted, start);
         go = r == kGo;
     }
@@ -453,6 +451,8 @@ __device__ __forceinline__ void service_wave(const Lattice &lat, int steps, int 
     }
     if (__ballot(!alive) != 0 && lane == 0) halt(lat, kLost, start);
     if (rank == 0) {
+        // every block has published its last step, hence gone past its check-in
+        if (lane == 0) __hip_atomic_store(arrivals(lat), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         tail.store(lat);
         if (lane == 0) {
             lat.sc->cur ^= steps & 1;
@@ -464,13 +464,13 @@ __device__ __forceinline__ void service_wave(const Lattice &lat, int steps, int 
 
 // A pool's resident launch: up to k steps of each of n lattices that nblk
 // blocks work.  The grid's blocks form groups of nblk; group g takes lattices
-// g, g + groups, ... one after the other, each for all its steps.  A group
-// checks in once, by its first lattice's words; one that does not start leaves
-// those of its lattices halted that had steps to take.
+// g, g + groups, ... one after the other, each for all its steps.  A group checks
+// in at the first of them that has steps to take; one that does not start leaves
+// all those halted.
 template <typename Body>
 __device__ __forceinline__ void run_members(const Lattice *lats, int n, int nblk, int k, const Start &start, Body body)
 {
-    const int rank = blockIdx.x % nblk, groups = gridDim.x / nblk, first = blockIdx.x / nblk;
+    const int rank = blockIdx.x % nblk, groups = gridDim.x / nblk;
     auto member = [&](int l) -> const Lattice & {
         return *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
     };
@@ -480,19 +480,23 @@ __device__ __forceinline__ void run_members(const Lattice *lats, int n, int nblk
         return __builtin_amdgcn_readfirstlane(halted(lat) != kRuns ? 0 : (int)min((long long)k, lat.sc->remaining));
     };
     __shared__ int go;
-    if (threadIdx.x == blockDim.x - 64) {
-        const int r = nblk > 1 ? check_in(member(first), nblk, start, false) : kGo;
-        if (r == kLeaveAndHalt)
-            for (int l = first; l < n; l += groups)
-                if (steps_of(member(l)) > 0) halt(member(l), kNotStarted, start);
-        go = r == kGo;
-    }
-    __syncthreads();
-    if (!__builtin_amdgcn_readfirstlane(go)) return;
-    for (int l = first; l < n; l += groups) {
+    bool fresh = nblk > 1;
+    for (int l = blockIdx.x / nblk; l < n; l += groups) {
         const Lattice &lat = member(l);
         const int steps = steps_of(lat);
         if (steps <= 0) continue;
+        if (fresh) {
+            if (threadIdx.x == blockDim.x - 64) {
+                const int r = check_in(lat, nblk, start);
+                if (r == kLeaveAndHalt)
+                    for (int m = l; m < n; m += groups)
+                        if (steps_of(member(m)) > 0) halt(member(m), kNotStarted, start);
+                go = r == kGo;
+            }
+            __syncthreads();
+            if (!__builtin_amdgcn_readfirstlane(go)) return;
+            fresh = false;
+        }
         body(lat, lat.sc->cur, steps, rank, nblk);
         __syncthreads();   // the next lattice takes over the block's LDS
     }

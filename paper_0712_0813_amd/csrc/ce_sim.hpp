@@ -119,8 +119,7 @@ struct ce_sim {
     } resident;
     bool resident_planned = false;   // for the launch as it is now
     unsigned *halt = nullptr;        // set by a resident launch that left the lattice halted
-    unsigned long long launches = 0; // resident ones so far
-    bool unsettled = false;          // one has been queued since settle()
+    bool unsettled = false;          // a resident launch has been queued since settle()
     unsigned long long wait = ce::host::kStartWait;
 };
 
@@ -133,6 +132,8 @@ ce_status apply_launch(ce_sim *s, const ce_launch &cfg);
 // the recorded field maxima and queue the start-up half step.
 ce_status start_run(ce_sim *s);
 void drop_graphs(ce_sim *s);
+// After a launch that did not start: blocks check in from none again.
+hipError_t clear_arrivals(ce_sim *s);
 // The steps that queued launches left out of a halted lattice, by plain launches
 // on its stream, which has nothing else queued; it has run when this returns.
 // left: of a pool's member, the steps it still has to be given (its scalar

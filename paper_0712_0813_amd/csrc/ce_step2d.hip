@@ -36,7 +36,7 @@ __device__ __forceinline__ void store_row(gptr<T> row, unsigned x, const Quad<T>
         store_quad(row, x, q);
 }
 
-// LONE: of a launch of its own (batched launches leave halted lattices out).
+// LONE: of a launch of its own.
 template <typename T, int NF, int MODEL, int MODE, bool LONE>
 __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b, int grid)
 {
@@ -117,7 +117,6 @@ __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b
                     rep[i] = edge ? (pin[i] + base)[edge_x] : (T)0;
                 }
             }
-            if (LONE && MODE == kStep && stands_still(lat)) return;
             for (int k = 0; k < rows; k++) {
                 const int y = y0 + k;
                 // issue the loads of row y+2 before working on row y
@@ -219,7 +218,6 @@ __device__ __forceinline__ void stream2d_body(const Lattice &lat, int src, int b
         }
     }
 
-    if (LONE && MODE == kStep && stands_still(lat)) return;   // waves without a unit too
     const bool per_group = !LONE && lat.per_group;
     if (!per_group) {
         block_sum<NQ>(acc, red);
@@ -232,6 +230,14 @@ template <typename T, int NF, int MODEL, int MODE>
 __global__ __launch_bounds__(kBlock) void stream2d_kernel(Lattice lat, int src)
 {
     stream2d_body<T, NF, MODEL, MODE, true>(lat, src, blockIdx.x, gridDim.x);
+}
+
+// A step that leaves a halted lattice as it is (see Halt).
+template <typename T, int NF, int MODEL>
+__global__ __launch_bounds__(kBlock) void stream2d_guarded(Lattice lat, int src)
+{
+    if (lat.sc->halted) return;
+    stream2d_body<T, NF, MODEL, kStep, true>(lat, src, blockIdx.x, gridDim.x);
 }
 
 template <typename T, int NF, int MODEL>
@@ -250,6 +256,15 @@ template <typename T, int MODEL>
 hipError_t launch_t(const Lattice &lat, int src, Mode mode, hipStream_t st)
 {
     const dim3 grid(lat.nblocks), block(kBlock);
+    if (mode == kGuardedStep) {
+        switch (lat.nf) {
+        case 1: hipLaunchKernelGGL((stream2d_guarded<T, 1, MODEL>), grid, block, 0, st, lat, src); break;
+        case 2: hipLaunchKernelGGL((stream2d_guarded<T, 2, MODEL>), grid, block, 0, st, lat, src); break;
+        case 3: hipLaunchKernelGGL((stream2d_guarded<T, 3, MODEL>), grid, block, 0, st, lat, src); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (lat.nf * 2 + (mode == kInit)) {
     case 2: hipLaunchKernelGGL((stream2d_kernel<T, 1, MODEL, kStep>), grid, block, 0, st, lat, src); break;
     case 3: hipLaunchKernelGGL((stream2d_kernel<T, 1, MODEL, kInit>), grid, block, 0, st, lat, src); break;

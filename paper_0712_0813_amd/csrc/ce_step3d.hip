@@ -289,7 +289,6 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
                 }
             }
         }
-        if (DYN && MODE == kStep && stands_still(lat)) return;   // (batched launches leave halted lattices out)
         __syncthreads();
 
         for (int k = 0; k < zlen; k++) {
@@ -392,7 +391,6 @@ __device__ __forceinline__ void tiled3d_body(const Lattice &lat, int src, int b,
         }
     }
 
-    if (DYN && MODE == kStep && stands_still(lat)) return;   // blocks without a tile too
     if (!per_tile) {
         block_sum<NQ>(acc, red);
         put_partials<NQ>(lat, red, b);
@@ -406,6 +404,15 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WavesHint<T,
 tiled3d_kernel(Lattice lat, int src)
 {
     tiled3d_body<T, NF, MODEL, MODE, VEC, LPR, BS, true, RAGGED>(lat, src, blockIdx.x, gridDim.x);
+}
+
+// A step that leaves a halted lattice as it is (see Halt).
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, bool RAGGED>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WavesHint<T, NF, MODEL, VEC>::value, 8))) void
+tiled3d_guarded(Lattice lat, int src)
+{
+    if (lat.sc->halted) return;
+    tiled3d_body<T, NF, MODEL, kStep, VEC, LPR, BS, true, RAGGED>(lat, src, blockIdx.x, gridDim.x);
 }
 
 // Step pass over many lattices of one class; see pass_batched.
@@ -442,6 +449,18 @@ hipError_t launch_one(const Lattice &lat, int src, hipStream_t st)
 {
     if constexpr (lds_fits<T, NF, VEC, LPR, BS>() && (!RAGGED || sizeof(T) == 4)) {
         hipLaunchKernelGGL((tiled3d_kernel<T, NF, MODEL, MODE, VEC, LPR, BS, RAGGED>), dim3(lat.nblocks), dim3(BS), 0, st, lat, src);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidConfiguration;
+    }
+}
+
+// Guarded steps: of the shapes that a resident pass takes (see guarded_built).
+template <typename T, int NF, int MODEL, int VEC, int LPR, int BS, bool RAGGED = false>
+hipError_t guarded_one(const Lattice &lat, int src, hipStream_t st)
+{
+    if constexpr (lds_fits<T, NF, VEC, LPR, BS>() && (!RAGGED || sizeof(T) == 4)) {
+        hipLaunchKernelGGL((tiled3d_guarded<T, NF, MODEL, VEC, LPR, BS, RAGGED>), dim3(lat.nblocks), dim3(BS), 0, st, lat, src);
         return hipGetLastError();
     } else {
         return hipErrorInvalidConfiguration;
@@ -508,6 +527,21 @@ struct ByShape {
         if (v == 4 && l == 64 && b == 512) return launch_one<T, NF, MODEL, MODE, 4, 64, 512>(lat, src, st);
         return hipErrorInvalidValue;
     }
+    static hipError_t guarded(const Lattice &lat, int src, hipStream_t st)
+    {
+        const int v = lat.vec, l = lat.lpr, b = lat.bs;
+        if constexpr (sizeof(T) == 4) {
+            if (lat.ragged)
+                return l == 16 ? guarded_one<T, NF, MODEL, 4, 16, 256, true>(lat, src, st)
+                               : guarded_one<T, NF, MODEL, 4, 8, 256, true>(lat, src, st);
+            if (v == 4 && l == 16 && b == 256) return guarded_one<T, NF, MODEL, 4, 16, 256>(lat, src, st);
+            if (v == 4 && l == 8 && b == 256) return guarded_one<T, NF, MODEL, 4, 8, 256>(lat, src, st);
+        } else {
+            if (v == 2 && l == 32 && b == 512) return guarded_one<T, NF, MODEL, 2, 32, 512>(lat, src, st);
+            if (v == 2 && l == 16 && b == 512) return guarded_one<T, NF, MODEL, 2, 16, 512>(lat, src, st);
+        }
+        return hipErrorInvalidValue;
+    }
     static hipError_t batched(const Lattice *lats, const int *blk_lat, int total, int grid, int v, int l, int b,
                               bool ragged, hipStream_t st)
     {
@@ -557,12 +591,15 @@ template <typename T, int MODEL>
 hipError_t launch_t(const Lattice &lat, int src, Mode mode, hipStream_t st)
 {
     switch (lat.nf) {
-    case 1: return mode == kStep ? ByShape<T, 1, MODEL>::template launch<kStep>(lat, src, st)
-                                 : ByShape<T, 1, MODEL>::template launch<kInit>(lat, src, st);
-    case 2: return mode == kStep ? ByShape<T, 2, MODEL>::template launch<kStep>(lat, src, st)
-                                 : ByShape<T, 2, MODEL>::template launch<kInit>(lat, src, st);
-    case 3: return mode == kStep ? ByShape<T, 3, MODEL>::template launch<kStep>(lat, src, st)
-                                 : ByShape<T, 3, MODEL>::template launch<kInit>(lat, src, st);
+    case 1: return mode == kGuardedStep ? ByShape<T, 1, MODEL>::guarded(lat, src, st)
+                    : mode == kStep      ? ByShape<T, 1, MODEL>::template launch<kStep>(lat, src, st)
+                                         : ByShape<T, 1, MODEL>::template launch<kInit>(lat, src, st);
+    case 2: return mode == kGuardedStep ? ByShape<T, 2, MODEL>::guarded(lat, src, st)
+                    : mode == kStep      ? ByShape<T, 2, MODEL>::template launch<kStep>(lat, src, st)
+                                         : ByShape<T, 2, MODEL>::template launch<kInit>(lat, src, st);
+    case 3: return mode == kGuardedStep ? ByShape<T, 3, MODEL>::guarded(lat, src, st)
+                    : mode == kStep      ? ByShape<T, 3, MODEL>::template launch<kStep>(lat, src, st)
+                                         : ByShape<T, 3, MODEL>::template launch<kInit>(lat, src, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -633,6 +670,13 @@ hipError_t launch_tiled_model<kUnit>(const Lattice &lat, int precision, int src,
 
 #if CE_UNIT_MODEL == CE_MODEL_QUARTIC
 // Model-independent functions and the dispatch on the model.
+
+bool guarded_built(const Lattice &lat, int precision)
+{
+    if (lat.kind != kTiled3d || lat.ragged) return true;
+    return precision == CE_FP64 ? lat.vec == 2 && lat.lpr >= 16 && lat.bs == 512
+                                : lat.vec == 4 && lat.lpr <= 16 && lat.bs == 256;
+}
 
 bool tiled_shape_built(int vec, int lpr, int bs)
 {
