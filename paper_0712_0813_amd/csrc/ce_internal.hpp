@@ -116,7 +116,7 @@ enum Halt { kRuns = 0, kNotStarted = 1, kLost = 2 };
 
 // What a resident launch's blocks agree with on whether it starts.
 struct Start {
-    unsigned long long wait;   // ticks (100 MHz) to wait for the other blocks
+    unsigned long long wait;   // ticks (100 MHz) to wait for the other blocks; 0: do not start
     unsigned *halt;            // page-locked host memory: set to 1 when a lattice halts
 };
 

@@ -301,6 +301,9 @@ __device__ __forceinline__ int check_in(const Lattice &lat, int nblk, const Star
 {
     unsigned long long *word = arrivals(lat);
     const unsigned long long all = (unsigned long long)nblk;
+    if (start.wait == 0)   // no block arrives
+        return __hip_atomic_fetch_or(word, kNoStart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < kNoStart ? kLeaveAndHalt
+                                                                                                       : kLeave;
     unsigned long long w = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
     const unsigned long long t0 = wall_clock64();
     while (w < all && wall_clock64() - t0 < start.wait) {
