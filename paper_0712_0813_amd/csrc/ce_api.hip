@@ -372,6 +372,21 @@ const void *resident_kernel(const ce_params *p, const ce_launch &c, bool ragged,
                                                               batched);
 }
 
+// Built resident passes that are so short of registers that plain launches of
+// the same tiling are as fast or faster (us a step, resident and plain): three
+// FP64 fields in the direct pass, 32^3 12.0 and 11.4, 48^3 20.5 and 13.5,
+// except where a block holds whole planes and there are few (16^3 7.5 and 10.2);
+// in units of four rows, 768^2 25.6 and 21.9; three FP32 fields of the
+// polynomial model in units of eight, 1280^2 44.7 and 43.8.
+bool resident_pays(const Lattice &lat, int precision)
+{
+    if (lat.nf < 3) return true;
+    if (lat.kind == kDirect && lat.dims == 3 && precision == CE_FP64)
+        return lat.N <= 16 && kBlock % (lat.N * lat.N / 4) == 0;
+    if (lat.kind == kStream2d) return precision == CE_FP64 ? lat.zc < 4 : lat.model != kPoly || lat.zc < 8;
+    return true;
+}
+
 // The resident pass that takes the same steps as s's launch, if there is one:
 // its blocks must all be resident at once, one per published row.
 void plan_resident(ce_sim *s)
@@ -379,6 +394,7 @@ void plan_resident(ce_sim *s)
     s->resident = ce_sim::Resident{};
     s->resident_planned = true;
     const Lattice &lat = s->lat;
+    if (!resident_pays(lat, s->p.precision)) return;
     ce_sim::Resident r;
     if (lat.kind == kDirect) {
         // one quad per thread, and no block without one; VB blocks of the
@@ -536,10 +552,14 @@ ce_launch default_launch(const ce_params *p, int cus)
     ce_launch c{CE_KERNEL_DIRECT, 0, 0, 0, 0, 0};
     if (p->dims == 2) {
         // lattices that a resident pass can take: the shortest units that
-        // leave no more groups of four than it has blocks
+        // leave no more groups of four than it has blocks.  (The polynomial
+        // model's units of sixteen rows only where they fill the chip: 1536^2 x 2
+        // fields, 144 groups, took 52.0 us a step, plain units of eight take 36.6.)
         for (int rows = 1; rows <= 16; rows *= 2) {
             const ce_launch r{CE_KERNEL_STREAM2D, 4, 64, kBlock, rows, 0};
-            if (stream2d_fits(2, p->N, rows) && resident_kernel(p, r, false, false)) return r;
+            if (!stream2d_fits(2, p->N, rows) || !resident_kernel(p, r, false, false)) continue;
+            if (p->model == kPoly && rows == 16 && stream2d_groups(p->N, rows) < cus) continue;
+            return r;
         }
         // rows per unit: the tallest (up to 64) that still gives every
         // compute unit a group of four units
@@ -620,7 +640,11 @@ ce_launch default_launch(const ce_params *p, int cus)
     for (int a = 0; a < 2; a++) {
         const bool fp64 = p->precision == CE_FP64;
         const int v = fp64 ? 2 : 4, l = (fp64 ? 32 : 16) >> a, bs = fp64 ? 512 : 256;
-        for (int z = 1; z <= 8 && p->N >= 64; z *= 2) {
+        // two planes at least where one gains the resident pass nothing and
+        // costs single steps (64^3 in FP64, one and two fields: 4.1 and 5.8 us a
+        // step, single ones 18.3 and 20.3; one plane 4.3 and 5.8, 22.8 and 25.0)
+        const int least = fp64 && p->model == kQuartic && p->nfields <= 2 ? 2 : 1;
+        for (int z = least; z <= 8 && p->N >= 64; z *= 2) {
             if (p->N % z || !tiled_fits(3, p->N, v, l, bs, z) || tiled_tiles(p->N, v, l, bs, z) > kSyncRows) continue;
             const ce_launch r{CE_KERNEL_TILED3D, v, l, bs, z, 0};
             if (resident_kernel(p, r, false, false)) return r;

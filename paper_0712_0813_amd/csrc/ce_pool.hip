@@ -308,6 +308,12 @@ void plan_resident_class(ClassTable &t, int cus, bool only)
     const long long fit = (long long)per * cus / tiles;   // members at a time
     const long long n = (long long)t.lats.size();
     if (fit < 1 || !(only || n * tiles >= cus / 2)) return;
+    // the polynomial model, bound by its instructions, only while every member
+    // is worked at once: in several rounds, of one block a compute unit, the
+    // batched pass with its more wavefronts is faster (us a pool step, resident
+    // and batched: 8 x 64^3 x 2 fields, one round, 26 and 44; 64 x 64^3 x 1 108
+    // and 74, 8 x 128^3 x 3 408 and 248, 16 x 1024^2 x 2 223 and 147)
+    if (p.model == kPoly && n > fit) return;
     t.res_kernel = kernel;
     t.res_tiles = (int)tiles;
     t.res_grid = (int)(std::min(fit, n) * tiles);
