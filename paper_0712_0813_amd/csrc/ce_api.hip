@@ -285,10 +285,6 @@ ce_status build_graph(ce_sim *s, int parity)
     return CE_OK;
 }
 
-// Steps of one resident launch at most: a millisecond or two, for which other
-// work on the GPU may have to wait.
-constexpr int kResidentSteps = 256;
-
 hipError_t launch_resident(ce_sim *s, int steps)
 {
     int src = s->cur;
@@ -1085,7 +1081,12 @@ ce_status ce_step(ce_sim *s, int64_t nsteps)
             const Alone alone;
             if (!alone && s->resident.blocks > 1) break;
             int n = (int)std::min<long long>(left, kResidentSteps);
-            CE_HIP(launch_resident(s, n));
+            if (launch_resident(s, n) != hipSuccess) {
+                // refused, nothing queued: plain launches until the next plan
+                (void)hipGetLastError();
+                s->resident = ce_sim::Resident{};
+                break;
+            }
             left -= n;
         }
     }

@@ -446,7 +446,12 @@ hipError_t launch_class(const ClassTable &t, hipStream_t st)
     return launch_batched(t.d_lats, t.d_blk, (int)t.blk_lat.size(), t.grid, t.proto, t.precision, st);
 }
 
-// k steps of a class: one resident launch (if such are free to take), or k
+// Steps of a resident launch of a class at most: other work may have to wait
+// for it.  A step of a tile takes some 12 us, so 25 ms; and no fewer steps than
+// make the launch and the loads of the members' states worth it.
+constexpr int kResidentTileSteps = 2048, kLeastSteps = 8;
+
+// k steps of a class: by resident launches (if such are free to take), or k
 // batched ones.
 hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, int k, bool resident)
 {
@@ -454,9 +459,22 @@ hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, 
         pl->resident_seq = pl->seq;
         const Lattice *lats = t.d_lats;
         int n = (int)t.lats.size(), tiles = t.res_tiles;
+        const int rounds = (n + t.res_grid / tiles - 1) / (t.res_grid / tiles);
+        const int most = std::min(kResidentSteps, std::max(kResidentTileSteps / rounds, kLeastSteps));
         Start start{pl->wait, pl->halt};
-        void *args[] = {&lats, &n, &tiles, &k, &start};
-        return hipLaunchCooperativeKernel(t.res_kernel, dim3(t.res_grid), dim3(t.proto.bs + 64), args, 0, st);
+        while (k > 0) {
+            int steps = std::min(k, most);
+            void *args[] = {&lats, &n, &tiles, &steps, &start};
+            if (hipLaunchCooperativeKernel(t.res_kernel, dim3(t.res_grid), dim3(t.proto.bs + 64), args, 0, st) !=
+                hipSuccess) {
+                // refused, nothing queued: batched launches instead
+                (void)hipGetLastError();
+                pl->no_resident = true;
+                pl->dirty = true;
+                break;
+            }
+            k -= steps;
+        }
     }
     for (int i = 0; i < k; i++) {
         const hipError_t e = launch_class(t, st);

@@ -80,6 +80,10 @@ void ready_halt_words();
 unsigned *take_halt_word();
 void give_halt_word(unsigned *w);
 
+// Steps of one resident launch at most: a millisecond or two, for which other
+// work on the GPU may have to wait.
+constexpr int kResidentSteps = 256;
+
 // Ticks of the GPU's clock (100 MHz) a resident launch waits for its blocks.
 // A launch queued behind another's blocks gets its units within that one's
 // time (at most some milliseconds of a resident launch, 7 ms of a 1024^3 pass,
