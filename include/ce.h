@@ -294,10 +294,17 @@ ce_status ce_time_steps(ce_sim *s, int64_t nsteps, float *ms);
 /* Wait for all work queued on the simulation's stream. */
 ce_status ce_sync(ce_sim *s);
 
-/* End a run: wait for its queued work and free everything the simulation
- * allocated (never the caller's arena or stream).  NULL-safe; s must not be
- * used afterwards. */
+/* End a run: wait for its queued work (and, like any freeing of device memory,
+ * for the device's) and free everything the simulation allocated (never the
+ * caller's arena or stream), but for its device memory, which the library keeps
+ * for the next simulation of the same size: at most 8 blocks and 4 GiB in the
+ * process, the oldest given back first, and all of it when an allocation of
+ * the library fails.  NULL-safe; s must not be used afterwards. */
 void ce_destroy(ce_sim *s);
+
+/* Give the device memory kept from destroyed simulations back now (for another
+ * allocator of the process, say). */
+ce_status ce_release_memory(void);
 
 /* ---- Spectra -------------------------------------------------------------
  * The paper's programs Fourier transform the fields to output their spectra

@@ -153,6 +153,7 @@ SIGNATURES = {
                       ctypes.c_int),
     "ce_get_step": ([_P, ctypes.POINTER(ctypes.c_int64)], ctypes.c_int),
     "ce_set_step_block": ([_P, ctypes.c_int32], ctypes.c_int),
+    "ce_release_memory": ([], ctypes.c_int),
     "ce_set_wait_limit": ([_P, ctypes.c_double], ctypes.c_int),
     "ce_get_launch": ([_P, ctypes.POINTER(ce_launch)], ctypes.c_int),
     "ce_set_launch": ([_P, ctypes.POINTER(ce_launch)], ctypes.c_int),
@@ -334,6 +335,11 @@ def ce_get_step(sim: int) -> int:
 
 def ce_set_step_block(sim: int, k: int) -> None:
     _check(load_library().ce_set_step_block(sim, int(k)), "ce_set_step_block")
+
+
+def ce_release_memory() -> None:
+    """Give the device memory kept from destroyed simulations back."""
+    _check(load_library().ce_release_memory(), "ce_release_memory")
 
 
 def ce_set_wait_limit(sim: int, ms: float) -> None:

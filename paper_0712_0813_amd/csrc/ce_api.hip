@@ -1267,12 +1267,21 @@ ce_status ce_read_sites(ce_sim *s, int32_t field, int64_t count, const int64_t *
     return st != CE_OK ? st : ce_read_sites(s, field, count, sites, f, fdot);
 }
 
+ce_status ce_release_memory(void)
+{
+    const Use use;
+    give_back_kept_memory();
+    return CE_OK;
+}
+
 void ce_destroy(ce_sim *s)
 {
     const Use use;
     if (!s) return;
-    // memory is kept only if everything that used it is known to have ended
-    const bool idle = s->stream && hipStreamSynchronize(s->stream) == hipSuccess;
+    // memory is kept only if everything that used it is known to have ended:
+    // steps captured on the stream may be running from a graph on another one
+    bool idle = s->stream && hipStreamSynchronize(s->stream) == hipSuccess;
+    if (s->own_mem && idle) idle = hipDeviceSynchronize() == hipSuccess;
     drop_graphs(s);
     if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
