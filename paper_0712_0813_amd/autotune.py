@@ -129,6 +129,9 @@ def candidates(dims: int, N: int, grids: Sequence[int] = (0, 512, 768, 1024)) ->
     return out
 
 
+MAX_STEP_BLOCK = 4096   # what ce_set_step_block takes
+
+
 def _load_cache(path: str) -> Dict[str, dict]:
     if os.path.exists(path):
         with open(path) as fh:
@@ -166,9 +169,18 @@ def tune(dims: int, N: int, nfields: int, precision: int = ce.CE_FP32, steps: in
                                      background=lat.background)
             s.load(phi, phid)
             del phi, phid
-        # no graph is captured (every timed call is shorter than a step block),
-        # and launches whose steps can stay on the chip are timed that way
-        s.set_step_block(max(steps, warmup, final_steps) + 1)
+        # no graph is captured (every call is shorter than a step block), and
+        # launches whose steps can stay on the chip are timed that way
+        most = min(max(steps, warmup, final_steps), MAX_STEP_BLOCK - 1)
+        s.set_step_block(most + 1)
+
+        def timed(n: int) -> float:
+            return sum(s.time_steps(min(most, n - k)) for k in range(0, n, most)) / n
+
+        def warm() -> None:
+            for k in range(0, warmup, most):
+                s.step(min(most, warmup - k))
+
         default = s.get_launch().as_tuple()
         screen = []
         for cfg in candidates(dims, N):
@@ -176,8 +188,8 @@ def tune(dims: int, N: int, nfields: int, precision: int = ce.CE_FP32, steps: in
                 s.set_launch(*cfg)
             except ce.CeError:
                 continue
-            s.step(warmup)
-            ms = s.time_steps(steps) / steps
+            warm()
+            ms = timed(steps)
             chosen = s.get_launch().as_tuple()
             screen.append((ms, chosen))
             if verbose:
@@ -193,8 +205,8 @@ def tune(dims: int, N: int, nfields: int, precision: int = ce.CE_FP32, steps: in
             finals.append(default)
         for cfg in finals:
             s.set_launch(*cfg)
-            s.step(warmup)
-            ms = min(s.time_steps(final_steps) / final_steps for _ in range(2))
+            warm()
+            ms = min(timed(final_steps) for _ in range(2))
             results.append((ms, cfg))
             if verbose:
                 print(f"final {cfg} {ms:.4f} ms/step", file=sys.stderr, flush=True)
