@@ -111,7 +111,7 @@ enum Mode { kStep = 0, kInit = 1, kGuardedStep = 2 };   // the last: kStep that 
 // (other work holds the compute units), the launch ends with the state as it
 // was and kNotStarted; every later step leaves such a lattice alone until the
 // host, which sees the launch's halt word, has taken the missing steps by plain
-// launches.  kLost: a block that had started stopped; the sums are lost.
+// launches (a pool's member has no steps left to take until then).  kLost: a block that had started stopped; the sums are lost.
 enum Halt { kRuns = 0, kNotStarted = 1, kLost = 2 };
 
 // What a resident launch's blocks agree with on whether it starts.

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kBlock) void pass_batched(const Lattice *lats, cons
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         const int l = __builtin_amdgcn_readfirstlane(blk_lat[v]);
         const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
-        if (lat.sc->remaining <= 0 || lat.sc->halted) continue;
+        if (lat.sc->remaining <= 0) continue;
         const int src = lat.sc->cur;
         pass_body<T, D, NF, MODEL, kStep>(lat, src, v - lat.first_block, lat.nblocks);
     }
@@ -206,11 +206,12 @@ hipError_t launch_dims(const Lattice &lat, int src, Mode mode, hipStream_t st)
     }
 }
 
-// Step budgets of a class's lattices for the coming block (pool quotas).
+// Step budgets of a class's lattices for the coming block (pool quotas); a
+// halted one (see Halt) takes none.
 __global__ __launch_bounds__(kBlock) void set_remaining_kernel(const Lattice *lats, const long long *vals, int n)
 {
     const int l = blockIdx.x * kBlock + threadIdx.x;
-    if (l < n) lats[l].sc->remaining = vals[l];
+    if (l < n) lats[l].sc->remaining = lats[l].sc->halted ? 0 : vals[l];
 }
 
 template <typename T>

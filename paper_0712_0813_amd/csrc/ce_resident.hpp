@@ -469,7 +469,7 @@ __device__ __forceinline__ void service_wave(const Lattice &lat, int steps, int 
 // blocks work.  The grid's blocks form groups of nblk; group g takes lattices
 // g, g + groups, ... one after the other, each for all its steps.  A group checks
 // in at the first of them that has steps to take; one that does not start leaves
-// all those halted.
+// all those halted, with no steps to take.
 template <typename Body>
 __device__ __forceinline__ void run_members(const Lattice *lats, int n, int nblk, int k, const Start &start, Body body)
 {
@@ -477,29 +477,30 @@ __device__ __forceinline__ void run_members(const Lattice *lats, int n, int nblk
     auto member = [&](int l) -> const Lattice & {
         return *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
     };
-    // the steps left and the buffer change only when every block of the group
-    // has published the last step, so all read the same
-    auto steps_of = [&](const Lattice &lat) {
-        return __builtin_amdgcn_readfirstlane(halted(lat) != kRuns ? 0 : (int)min((long long)k, lat.sc->remaining));
-    };
-    __shared__ int go;
-    bool fresh = nblk > 1;
-    for (int l = blockIdx.x / nblk; l < n; l += groups) {
-        const Lattice &lat = member(l);
-        const int steps = steps_of(lat);
-        if (steps <= 0) continue;
-        if (fresh) {
-            if (threadIdx.x == blockDim.x - 64) {
-                const int r = check_in(lat, nblk, start);
-                if (r == kLeaveAndHalt)
-                    for (int m = l; m < n; m += groups)
-                        if (steps_of(member(m)) > 0) halt(member(m), kNotStarted, start);
-                go = r == kGo;
-            }
-            __syncthreads();
-            if (!__builtin_amdgcn_readfirstlane(go)) return;
-            fresh = false;
+    int l = blockIdx.x / nblk;
+    if (nblk > 1) {
+        __shared__ int go;
+        while (l < n && member(l).sc->remaining <= 0) l += groups;
+        if (l >= n) return;
+        if (threadIdx.x == blockDim.x - 64) {
+            const int r = check_in(member(l), nblk, start);
+            if (r == kLeaveAndHalt)
+                for (int m = l; m < n; m += groups)
+                    if (member(m).sc->remaining > 0) {
+                        halt(member(m), kNotStarted, start);
+                        member(m).sc->remaining = 0;
+                    }
+            go = r == kGo;
         }
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane(go)) return;
+    }
+    for (; l < n; l += groups) {
+        const Lattice &lat = member(l);
+        // the steps left and the buffer change only when every block of the
+        // group has published the last step, so all read the same
+        const int steps = (int)min((long long)k, lat.sc->remaining);
+        if (steps <= 0) continue;
         body(lat, lat.sc->cur, steps, rank, nblk);
         __syncthreads();   // the next lattice takes over the block's LDS
     }

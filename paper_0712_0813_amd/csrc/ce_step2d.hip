@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kBlock) void stream2d_batched(const Lattice *lats, 
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         const int l = __builtin_amdgcn_readfirstlane(blk_lat[v]);
         const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
-        if (lat.sc->remaining <= 0 || lat.sc->halted) continue;
+        if (lat.sc->remaining <= 0) continue;
         const int src = lat.sc->cur;
         stream2d_body<T, NF, MODEL, kStep, false>(lat, src, v - lat.first_block, lat.nblocks);
     }

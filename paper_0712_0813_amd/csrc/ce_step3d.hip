@@ -423,7 +423,7 @@ tiled3d_batched(const Lattice *lats, const int *blk_lat, int total)
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         const int l = __builtin_amdgcn_readfirstlane(blk_lat[v]);
         const Lattice &lat = *(const Lattice *)((const __attribute__((address_space(4))) Lattice *)lats + l);
-        if (lat.sc->remaining <= 0 || lat.sc->halted) continue;
+        if (lat.sc->remaining <= 0) continue;
         const int src = lat.sc->cur;
         tiled3d_body<T, NF, MODEL, kStep, VEC, LPR, BS, false, RAGGED>(lat, src, v - lat.first_block, lat.nblocks);
     }
