@@ -483,23 +483,57 @@ hipError_t launch_class_steps(ce_pool *pl, const ClassTable &t, hipStream_t st, 
     return hipSuccess;
 }
 
-// k steps of every class, ordered after the work already on `st` and ahead of
-// what follows it.  One class runs its chain on `st`; several fork onto the
-// lanes, each lane running the chains of its classes, and join again.
-hipError_t launch_block(ce_pool *pl, hipStream_t st, int k, bool resident)
+// Which classes of a pool: those planned resident, the others, or all.
+enum Part { kResidentClasses = 1, kBatchedClasses = 2, kAllClasses = 3 };
+bool in_part(const ClassTable &t, int part) { return (t.res_kernel ? kResidentClasses : kBatchedClasses) & part; }
+
+// k steps of the classes of `part`, each class's chain on its lane behind
+// fork_ev; their ends are recorded in the lanes' join_ev.
+hipError_t launch_lanes(ce_pool *pl, int part, int k, bool resident)
 {
-    const int nc = (int)pl->classes.size();
-    if (nc == 1) return launch_class_steps(pl, pl->classes[0], st, k, resident);
-    const int nl = std::min(nc, ce_pool::kLanes);
-    hipError_t e = hipEventRecord(pl->fork_ev, st);
+    const int nc = (int)pl->classes.size(), nl = std::min(nc, ce_pool::kLanes);
+    hipError_t e = hipSuccess;
     for (int l = 0; l < nl && e == hipSuccess; l++) e = hipStreamWaitEvent(pl->lanes[l], pl->fork_ev, 0);
     for (int c = 0; c < nc && e == hipSuccess; c++)
-        e = launch_class_steps(pl, pl->classes[c], pl->lanes[pl->lane_of[c]], k, resident);
-    for (int l = 0; l < nl && e == hipSuccess; l++) {
-        e = hipEventRecord(pl->join_ev[l], pl->lanes[l]);
-        if (e == hipSuccess) e = hipStreamWaitEvent(st, pl->join_ev[l], 0);
-    }
+        if (in_part(pl->classes[c], part))
+            e = launch_class_steps(pl, pl->classes[c], pl->lanes[pl->lane_of[c]], k, resident);
+    for (int l = 0; l < nl && e == hipSuccess; l++) e = hipEventRecord(pl->join_ev[l], pl->lanes[l]);
     return e;
+}
+
+hipError_t join_lanes(ce_pool *pl, hipStream_t st)
+{
+    const int nl = std::min((int)pl->classes.size(), ce_pool::kLanes);
+    hipError_t e = hipSuccess;
+    for (int l = 0; l < nl && e == hipSuccess; l++) e = hipStreamWaitEvent(st, pl->join_ev[l], 0);
+    return e;
+}
+
+// k steps of the classes of `part`, ordered after the work already on `st` and
+// ahead of what follows it.  One class runs its chain on `st`; several fork
+// onto the lanes, each lane running the chains of its classes, and join again.
+hipError_t launch_block(ce_pool *pl, hipStream_t st, int part, int k, bool resident)
+{
+    int only = -1, count = 0;
+    for (int c = 0; c < (int)pl->classes.size(); c++)
+        if (in_part(pl->classes[c], part)) only = c, count++;
+    if (count == 1) return launch_class_steps(pl, pl->classes[only], st, k, resident);
+    hipError_t e = hipEventRecord(pl->fork_ev, st);
+    if (e == hipSuccess) e = launch_lanes(pl, part, k, resident);
+    return e == hipSuccess ? join_lanes(pl, st) : e;
+}
+
+// The same of all classes with the batched ones' chains as a graph.
+hipError_t launch_block_with_graph(ce_pool *pl, hipGraphExec_t graph, int k, bool resident_planned)
+{
+    if (!resident_planned) return hipGraphLaunch(graph, pl->stream);
+    hipError_t e = hipEventRecord(pl->fork_ev, pl->stream);
+    if (e == hipSuccess) {
+        const Alone alone;
+        e = launch_lanes(pl, kResidentClasses, k, (bool)alone);
+    }
+    if (e == hipSuccess) e = hipGraphLaunch(graph, pl->stream);
+    return e == hipSuccess ? join_lanes(pl, pl->stream) : e;
 }
 
 
@@ -508,7 +542,7 @@ ce_status build_pool_graph(ce_pool *pl, int k, hipGraphExec_t *out)
     if (!pl->cap_stream) CE_HIP(hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking));
     hipGraph_t g = nullptr;
     CE_HIP(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeRelaxed));
-    hipError_t err = launch_block(pl, pl->cap_stream, k, false);
+    hipError_t err = launch_block(pl, pl->cap_stream, kBatchedClasses, k, false);
     const hipError_t e2 = hipStreamEndCapture(pl->cap_stream, &g);
     if (err != hipSuccess || e2 != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -850,11 +884,19 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
     // A capture is attempted only while no admission is running on another
     // thread (its HIP calls could invalidate the capture); a failed capture
     // falls back to launching the block directly.
-    // Resident classes take a block in one launch and are not captured.
+    // The graph is of the batched classes; resident ones take a block in a
+    // launch or a few.  Beside those, a few launches are not worth a graph (a
+    // mix of three resident classes and a batched one, us a pool step with a
+    // graph and without: blocks of four steps 95 and 89, of fifty 54.5 and 56).
     hipGraphExec_t graph = nullptr;
     bool resident = false;
-    for (const ClassTable &t : pl->classes) resident |= t.res_kernel != nullptr;
-    if (k > 1 && pl->blocks_since_rebuild > 0 && !resident) {
+    int batched = 0;
+    for (const ClassTable &t : pl->classes)
+        if (t.res_kernel)
+            resident = true;
+        else
+            batched++;
+    if (k > 1 && pl->blocks_since_rebuild > 0 && batched > 0 && (!resident || batched * k >= 32)) {
         auto it = T.graphs.find(k);
         if (it != T.graphs.end()) {
             graph = it->second;
@@ -865,12 +907,12 @@ ce_status ce_pool_run_block(ce_pool *pl, int32_t k)
         }
     }
     if (graph) {
-        CE_HIP(hipGraphLaunch(graph, pl->stream));
+        CE_HIP(launch_block_with_graph(pl, graph, k, resident));
     } else if (resident) {
         const Alone alone;
-        CE_HIP(launch_block(pl, pl->stream, k, (bool)alone));
+        CE_HIP(launch_block(pl, pl->stream, kAllClasses, k, (bool)alone));
     } else {
-        CE_HIP(launch_block(pl, pl->stream, k, false));
+        CE_HIP(launch_block(pl, pl->stream, kAllClasses, k, false));
     }
     const long long s = pl->seq++;
     CE_HIP(hipEventRecord(pl->block_ev[s % ce_pool::kEvRing], pl->stream));

@@ -48,3 +48,25 @@ def test_a_pool_launch_lasts_some_milliseconds(lib, members, k, launches):
             assert (calls(COOP), calls(KERNEL)) == ({launches}, 0), (calls(COOP), calls(KERNEL))
             assert pool.steps_left(j) == 10000 - {k}
     """)
+
+
+def test_batched_classes_are_replayed_beside_resident_ones(lib):
+    # 8 x 64^3 stays on the chip for a block; two lines and a 48^3 cube are
+    # batched, as a graph from the composition's second block on
+    _hoststub.run(lib, """
+        with ce.Pool(8 << 30) as pool:
+            for _ in range(8):
+                j = pool.admit_generated(params(3, 64, 2), SPEC, 10000)
+            for p in (params(1, 1024, 1), params(1, 1024, 2)):
+                pool.admit_generated(p, SPEC, 10000)
+            lib.stub_reset()
+            pool.run_block(16)
+            assert (calls(COOP), calls(KERNEL), calls("hipGraphLaunch")) == (1, 32, 0)
+            for n in range(2, 5):
+                pool.run_block(16)
+                assert (calls(COOP), calls(KERNEL), calls("hipGraphLaunch")) == (n, 64, n - 1)
+            assert calls("hipGraphInstantiate") == 1
+            pool.run_block(4)    # too few launches for a graph beside others
+            assert (calls(COOP), calls(KERNEL), calls("hipGraphLaunch")) == (5, 72, 3)
+            assert pool.steps_left(j) == 10000 - 68
+    """)
