@@ -500,6 +500,10 @@ ce_status ce_pool_admit_image(ce_pool *pl, const void *image, size_t bytes, int6
 
 ce_status ce_pool_get_info(const ce_pool *pl, ce_pool_info *out);
 
+/* Of the classes of the last block, how many take a whole block of steps in
+ * one launch (or a few) that keeps their members on the chip. */
+ce_status ce_pool_resident_classes(const ce_pool *pl, int32_t *out);
+
 /* Free the pool and every member still in it.  NULL-safe. */
 void ce_pool_destroy(ce_pool *pl);
 

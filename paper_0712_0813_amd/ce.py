@@ -180,6 +180,7 @@ SIGNATURES = {
     "ce_pool_poll": ([_P, ctypes.c_int64, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ce_energy)],
                      ctypes.c_int),
     "ce_pool_steps_left": ([_P, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)], ctypes.c_int),
+    "ce_pool_resident_classes": ([_P, ctypes.POINTER(ctypes.c_int32)], ctypes.c_int),
     "ce_pool_set_quota": ([_P, ctypes.c_int64, ctypes.c_int64], ctypes.c_int),
     "ce_pool_set_wait_limit": ([_P, ctypes.c_double], ctypes.c_int),
     "ce_pool_retire": ([_P, ctypes.c_int64, _DP, _DP], ctypes.c_int),
@@ -672,6 +673,12 @@ def ce_pool_get_info(pool: int) -> ce_pool_info:
     return out
 
 
+def ce_pool_resident_classes(pool: int) -> int:
+    n = ctypes.c_int32()
+    _check(load_library().ce_pool_resident_classes(pool, ctypes.byref(n)), "ce_pool_resident_classes")
+    return n.value
+
+
 def ce_pool_destroy(pool: Optional[int]) -> None:
     if pool:
         load_library().ce_pool_destroy(pool)
@@ -737,6 +744,10 @@ class Pool:
     def retire(self, job_id: int, read: bool = True):
         shape, nf = self.shapes.pop(job_id)
         return ce_pool_retire(self.handle, job_id, shape if read else None, nf)
+
+    def resident_classes(self) -> int:
+        """Classes of the last block that keep their members on the chip for it."""
+        return ce_pool_resident_classes(self.handle)
 
     def info(self) -> ce_pool_info:
         return ce_pool_get_info(self.handle)

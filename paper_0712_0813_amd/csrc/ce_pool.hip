@@ -1076,6 +1076,15 @@ ce_status ce_pool_member_image_bytes(const ce_pool *pl, int64_t job_id, size_t *
     return ce_image_bytes(m->sim, out);
 }
 
+ce_status ce_pool_resident_classes(const ce_pool *pl, int32_t *out)
+{
+    if (!pl || !out) return fail(CE_EINVAL, "NULL argument");
+    std::lock_guard<std::mutex> g(const_cast<ce_pool *>(pl)->mu);
+    *out = 0;
+    for (const ClassTable &t : pl->classes) *out += t.res_kernel != nullptr && !pl->no_resident;
+    return CE_OK;
+}
+
 ce_status ce_pool_get_info(const ce_pool *pl, ce_pool_info *out)
 {
     if (!pl || !out) return fail(CE_EINVAL, "NULL argument");
