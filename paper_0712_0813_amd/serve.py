@@ -83,12 +83,9 @@ def ensemble_member_launch(lat: Lattice, precision: int = ce.CE_FP32):
     return autotune.lookup(lat.dims, lat.N, lat.nfields, precision, pool=True)
 
 
-def tuned_member_launch(lat: Lattice, precision: int = ce.CE_FP32):
-    """The launch of the server's members: tall tiles, one per block (columns
-    of up to 64 planes, units of up to 64 rows).  Its admission threads work
-    beside the blocks, and only these tilings have carried the whole serving
-    stream: with finer ones two runs ended in a host fault whose cause was not
-    found.  None where no such tiling fits: the pool's default."""
+def tall_member_launch(lat: Lattice):
+    """Columns of up to 64 planes, units of up to 64 rows, one a block; None
+    where no such tiling fits."""
     n = lat.N
     if lat.dims == 2 and n % 256 == 0:
         rows = 64
@@ -109,6 +106,21 @@ def tuned_member_launch(lat: Lattice, precision: int = ce.CE_FP32):
                     return (ce.CE_KERNEL_TILED3D, 4, lanes, 256, z, tiles)
                 z *= 2
     return None
+
+
+def tuned_member_launch(lat: Lattice, precision: int = ce.CE_FP32):
+    """The launch of the server's members: the cached tuned one if its tiles
+    are as tall as tall_member_launch's, else that.  The server's admission
+    threads work beside the blocks, and only tall tilings have carried the
+    whole serving stream: with finer ones two runs ended in a host fault whose
+    cause was not found (the tuner's choice for an ensemble from one thread is
+    such a finer one).  None where no tall tiling fits: the pool's default,
+    whose tiles the pool works in tall blocks beside other threads."""
+    tall = tall_member_launch(lat)
+    cached = ensemble_member_launch(lat, precision)
+    if tall is not None and cached is not None and cached[0] == tall[0] and cached[4] >= tall[4]:
+        return cached
+    return tall
 
 
 def run_batched(lattices: Sequence[Lattice], inputs, steps: int, block: int = 50,
