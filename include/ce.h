@@ -248,7 +248,9 @@ ce_status ce_get_step(const ce_sim *s, int64_t *step);
 /* Kernel launch configuration of the per-step pass.  The volume sums are
  * reduced in an order fixed by this configuration, so results are bitwise
  * reproducible for a given configuration and agree to rounding across them. */
-enum { CE_KERNEL_DIRECT = 0,    /* one quad of 4 x-sites per thread, neighbours from cache; any dims */
+enum { CE_KERNEL_DIRECT = 0,    /* one quad of 4 x-sites per thread, neighbours from cache; any dims.
+                                   FP32 cubes of edge 84 to 124 that 32 does not divide run on tiles
+                                   that need not divide the edge instead, their sums kept per tile */
        CE_KERNEL_TILED3D = 1,   /* 3-D z-streaming through an LDS plane tile */
        CE_KERNEL_STREAM2D = 2 };/* 2-D y-streaming, one 256-site x segment per wavefront; N % 256 == 0 */
 typedef struct {

@@ -163,9 +163,9 @@ ce_status note_thread(ce_pool *pl)
 // Blocks of a member in a pool that several threads use: those of the tallest
 // tiling of its tile shape, columns of up to 64 planes or units of up to 64
 // rows (two blocks at least).  Each works the tiles or groups of such a column
-// one after the other; sums are kept per tile or group, so the results are those of one
-// block each.  (us a pool step, tall blocks and one a tile: 16 x 64^3 x 2: 138
-// and 42, 256 x 64^3 x 2: 524 and 467, 16 x 1024^2 x 2: 139 and 121.)
+// one after the other; sums are kept per tile or group, so the results are those
+// of one block each.  (us a pool step, tall blocks and one a tile: 16 x 64^3 x 2:
+// 162 and 42, 256 x 64^3 x 2: 503 and 467, 16 x 1024^2 x 2: 130 and 121.)
 int tall_blocks(const Lattice &L)
 {
     if (L.kind == kTiled3d && !L.ragged && tiled_tiles(L.N, L.vec, L.lpr, L.bs, L.zc) <= L.slots) {

@@ -16,8 +16,8 @@
 //
 // Two FP32 fields, us a step, here and with one launch a step: 256^2 4.2 and
 // 9.2, 512^2 4.7 and 11.9, 1024^2 7.7 and 17.0, 2048^2 17.7 and 36.1.
-// The small ones are the exchange (2.1 us) and the tail (0.7); 2048^2 is bound
-// by the sites' instructions at one block of four wavefronts a compute unit.
+// The small ones are the exchange (2.1 us) and the tail (0.7); 2048^2 is the sites
+// at one wavefront a SIMD, which issues vector instructions in 45% of the cycles.
 #include "ce_resident.hpp"
 
 #ifndef CE_UNIT_MODEL
@@ -280,8 +280,12 @@ __global__ __launch_bounds__(kBlock + 64) void resident_stream2d_batched(const L
     });
 }
 
-// Built where p and the halo stay in registers (a block of five waves has 256
-// a thread) and the units in LDS.
+// Built where p and the halo come near the registers of a thread (a block of five
+// waves has 256) and the units in LDS.  Some spill and still beat plain launches
+// of the same units (us a step, resident and plain): two FP32 fields in sixteen
+// rows, 31 spilled, 2048^2 17.8 and 36.3; one FP64 field, 158, 17.6 and 36.6; two
+// in eight rows, 205, 1280^2 20.9 and 31.9.  Where they do not, they are not taken
+// (resident_pays).
 template <typename T, int NF, int R>
 constexpr bool built()
 {

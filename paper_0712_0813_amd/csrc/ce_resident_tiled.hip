@@ -16,9 +16,10 @@
 // pass, so a step taken here is bitwise a step taken there.
 //
 // Two FP32 fields, us a step, here and with one launch a step: 64^3 4.9 and
-// 13.4, 96^3 8.1 and 19.4, 128^3 10.5 and 29.3.  Of 10.5, the sites take 6.9 (bound by
-// their instructions, as many as two wavefronts a SIMD can issue), exchange and
-// tail the rest.
+// 13.4, 96^3 8.1 and 19.4, 128^3 10.5 and 29.3.  Of 10.5, the sites take 6.9, exchange
+// and tail the rest.  With one wavefront of sites a SIMD, vector instructions are
+// issued in 42% of the cycles (128^3; 47% in a pool of 64^3): bound by the latency
+// of dependent instructions, LDS and the exchange, not by their number.
 #include "ce_resident.hpp"
 
 #ifndef CE_UNIT_MODEL
@@ -297,8 +298,9 @@ __device__ __forceinline__ void resident_tiled_body(const Lattice &lat, int src,
     }
 }
 
-// Waves per SIMD aimed at: three leave 168 registers, and two blocks of a pool
-// on a compute unit, one working its sites while the other exchanges its sums.
+// Waves per SIMD aimed at: three leave 168 registers and room for two blocks on a
+// compute unit, where the state of a thread is small enough (two FP32 fields in
+// eight planes take 243 registers and get one).
 template <typename T, int NF, int BS, int ZP>
 constexpr int waves_wanted()
 {
@@ -322,8 +324,12 @@ resident_tiled_batched(const Lattice *lats, int n, int nblk, int k, Start start)
     });
 }
 
-// Built where p and the halo stay in registers (a block of five waves has 256
-// a thread, one of nine 168) and the tile in LDS.
+// Built where p and the halo come near the registers of a thread (a block of five
+// waves has 256, one of nine 168: the service wave is the one too many) and the
+// tile in LDS.  Some spill and still beat plain launches of the same tiling (us a
+// step, resident and plain): three FP64 fields in one plane, 90 spilled, 64^3 8.4
+// and 27.5, in two planes, 200, 14.2 and 23.7; three FP32 fields in eight planes,
+// 102, 128^3 22.4 and 35.7.
 template <typename T, int NF, int VEC, int LPR, int BS, int ZP>
 constexpr bool built()
 {
