@@ -287,7 +287,11 @@ ce_status trim_cache(ce_pool *pl, size_t want)
 // The resident form of a class, if it has one and it pays: every member the
 // same tiles, and enough members that their tiles fill half the compute units
 // or nothing else to run beside them (resident launches of different classes
-// follow one another).
+// follow one another, batched ones run side by side: us a pool step beside three
+// other classes, resident and batched: 4 x 64^3 x 2 fields, 128 tiles, 22.1 and
+// 39.3; 16 x 64^3 33.2 and 51.8; 8 x 512^2, 128 tiles, 27.9 and 36.7; beside one
+// other 23.8 and 34.3, 33.0 and 47.8, 31.5 and 33.2; a smaller class, which costs
+// the batched launches little, 3 x 64^3 38.0, stays with them)
 void plan_resident_class(ClassTable &t, int cus, bool only)
 {
     const Lattice &p = t.proto;

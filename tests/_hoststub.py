@@ -35,7 +35,16 @@ def sim(dims, N, nf, **kw):
 """
 
 
+_built = []   # one library serves every module of a run
+
+
 def build(folder) -> str:
+    if not _built:
+        _built.append(_build(folder))
+    return _built[0]
+
+
+def _build(folder) -> str:
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc is not available")
